@@ -23,7 +23,8 @@ int run_gemm(int dtype, int impl, const GemmDesc& d, void* stream) {
   if (d.M <= 0 || d.N <= 0 || d.K <= 0 || !d.A || !d.B || !d.C) return BAMBOO_E_ARG;
   hipStream_t s = (hipStream_t)stream;
   if (impl == 1) return finish(launch_gemm_simple(s, dtype, d));
-  if (impl == 2) return dtype == 1 ? finish(launch_gemm_mfma(s, d)) : BAMBOO_E_STATE;
+  // the forced kernel takes whole groups of 8 in every dimension; the automatic choice has no such limit on rows
+  if (impl == 2) return dtype == 1 && d.M % 8 == 0 && d.K % 8 == 0 ? finish(launch_gemm_mfma(s, d)) : BAMBOO_E_STATE;
   if (impl != 0) return BAMBOO_E_ARG;
   return finish(launch_gemm(s, dtype, d));
 }

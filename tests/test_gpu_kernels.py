@@ -148,6 +148,39 @@ def test_mfma_kernel_refuses_what_it_does_not_cover(B):
     assert e.value.status == B.E_STATE
 
 
+@pytest.mark.parametrize("T", [1, 7, 63, 65, 129, 333])
+@pytest.mark.parametrize("K,N", [(8, 8), (56, 1032), (200, 392), (1024, 264)])
+def test_any_row_count_and_contraction_tail(B, T, K, N):
+    """Token counts that divide by nothing and contraction lengths that end inside a 64-deep slice (the missing part
+    is loaded as zeros), in every form and tile shape; the row behind the output stays untouched.  Bound: the
+    results round once to bf16 (2^-9 relative per element, so relative L2 below it), the weight gradient sums
+    T products in fp32 (T 2^-24 relative to the sum of magnitudes at most; 1e-5 leaves an order of magnitude)."""
+    rng = np.random.default_rng(T * 31 + K + N)
+    X, W = _mk(rng, (T, K), 1), _mk(rng, (K, N), 1, 0.05)
+    b, dY, Mu = _mk(rng, (N,), 1, 0.1), _mk(rng, (T, N), 1), _mk(rng, (T, K), 1)
+    Xd, Wd, bd, dYd, Md = (_dev(B, a, 1) for a in (X, W, b, dY, Mu))
+    h = X.astype(np.float64) @ W.astype(np.float64) + b
+    dx = dY.astype(np.float64) @ W.astype(np.float64).T
+    dw = X.astype(np.float64).T @ dY.astype(np.float64)
+    try:
+        for tile in (0, 11, 22, 24, 42, 44):
+            B.bk_gemm_tile(tile)
+            Y, G, dX = (torch.full((T + 1, n), 7.0, device=DEV).to(torch.bfloat16) for n in (N, N, K))
+            dW, dWg = torch.zeros(K, N, device=DEV), torch.zeros(K, N, device=DEV)
+            B.bk_linear_fwd(Xd, Wd, bd, Y[:T])
+            assert rel_l2(B.to_host(Y[:T]), h) < 2.0 ** -8 and bool((Y[T] == 7).all())
+            B.bk_linear_fwd(Xd, Wd, bd, Y[:T], gelu_out=G[:T])
+            assert rel_l2(B.to_host(G[:T]), L.gelu(h)) < 2.0 ** -7 and bool((G[T] == 7).all())   # and the table's bf16 argument
+            B.bk_linear_bwd_input(dYd, Wd, dX[:T], mul=Md)
+            assert rel_l2(B.to_host(dX[:T]), dx * Mu) < 2.0 ** -8 and bool((dX[T] == 7).all())
+            B.bk_linear_bwd_weight(Xd, dYd, dW)
+            assert rel_l2(dW.cpu().numpy(), dw) < 1e-5
+            B.bk_linear_bwd_weight_group([Xd], [dYd], [dWg])
+            assert torch.equal(dWg, dW)
+    finally:
+        B.bk_gemm_tile(0)
+
+
 @pytest.mark.parametrize("dtype,impl", IMPLS)
 @pytest.mark.parametrize("T,N,K", GEMM_SHAPES)
 def test_linear_backward_variants(B, dtype, impl, T, N, K):
