@@ -104,6 +104,8 @@ struct GemmDesc {
   // take whatever CUs it leaves idle, so the tile that costs the least CU time is the best one, not the
   // one that finishes first on an empty chip.
   int shared_chip;
+  // 1: only the kernel whose output tile bk_gemm_tile chooses (the one that adds up K in one chain per tile)
+  int tiled_only;
 };
 
 // Ordered final sums of partial rows (see launch_grad_reduce below): out0[c] += sum_y p0[y][c] over `parts`
@@ -125,6 +127,8 @@ struct GemmGroup {
 // dtype: 0 fp32, 1 bf16 (enum bamboo_dtype).  All launchers return hipError_t
 // from the launch and never synchronise.
 hipError_t launch_gemm_simple(hipStream_t s, int dtype, const GemmDesc& d);
+// fp32 MFMA path; hipErrorNotSupported when neither stride of an operand is 1
+hipError_t launch_gemm_f32(hipStream_t s, const GemmDesc& d);
 // bf16 MFMA path; returns hipErrorNotSupported when the shape is not covered.
 hipError_t launch_gemm_mfma(hipStream_t s, const GemmDesc& d);
 hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& d);

@@ -1,0 +1,135 @@
+// fp32 GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation) for the fp32
+// configuration.  One wavefront owns a 32 x 32 output tile and takes its operands straight from memory: a 32-bit
+// matrix instruction works 64 clocks on two fragments, so the vector L1 feeds all four SIMDs without LDS in
+// between.  Which k a fragment register stands for is free as long as both operands agree: lane l of a step of 8
+// holds row (column) l % 32 and k = 4 * (l / 32) .. + 3, i.e. one 16-byte load of a K-contiguous operand, and four
+// loads of 128 contiguous bytes per half-wave of a row-contiguous one; register j of both feeds instruction j.
+//
+// A layer of the fp32 configuration has 32 tokens and matrices of 64 x 64 to 64 x 256: a launch is a handful of
+// tiles, and its time is the serial chain through K.  So the NW wavefronts of a workgroup share ONE tile and take
+// every NW-th step; their partial tiles are summed through LDS in wavefront order.  Larger outputs (more tiles than
+// wavefront slots) take one wavefront per tile instead.
+#include "common.h"
+
+namespace bamboo {
+
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// Four k values (kb .. kb+3) of row `row`; KC: contraction index contiguous.  Zero beyond the edges.
+template <bool KC, bool VEC>
+__device__ __forceinline__ f32x4 frag4(const float* p, long s_row, long s_k, int row, int rows, int kb, int K) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (row >= rows) return v;
+  if (KC) {
+    const float* q = p + (long)row * s_row + kb;
+    if (VEC) {                                    // K a multiple of 4 and 16-byte rows
+      if (kb < K) v = *(const f32x4*)q;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) if (kb + j < K) v[j] = q[j];
+    }
+  } else {
+    const float* q = p + (long)kb * s_k + row;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) if (kb + j < K) v[j] = q[(long)j * s_k];
+  }
+  return v;
+}
+
+__device__ __forceinline__ void epilogue1(const GemmDesc& d, int m, int n, float acc) {
+  const long i = (long)m * d.N + n;
+  float* C = (float*)d.C;
+  switch (d.epi) {
+    case EPI_STORE: C[i] = acc; break;
+    case EPI_BIAS: C[i] = acc + ((const float*)d.bias)[n]; break;
+    case EPI_BIAS_RES: C[i] = acc + ((const float*)d.bias)[n] + ((const float*)d.res)[i]; break;
+    case EPI_BIAS_GELU: {
+      const float h = acc + ((const float*)d.bias)[n];
+      C[i] = gelu_grad_f(h);
+      ((float*)d.aux_out)[i] = gelu_f(h);
+      break;
+    }
+    case EPI_RES: C[i] = acc + ((const float*)d.res)[i]; break;
+    case EPI_MUL: C[i] = acc * ((const float*)d.aux_in)[i]; break;
+    case EPI_ACC_F32: C[i] += acc; break;
+  }
+}
+
+constexpr int kStepK = 8;      // k of one step (four matrix instructions)
+constexpr int kAhead = 4;      // steps whose operands a wavefront requests together
+
+// SPLIT: the workgroup's NW wavefronts share one tile; otherwise each has a tile of its own.
+template <bool A_K, bool B_K, bool VEC, int NW, bool SPLIT>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmDesc d) {
+  __shared__ float part[SPLIT ? NW : 1][SPLIT ? 32 * 33 : 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int tiles_n = (d.N + 31) / 32, tiles = ((d.M + 31) / 32) * tiles_n;
+  const int tile = SPLIT ? (int)blockIdx.x : (int)blockIdx.x * NW + wave;
+  if (!SPLIT && tile >= tiles) return;
+  const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
+  const float* A = (const float*)d.A;
+  const float* B = (const float*)d.B;
+  const int row = m0 + (lane & 31), col = n0 + (lane & 31), kh = 4 * (lane >> 5);
+  f32x16 acc = {};
+  const int first = SPLIT ? wave : 0, stride = SPLIT ? NW : 1;
+  const int steps = (d.K + kStepK - 1) / kStepK;
+  for (int s0 = first; s0 < steps; s0 += stride * kAhead) {
+    f32x4 a[kAhead], b[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int kb = (s0 + u * stride) * kStepK + kh;      // beyond K: zeros
+      a[u] = frag4<A_K, VEC>(A, d.a_sm, d.a_sk, row, d.M, kb, d.K);
+      b[u] = frag4<B_K, VEC>(B, d.b_sn, d.b_sk, col, d.N, kb, d.K);
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][j], b[u][j], acc, 0, 0, 0);
+  }
+  // D[row][col]: lane holds col = lane % 32, rows 8 * (r / 4) + 4 * (lane / 32) + r % 4
+  if (SPLIT) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[wave][(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 33 + (lane & 31)] = acc[r];
+    __syncthreads();
+    for (int o = threadIdx.x; o < 1024; o += 64 * NW) {
+      const int m = m0 + (o >> 5), n = n0 + (o & 31);
+      float s = part[0][(o >> 5) * 33 + (o & 31)];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) s += part[w][(o >> 5) * 33 + (o & 31)];
+      if (m < d.M && n < d.N) epilogue1(d, m, n, s);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), n = n0 + (lane & 31);
+      if (m < d.M && n < d.N) epilogue1(d, m, n, acc[r]);
+    }
+  }
+}
+
+template <bool A_K, bool B_K, bool VEC>
+static hipError_t launch(hipStream_t s, const GemmDesc& d) {
+  const long tiles = (long)((d.M + 31) / 32) * ((d.N + 31) / 32);
+  if (tiles <= 1024) {
+    hipLaunchKernelGGL((gemm_f32_kernel<A_K, B_K, VEC, 8, true>), dim3((unsigned)tiles), dim3(512), 0, s, d);
+  } else {
+    hipLaunchKernelGGL((gemm_f32_kernel<A_K, B_K, VEC, 4, false>), dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, s, d);
+  }
+  return hipGetLastError();
+}
+
+// any M, N, K and the operand strides of the three forms a layer needs
+hipError_t launch_gemm_f32(hipStream_t s, const GemmDesc& d) {
+  if (d.M <= 0 || d.N <= 0) return hipSuccess;
+  const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1;
+  if ((!a_k && d.a_sm != 1) || (!b_k && d.b_sn != 1)) return hipErrorNotSupported;
+  const bool vec = d.K % 4 == 0 && (!a_k || (d.a_sm % 4 == 0 && ((uintptr_t)d.A & 15) == 0)) &&
+                   (!b_k || (d.b_sn % 4 == 0 && ((uintptr_t)d.B & 15) == 0));
+  if (a_k && !b_k) return vec ? launch<true, false, true>(s, d) : launch<true, false, false>(s, d);
+  if (a_k && b_k) return vec ? launch<true, true, true>(s, d) : launch<true, true, false>(s, d);
+  if (!a_k && !b_k) return launch<false, false, false>(s, d);
+  return launch<false, true, false>(s, d);
+}
+
+}  // namespace bamboo

@@ -148,11 +148,14 @@ def test_mfma_kernel_refuses_what_it_does_not_cover(B):
     assert e.value.status == B.E_STATE
 
 
-@pytest.mark.parametrize("T", [1, 7, 63, 65, 129, 333])
-@pytest.mark.parametrize("K,N", [(8, 8), (56, 1032), (200, 392), (1024, 264)])
+@pytest.mark.parametrize("T,K,N", [
+    # few output tiles: the kernels whose wavefronts split K, at the edges of their 32 / 64 tiles and of K's slices
+    (1, 8, 8), (7, 56, 1032), (31, 1024, 264), (33, 520, 40), (129, 4096, 72), (333, 1096, 1024), (999, 1024, 1032),
+    # many: the tiled kernels (every shape is forced below)
+    (2077, 200, 1032), (2049, 56, 1160), (1999, 1032, 1544)])
 def test_any_row_count_and_contraction_tail(B, T, K, N):
     """Token counts that divide by nothing and contraction lengths that end inside a 64-deep slice (the missing part
-    is loaded as zeros), in every form and tile shape; the row behind the output stays untouched.  Bound: the
+    is loaded as zeros), in every form; the row behind the output stays untouched.  Bound: the
     results round once to bf16 (2^-9 relative per element, so relative L2 below it), the weight gradient sums
     T products in fp32 (T 2^-24 relative to the sum of magnitudes at most; 1e-5 leaves an order of magnitude)."""
     rng = np.random.default_rng(T * 31 + K + N)
@@ -315,3 +318,30 @@ def test_attention_forward_backward(B, dtype, impl, causal, batch, seq, heads, d
     floor = float(np.sqrt(np.mean(dqkv_ref ** 2))) if seq == 1 else 0.0
     for name, sl in (("dq", slice(0, H)), ("dk", slice(H, 2 * H)), ("dv", slice(2 * H, 3 * H))):
         assert_close(got[:, sl], dqkv_ref[:, sl], TOL[dtype], "kernels got[:, sl] %s" % (name,), floor=floor)
+
+
+@pytest.mark.parametrize("T,K,N", [(1, 1, 1), (31, 33, 65), (32, 64, 256), (100, 72, 200), (513, 130, 2049)])
+def test_fp32_matrix_core_gemm(B, T, K, N):
+    """The fp32 kernel at tile and step edges, unaligned lengths (no 16-byte loads) and on both sides of its split of K
+    over wavefronts.  Bound: a sum of n products in fp32 is off by at most n 2^-24 of the sum of magnitudes, far less in
+    relative L2; 1e-6 + n 2^-24 covers it."""
+    rng = np.random.default_rng(T + K + N)
+    X, W = rng.standard_normal((T, K)).astype(np.float32), rng.standard_normal((K, N)).astype(np.float32)
+    b, R = rng.standard_normal(N).astype(np.float32), rng.standard_normal((T, N)).astype(np.float32)
+    dY, Mu = rng.standard_normal((T, N)).astype(np.float32), rng.standard_normal((T, K)).astype(np.float32)
+    Xd, Wd, bd, Rd, dYd, Md = (torch.from_numpy(a).to(DEV) for a in (X, W, b, R, dY, Mu))
+    f = lambda a: a.astype(np.float64)
+    tol = lambda n: 1e-6 + n * 2.0 ** -24
+    Y, G, dX, dW = (torch.empty(*s, device=DEV) for s in ((T, N), (T, N), (T, K), (K, N)))
+    h = f(X) @ f(W) + b
+    B.bk_linear_fwd(Xd, Wd, bd, Y, res=Rd)
+    assert rel_l2(B.to_host(Y), h + R) < tol(K)
+    B.bk_linear_fwd(Xd, Wd, bd, Y, gelu_out=G)
+    # 1 + erf cancels for negative h: GELU and its derivative are off by an fp32 ulp of h resp. of 1, whatever their value
+    for got, want, size in ((G, L.gelu(h), h), (Y, L.gelu_grad(h), np.maximum(np.abs(h), 1.0))):
+        assert np.linalg.norm(B.to_host(got) - want) < tol(K) * np.linalg.norm(size)
+    B.bk_linear_bwd_input(dYd, Wd, dX, mul=Md)
+    assert rel_l2(B.to_host(dX), (f(dY) @ f(W).T) * Mu) < tol(N)
+    dW.fill_(1.0)
+    B.bk_linear_bwd_weight(Xd, dYd, dW)
+    assert rel_l2(dW.cpu().numpy(), 1.0 + f(X).T @ f(dY)) < tol(T)
