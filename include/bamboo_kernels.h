@@ -9,7 +9,8 @@
  * hipStream_t passed as void*.  Calls enqueue and return.  dtype: 0 fp32,
  * 1 bf16 storage with fp32 accumulation.  impl: 0 automatic (MFMA kernel when it
  * covers the shape, vector-ALU kernel otherwise), 1 vector-ALU kernel,
- * 2 MFMA kernel (BAMBOO_E_STATE if it does not cover the shape).
+ * 2 bf16 MFMA kernel, matrix products with one K chain per output tile (BAMBOO_E_STATE if it does not cover the
+ * shape; matrix products: every dimension a multiple of 8).  fp32 matrix products run on the matrix cores too (impl 0).
  * Return: 0 or a negative bamboo_status (see bamboo_stage.h).
  * Tensors are row-major; "tokens" T = batch * seq.
  */
@@ -44,7 +45,7 @@ int bk_linear_bwd_weight(int dtype, int impl, int T, int K, int N, const void* X
 
 /* n (1..4) independent weight gradients in one go: dW[i][K[i],N[i]] (fp32) += X[i][T[i],K[i]]^T dY[i][T[i],N[i]].
  * T, K, N: host int arrays; X, dY, dW: host arrays of device pointers.  Where the MFMA kernel covers all
- * of them with one tile shape (bf16, T a multiple of 64 and >= 192, K and N multiples of 8) they run as
+ * of them with one tile shape (bf16, any T, K and N multiples of 8) they run as
  * ONE launch whose workgroups are dealt over the problems, so that problems that do not fill the chip on
  * their own share its rounds; otherwise one launch each.  The results do not depend on which. */
 int bk_linear_bwd_weight_group(int dtype, int n, const int* T, const int* K, const int* N, const void* const* X,

@@ -729,6 +729,250 @@ static hipError_t launch_pl(hipStream_t s, const GemmDesc& d, int tiles) {
   return hipGetLastError();
 }
 
+// ---- few output tiles, long contraction: the wavefronts of a workgroup split K ------------------
+// A micro-batch of a few hundred tokens gives the products of a layer 30 to 250 tiles of 64 x 64 or less, so a launch
+// is one round whose time is the serial walk through K (K = 4096: 64 slices at 0.4 us, a workgroup barrier and a
+// load round trip each), while most matrix pipes idle.  Here every wavefront of a workgroup works on the SAME
+// tile, 32 x 32 with eight wavefronts or 64 x 64 with four, and takes every NW-th slice through a ring of two
+// buffers of its own, with no barrier before the end, so all their loads are in flight side by side; the partial
+// tiles are summed through LDS in wavefront order (deterministic).  Bound by the vector L1 (64 bytes per clock:
+// 4 us of a 128 x 1024 x 4096 launch) and the latency of the few round trips left.  See choose_split for figures.
+template <int ROWS>
+struct WvK {                       // K-contiguous operand: ROWS x 64, the placement of PlK, copied by one wavefront
+  static constexpr int NLOAD = ROWS / 8;
+  static constexpr int BYTES = ROWS * BK * 2;
+  __device__ static __forceinline__ int chunk(int i) {
+    const int l = threadIdx.x & 63;
+    return (l & 7) ^ ((4 * i + (l >> 4)) & 7);
+  }
+  __device__ static __forceinline__ void load_offsets(unsigned (&off)[NLOAD], long ld, int row0, int row_lim) {
+    const int l = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      const int row = min(row0 + i * 8 + (l >> 3), row_lim - 1) - row0;
+      off[i] = (unsigned)((long)row * ld * 2 + (chunk(i) << 4));
+    }
+  }
+  __device__ static __forceinline__ void mask_tail(unsigned (&off)[NLOAD], int rem) {
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) off[i] = chunk(i) * 8 < rem ? off[i] : kBufOutside;
+  }
+  __device__ static __forceinline__ bf16x8 frag(unsigned lds_base, int blk, int ks) {
+    const int l = threadIdx.x & 63;
+    return *(lds_bf16x8_ptr)(lds_base + (blk * 32 + (l & 31)) * (BK * 2) + (((2 * ks + (l >> 5)) ^ ((l >> 1) & 7)) << 4));
+  }
+};
+template <int ROWS>
+struct WvMN {                      // row-contiguous operand: 64 k-rows x ROWS, the placement of PlMN
+  static constexpr int NLOAD = ROWS / 8;
+  static constexpr int BYTES = ROWS * BK * 2;
+  static constexpr int CPR = ROWS / 8;
+  static_assert(ROWS == 32 || ROWS == 64, "");
+  // rows of 64 bytes: four consecutive k-rows fill the bank line by themselves; rows of 128: see PlMN
+  __device__ static __forceinline__ int swz(int k) { return ROWS == 64 ? 4 * ((k >> 1) & 1) : 0; }
+  __device__ static __forceinline__ int krow(int i) { return (i * 64 + ((int)threadIdx.x & 63)) / CPR; }
+  __device__ static __forceinline__ void load_offsets(unsigned (&off)[NLOAD], long ld, int row0, int row_lim) {
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      const int p = (threadIdx.x & 63) % CPR, kr = krow(i);
+      const int col = min(row0 + ((p ^ swz(kr)) << 3), row_lim - 8) - row0;
+      off[i] = (unsigned)((long)kr * ld * 2 + col * 2);
+    }
+  }
+  __device__ static __forceinline__ void mask_tail(unsigned (&off)[NLOAD], int rem) {
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) off[i] = krow(i) < rem ? off[i] : kBufOutside;
+  }
+  __device__ static __forceinline__ bf16x8 frag(unsigned lds_base, int blk, int ks) {
+    const int l = threadIdx.x & 63, i = l & 15;
+    const int k = ks * 16 + (l >> 5) * 8 + (i >> 2), col = blk * 32 + ((l >> 4) & 1) * 16 + (i & 3) * 4;
+    const unsigned a = lds_base + k * ROWS * 2 + (((col >> 3) ^ swz(k)) << 4) + (col & 7) * 2;
+    union { short4_t s4[2]; bf16x8 b; } u;
+    u.s4[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(a));
+    u.s4[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(a + 4 * ROWS * 2));   // k + 4: the same swizzle
+    return u.b;
+  }
+};
+
+// operands the epilogue of one 8-output chunk reads from memory
+template <int EPI>
+struct ChunkOperands {
+  bf16x8 bias, pre;
+  __device__ __forceinline__ void fetch(const GemmDesc& d, int m, int n) {
+    if (m >= d.M || n >= d.N) return;
+    if (EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU) bias = *(const bf16x8*)((const bf16_t*)d.bias + n);
+    if (EPI == EPI_BIAS_RES || EPI == EPI_RES) pre = *(const bf16x8*)((const bf16_t*)d.res + (long)m * d.N + n);
+    if (EPI == EPI_MUL) pre = *(const bf16x8*)((const bf16_t*)d.aux_in + (long)m * d.N + n);
+  }
+};
+
+template <int T32, int NW, bool B_K, int EPI>
+struct SmemSplit {
+  static constexpr int TILE = 32 * T32;
+  static constexpr int STAGE = 2 * TILE * BK * 2;              // bytes of one slice of A and B
+  static constexpr int LD = TILE + 4;                           // floats per row of a partial tile
+  static constexpr int RING = NW * 2 * STAGE, PART = NW * TILE * LD * 4;
+  static constexpr int TABLE_OFF = RING > PART ? RING : PART;
+  static constexpr int BYTES = TABLE_OFF + (EPI == EPI_BIAS_GELU ? kGeluBytes : 0);
+};
+
+template <int T32, int NW, bool B_K, int EPI>
+__global__ __launch_bounds__(64 * NW) void gemm_mfma_split_kernel(GemmDesc d) {
+  typedef SmemSplit<T32, NW, B_K, EPI> SM;
+  constexpr int TILE = SM::TILE, LD = SM::LD;
+  typedef WvK<TILE> OpA;
+  typedef typename std::conditional<B_K, WvK<TILE>, WvMN<TILE>>::type OpB;
+  constexpr int NL = OpA::NLOAD + OpB::NLOAD;
+  constexpr int CH = TILE / 8, CHUNKS = TILE * CH;              // 8-output chunks: per row, per tile
+  constexpr int PER = (CHUNKS + 64 * NW - 1) / (64 * NW);       // per thread
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int tiles_m = (d.M + TILE - 1) / TILE, tiles_n = (d.N + TILE - 1) / TILE;
+  int tm, tn;
+  tile_walk(xcd_range(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, &tm, &tn);
+  const int m0 = tm * TILE, n0 = tn * TILE;
+  const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem_raw;
+  const unsigned ring = lds0 + wave * 2 * SM::STAGE;
+
+  // everything the epilogue reads is requested first: older than the slice loads, hence covered by their waits
+  ChunkOperands<EPI> ops[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int idx = threadIdx.x + q * 64 * NW;
+    if (CHUNKS >= 64 * NW || idx < CHUNKS) ops[q].fetch(d, m0 + idx / CH, n0 + (idx % CH) * 8);
+  }
+  if (EPI == EPI_BIAS_GELU) {
+    for (int c0 = wave * 64; c0 < kGeluBytes / 16; c0 += 64 * NW)
+      gload_lds16((unsigned)(lane << 4), (const char*)g_gelu_table + (long)c0 * 16, lds0 + SM::TABLE_OFF + c0 * 16);
+  }
+  BAMBOO_SCHED_FENCE();
+
+  unsigned offA[OpA::NLOAD], offB[OpB::NLOAD];
+  OpA::load_offsets(offA, d.a_sm, m0, d.M);
+  const long ldb = B_K ? d.b_sn : d.b_sk;
+  OpB::load_offsets(offB, ldb, n0, d.N);
+  const long stepA = BK * 2, stepB = B_K ? BK * 2 : BK * ldb * 2;
+  buf_rsrc rA = make_rsrc((const char*)((const bf16_t*)d.A + (long)m0 * d.a_sm) + wave * stepA);
+  buf_rsrc rB = make_rsrc((const char*)((const bf16_t*)d.B + (B_K ? (long)n0 * ldb : (long)n0)) + wave * stepB);
+  int rem = d.K - wave * BK;                                    // contraction left from this wavefront's next slice on
+  const int mine = rem <= 0 ? 0 : (rem + NW * BK - 1) / (NW * BK);
+  auto issue = [&](unsigned stage) __attribute__((always_inline)) {
+    if (rem < BK) {
+      OpA::mask_tail(offA, rem);
+      OpB::mask_tail(offB, rem);
+    }
+    rem -= NW * BK;
+#pragma unroll
+    for (int i = 0; i < OpA::NLOAD; ++i) bload_lds16(offA[i], rA, ring + stage + i * 1024);
+#pragma unroll
+    for (int i = 0; i < OpB::NLOAD; ++i) bload_lds16(offB[i], rB, ring + stage + OpA::BYTES + i * 1024);
+    bump_rsrc(rA, NW * stepA);
+    bump_rsrc(rB, NW * stepB);
+  };
+  f32x16 acc[T32][T32];
+#pragma unroll
+  for (int i = 0; i < T32; ++i)
+#pragma unroll
+    for (int j = 0; j < T32; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  if (mine > 0) issue(0);
+  if (mine > 1) issue(SM::STAGE);
+  for (int s = 0; s < mine; ++s) {
+    const unsigned st = (s & 1) * SM::STAGE;
+    if (s + 1 < mine) wait_loads_and_lds<NL>();                 // the slice after this one may be in flight
+    else wait_loads_and_lds<0>();
+    asm volatile("" ::: "memory");
+    bf16x8 fa[4][T32], fb[4][T32];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int i = 0; i < T32; ++i) fa[ks][i] = OpA::frag(ring + st, i, ks);
+#pragma unroll
+      for (int j = 0; j < T32; ++j) fb[ks][j] = OpB::frag(ring + st + OpA::BYTES, j, ks);
+    }
+    if (s + 2 < mine) {
+      __builtin_amdgcn_s_waitcnt(0xc07f);                       // the reads have returned: the buffer is free
+      BAMBOO_SCHED_FENCE();
+      issue(st);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < T32; ++i)
+#pragma unroll
+        for (int j = 0; j < T32; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);                           // vmcnt(0) lgkmcnt(0): also where a wavefront had no slice
+  __syncthreads();
+  float* part = (float*)smem_raw + wave * TILE * LD;
+#pragma unroll
+  for (int i = 0; i < T32; ++i)
+#pragma unroll
+    for (int j = 0; j < T32; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        part[(i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * LD + j * 32 + (lane & 31)] = acc[i][j][r];
+  __syncthreads();
+  constexpr bool SUMS = EPI == EPI_MUL;
+  float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int idx = threadIdx.x + q * 64 * NW;
+    const int row = idx / CH, c = (idx % CH) * 8, m = m0 + row, n = n0 + c;
+    if ((CHUNKS >= 64 * NW || idx < CHUNKS) && m < d.M && n < d.N) {
+      float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {                            // partial tiles in wavefront order
+        const float* p = (const float*)smem_raw + (w * TILE + row) * LD + c;
+        const f32x4 lo = *(const f32x4*)p, hi = *(const f32x4*)(p + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { v[j] += lo[j]; v[4 + j] += hi[j]; }
+      }
+      const f32x4 none[2] = {};
+      float st8[8];
+      epilogue8<EPI>(d, m, n, v, ops[q].pre, none, ops[q].bias, lds0 + SM::TABLE_OFF, SUMS ? st8 : nullptr);
+      if (SUMS) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) cs[j] += st8[j];
+      }
+    }
+  }
+  if (SUMS && d.tile_colsum != nullptr) {                       // uniform: column sums of the stored outputs
+    // lanes of a wavefront that share the 8 columns, then the wavefronts that hold rows of the tile, in order
+#pragma unroll
+    for (int o = CH; o < 64; o <<= 1)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) cs[j] += __shfl_xor(cs[j], o, 64);
+    constexpr int WAVES = CHUNKS >= 64 * NW ? NW : CHUNKS / 64; // wavefronts that stored something
+    __syncthreads();
+    float* x = (float*)smem_raw;
+    if (wave < WAVES && lane < CH)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[wave * TILE + lane * 8 + j] = cs[j];
+    __syncthreads();
+    if (threadIdx.x < TILE && n0 + (int)threadIdx.x < d.N) {
+      float t = x[threadIdx.x];
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) t += x[w * TILE + threadIdx.x];
+      d.tile_colsum[(long)tm * d.N + n0 + threadIdx.x] = t;
+    }
+  }
+}
+
+template <int T32, int NW, bool B_K, int EPI>
+static hipError_t launch_split(hipStream_t s, const GemmDesc& d) {
+  typedef SmemSplit<T32, NW, B_K, EPI> SM;
+  constexpr auto kern = gemm_mfma_split_kernel<T32, NW, B_K, EPI>;
+  const hipError_t e = ensure_lds_attribute<kern, SM::BYTES>();
+  if (e != hipSuccess) return e;
+  const int tiles_m = (d.M + SM::TILE - 1) / SM::TILE, tiles_n = (d.N + SM::TILE - 1) / SM::TILE;
+  if (EPI == EPI_MUL && d.tile_colsum != nullptr && d.tile_colsum_parts != nullptr) *d.tile_colsum_parts = tiles_m;
+  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(64 * NW), SM::BYTES, s, d);
+  return hipGetLastError();
+}
+
 static std::atomic<int> g_forced_stages{0};      // test / tuning knob, process-wide
 int set_gemm_stages(int n) { return g_forced_stages.exchange(n); }
 
@@ -776,8 +1020,8 @@ static const TileCost kCostAcc[] = {       // fp32 read-modify-write output (wei
     {22, 3, 0.f, 0.616f, 2.88f}, {24, 2, 0.f, 1.216f, 6.12f}, {24, 3, 0.f, 1.072f, 1.03f},
     {42, 2, 0.f, 1.102f, 11.56f}, {42, 3, 0.f, 0.997f, 4.55f}, {44, 2, 0.f, 1.737f, 0.f}};
 
-static void choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, int* code, int* ns, bool offer_43 = false) {
-  const bool by_work = d.shared_chip != 0;
+static float choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, bool by_work, int* code, int* ns,
+                         bool offer_43 = false) {
   const int nk = k_slices(d.K);
   const TileCost* tab = acc_form ? kCostAcc : kCostStore;
   const int ntab = acc_form ? (int)(sizeof(kCostAcc) / sizeof(kCostAcc[0])) : (int)(sizeof(kCostStore) / sizeof(kCostStore[0]));
@@ -807,17 +1051,54 @@ static void choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, int* c
       *ns = t.ns;
     }
   }
+  return best;
+}
+
+// Whether the wavefronts of a workgroup should split K (gemm_mfma_split_kernel): 0 no, 1 with 32 x 32, 2 with
+// 64 x 64 tiles.  Estimated like the tiles above, rounds * (a + b * slices) + c, one workgroup per CU; fitted to
+// timings of 54 shapes (16 to 2048 rows, N 256 to 4096, K 1024 to 6400; microseconds, forward / input gradient):
+//     rows  N     K      tiles        split 32        split 64
+//     128   1024  1024    6.6 /  6.5    4.1 /  4.1      6.4 /  6.3
+//     128   1024  4096   31.0 / 31.2   11.9 /  8.4     16.0 / 13.7
+//     512   1024  4096   31.7 / 31.7   19.3 / 14.9     15.2 / 14.7
+//     1000  1024  4096   31.8 / 31.8   35.0 / 27.1     16.5 / 16.0
+//     1536  1024  4096   32.7 / 32.5   50.8 / 39.3     28.9 / 27.9
+//     512   3072  1024   11.0 / 10.8   22.9 / 18.4     12.9 / 12.1
+// i.e. splitting pays where one round of small tiles covers the output, and more the longer K is.  The choice depends
+// on the shape alone (not on the stream, nor on a forced tile): the sums are taken in another order than the tiles'.
+static int choose_split(const GemmDesc& d, bool b_k, long extra_lds) {
+  int code, ns;
+  float best = choose_tile(d, false, extra_lds, false, &code, &ns);
+  const int nk = k_slices(d.K);
+  int pick = 0;
+  for (int t = 1; t <= 2; ++t) {
+    const long tiles = (long)((d.M + 32 * t - 1) / (32 * t)) * ((d.N + 32 * t - 1) / (32 * t));
+    const long rounds = (tiles + 255) / 256;
+    const float cost = rounds * (t == 1 ? (b_k ? 2.7f + 0.09f * nk : 1.5f + 0.16f * nk) : 4.0f + 0.18f * nk) + 3.0f;
+    if (cost < best) {
+      best = cost;
+      pick = t;
+    }
+  }
+  return pick;
 }
 
 template <bool A_K, bool B_K, int EPI>
 static hipError_t launch_form(hipStream_t s, const GemmDesc& d) {
-  int pick, ns;
-  constexpr bool HAS_43 = A_K && !B_K && EPI == EPI_BIAS;
-  choose_tile(d, EPI == EPI_ACC_F32, EPI == EPI_BIAS_GELU ? kGeluBytes : 0, &pick, &ns, HAS_43 && !g_forced_stages);
   if (EPI == EPI_BIAS_GELU) {
     const hipError_t e = ensure_gelu_table(s);
     if (e != hipSuccess) return e;
   }
+  if constexpr (EPI != EPI_ACC_F32) {
+    switch (d.tiled_only ? 0 : choose_split(d, B_K, EPI == EPI_BIAS_GELU ? kGeluBytes : 0)) {
+      case 1: return launch_split<1, 8, B_K, EPI>(s, d);
+      case 2: return launch_split<2, 4, B_K, EPI>(s, d);
+      default: break;
+    }
+  }
+  int pick, ns;
+  constexpr bool HAS_43 = A_K && !B_K && EPI == EPI_BIAS;
+  choose_tile(d, EPI == EPI_ACC_F32, EPI == EPI_BIAS_GELU ? kGeluBytes : 0, d.shared_chip != 0, &pick, &ns, HAS_43 && !g_forced_stages);
   if (g_forced_tile) {
     pick = g_forced_tile;
     ns = 2;

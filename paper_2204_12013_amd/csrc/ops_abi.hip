@@ -17,12 +17,13 @@ int finish(hipError_t e) {
   (void)hipGetLastError();
   return e == hipErrorNotSupported ? BAMBOO_E_STATE : BAMBOO_E_HIP;
 }
-int run_gemm(int dtype, int impl, const GemmDesc& d, void* stream) {
+int run_gemm(int dtype, int impl, GemmDesc& d, void* stream) {
   (void)hipGetLastError();  // an earlier, unrelated failure in this thread must not be blamed on this launch
   if (dtype != 0 && dtype != 1) return BAMBOO_E_ARG;
   if (d.M <= 0 || d.N <= 0 || d.K <= 0 || !d.A || !d.B || !d.C) return BAMBOO_E_ARG;
   hipStream_t s = (hipStream_t)stream;
   if (impl == 1) return finish(launch_gemm_simple(s, dtype, d));
+  d.tiled_only = impl == 2;
   // the forced kernel takes whole groups of 8 in every dimension; the automatic choice has no such limit on rows
   if (impl == 2) return dtype == 1 && d.M % 8 == 0 && d.K % 8 == 0 ? finish(launch_gemm_mfma(s, d)) : BAMBOO_E_STATE;
   if (impl != 0) return BAMBOO_E_ARG;
