@@ -135,3 +135,15 @@ def test_bad_arguments_are_rejected(B):
     assert B.lib.bk_embedding_bwd(0, 16, 5, 16, 16, p(lab), p(t), p(t), p(t), None) == B.E_ARG       # tokens not a multiple of seq
     assert B.lib.bk_ordered_sum(0, p(f), 1.0, p(f), None) == B.E_ARG
     assert B.lib.bk_ordered_sum(16, None, 1.0, p(f), None) == B.E_ARG
+
+
+@pytest.mark.parametrize("dtype,V,S,Bsz,H", [(0, 1, 4097, 1, 8), (1, 300, 2500, 2, 2056)])
+def test_embedding_gradient_beyond_one_list_and_one_column_pass(B, dtype, V, S, Bsz, H):
+    """More tokens than the kernel lists at a time and more columns than a workgroup covers in one pass; one id
+    collecting every token."""
+    test_embedding_forward_and_gradient(B, dtype, V, S, Bsz, H)
+
+
+@pytest.mark.parametrize("dtype,T,V", [(1, 3, 8), (0, 2, 2056), (1, 5, 8200)])
+def test_softmax_cross_entropy_at_the_edges_of_its_vector_passes(B, dtype, T, V):
+    test_softmax_cross_entropy(B, dtype, T, V)
