@@ -212,7 +212,14 @@ __device__ __forceinline__ void epilogue8(const GemmDesc& d, int m, int n, const
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[j] = (bf16_t)v[j];
   }
-  *(bf16x8*)((bf16_t*)d.C + i) = o;
+  // Streaming stores where the next reader takes the output once (a LayerNorm, the elementwise part of a later
+  // epilogue, the backward pass): what stays dirty in the eight L2s has to be written back before the next kernel
+  // starts.  4096 x 4096 outputs, K = 1024: 37.8 -> 35.2 us per launch, all of it in the gap to the next one.
+  // Outputs that the next kernel reads as a matrix operand, many times over (Q|K|V, GELU(h), the gradient at h),
+  // stay cacheable: streaming those too gains nothing at the BERT-large-shaped iteration (22.25 against 22.30 ms,
+  // 22.52 with no streaming) and costs 1.6 % at the GPT-2-shaped one (49.92 against 49.12 ms, 49.34 with none).
+  if (EPI == EPI_BIAS || EPI == EPI_MUL) *(bf16x8*)((bf16_t*)d.C + i) = o;
+  else __builtin_nontemporal_store(o, (bf16x8*)((bf16_t*)d.C + i));
 }
 
 // Accumulators -> wavefront-private LDS rows -> 16-byte global accesses.  `first` holds the operands
@@ -372,6 +379,16 @@ struct PlK {
       off[i] = (unsigned)((long)row * ld * 2 + ((p ^ ((r >> 1) & 7)) << 4));
     }
   }
+  // half h of a 256-row operand as ROWS = 128 rows: of every 128 rows the first (h = 0) or second 64
+  __device__ static __forceinline__ void load_offsets_half(unsigned (&off)[NLOAD], long ld, int row0, int row_lim, int h) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      const int r = i * 32 + (tid >> 3), p = tid & 7;
+      const int row = min(row0 + (r >> 6) * 128 + h * 64 + (r & 63), row_lim - 1) - row0;
+      off[i] = (unsigned)((long)row * ld * 2 + ((p ^ ((r >> 1) & 7)) << 4));
+    }
+  }
   __device__ static __forceinline__ const char* base(const bf16_t* g, long ld, int row0) {
     return (const char*)(g + (long)row0 * ld);
   }
@@ -427,6 +444,16 @@ struct PlMN {
       const int c = i * 256 + tid;
       const int kr = c / CPR, p = c % CPR;
       const int col = min(row0 + (chunk_at(p, kr) << 3), row_lim - 8) - row0;
+      off[i] = (unsigned)((long)kr * ld * 2 + col * 2);
+    }
+  }
+  __device__ static __forceinline__ void load_offsets_half(unsigned (&off)[NLOAD], long ld, int row0, int row_lim, int h) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      const int c = i * 256 + tid;
+      const int kr = c / CPR, r = chunk_at(c % CPR, kr) << 3;
+      const int col = min(row0 + (r >> 6) * 128 + h * 64 + (r & 63), row_lim - 8) - row0;
       off[i] = (unsigned)((long)kr * ld * 2 + col * 2);
     }
   }
@@ -681,10 +708,202 @@ __device__ __forceinline__ void gemm_pl_body(const GemmDesc& d, int pid) {
   write_tile<WM, WN, EPI, SM::EPI_LD>(d, acc, (float*)smem_raw, m0, n0, ops, L.lds0 + SM::TABLE_OFF);
 }
 
+// ---- 256 x 256 tile: quarter-tile phases ---------------------------------------------------------
+// One 256 x 256 tile per CU reads the fewest LDS fragments and L1 bytes per matrix instruction, but two slices are
+// all the LDS holds (128 of 160 KB).  With whole slices as the unit of reuse a buffer was refilled half a slice time
+// before it was needed, less than a trip to memory: 2048 x 12288 x 49152 took 2450 us.  Here the unit is half an
+// operand slice (128 rows x 64): a wavefront works through the four quarters of its 128 x 128 in phases of 16 matrix
+// instructions,
+//     phase   multiplies   reads for later      loads (slice + 2, + 3) into what the previous phase read last
+//       1      A0 x B0      B1                   B0 (+2)
+//       2      A0 x B1      A1                   B1 (+2)
+//       3      A1 x B0      A0 of the next       A1 (+2)
+//       4      A1 x B1      B0 of the next       A0 (+3)
+// so every half is on its way for seven phases, 1.75 slice times, in the same LDS and with the same four fragment
+// register sets.  One barrier per phase tells that the half read in the phase before is free everywhere and that the
+// one to be read now has landed everywhere: 2120 us for the shape above, 97 -> 78 us for 64 tiles over K = 4096.
+// The order of the sums is that of the other tiles.
+// What bounds it now: the matrix cores at the clock the chip holds under them.  The loop is 89 % busy (2300 clocks per
+// 2048 of matrix work; taking waits and barriers out of a copy changes nothing), but the clock falls to 1.3-1.6 GHz
+// with 256 CUs on random data; without loads and LDS reads the same instructions reach 1.9 PFLOP/s, with them 1.47.
+template <bool A_K, bool B_K>
+struct PhLoop {
+  typedef typename std::conditional<A_K, PlK<128>, PlMN<128>>::type OpA;
+  typedef typename std::conditional<B_K, PlK<128>, PlMN<128>>::type OpB;
+  static constexpr int QUARTER = 16384;               // bytes of one half-operand slice: 128 rows x 64
+  static constexpr unsigned A0 = 0, A1 = QUARTER, B0 = 2 * QUARTER, B1 = 3 * QUARTER, STAGE = 4 * QUARTER;
+  unsigned offA[2][4], offB[2][4];                    // per-thread byte offsets of the halves' loads
+  unsigned tabA[4], tabB[4];                          // per-thread LDS fragment addresses inside a half
+  buf_rsrc rA, rB;                                    // based at the next slice to load
+  long stepA, stepB;
+  int remA[2], remB[2];                               // contraction left from each half's next slice on
+  unsigned lds0, wave_lds;
+
+  template <int H>
+  __device__ __forceinline__ void begin_a() {
+    if (remA[H] < BK) OpA::mask_tail(offA[H], remA[H]);
+    remA[H] -= BK;
+  }
+  template <int H>
+  __device__ __forceinline__ void begin_b() {
+    if (remB[H] < BK) OpB::mask_tail(offB[H], remB[H]);
+    remB[H] -= BK;
+  }
+  template <int H> __device__ __forceinline__ void load_a(int n, unsigned stage) const {
+    bload_lds16(offA[H][n], rA, lds0 + stage + (H ? A1 : A0) + n * 4096 + wave_lds);
+  }
+  template <int H> __device__ __forceinline__ void load_b(int n, unsigned stage) const {
+    bload_lds16(offB[H][n], rB, lds0 + stage + (H ? B1 : B0) + n * 4096 + wave_lds);
+  }
+  template <int H> __device__ __forceinline__ void issue_a(unsigned stage) {
+    begin_a<H>();
+#pragma unroll
+    for (int n = 0; n < 4; ++n) load_a<H>(n, stage);
+  }
+  template <int H> __device__ __forceinline__ void issue_b(unsigned stage) {
+    begin_b<H>();
+#pragma unroll
+    for (int n = 0; n < 4; ++n) load_b<H>(n, stage);
+  }
+};
+
+template <int N>
+__device__ __forceinline__ void phase_barrier() {
+  BAMBOO_SCHED_FENCE();
+  wait_loads_and_lds<N>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  BAMBOO_SCHED_FENCE();
+}
+
+template <bool A_K, bool B_K, int EPI>
+__device__ __forceinline__ void gemm_ph_body(const GemmDesc& d, int pid) {
+  typedef SmemPl<4, 4, 2, EPI == EPI_BIAS_GELU> SM;
+  typedef PhLoop<A_K, B_K> Loop;
+  static_assert(SM::MAIN_BYTES == 2 * Loop::STAGE, "");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  int tile_m, tile_n;
+  tile_walk(pid, (d.M + 255) / 256, (d.N + 255) / 256, &tile_m, &tile_n);
+  const int m0 = tile_m * 256, n0 = tile_n * 256;
+  const long lda = A_K ? d.a_sm : d.a_sk;
+  const long ldb = B_K ? d.b_sn : d.b_sk;
+
+  Loop L;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    Loop::OpA::load_offsets_half(L.offA[h], lda, m0, d.M, h);
+    Loop::OpB::load_offsets_half(L.offB[h], ldb, n0, d.N, h);
+    L.remA[h] = L.remB[h] = d.K;
+  }
+  Loop::OpA::frag_table(L.tabA, wm * 64);
+  Loop::OpB::frag_table(L.tabB, wn * 64);
+  L.rA = make_rsrc(Loop::OpA::base((const bf16_t*)d.A, lda, m0));
+  L.rB = make_rsrc(Loop::OpB::base((const bf16_t*)d.B, ldb, n0));
+  L.stepA = Loop::OpA::slice_bytes(lda);
+  L.stepB = Loop::OpB::slice_bytes(ldb);
+  L.lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem_raw;
+  L.wave_lds = wave * 1024;
+
+  f32x16 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const int nk = k_slices(d.K);
+  if (EPI == EPI_BIAS_GELU) {     // the table: requested ahead of the slices, covered by the first wait
+#pragma unroll
+    for (int it = 0; it < (kGeluBytes / 16 + 255) / 256; ++it) {
+      const int c0 = it * 256 + wave * 64;
+      if (c0 < kGeluBytes / 16)
+        gload_lds16((unsigned)(((threadIdx.x & 63)) << 4), (const char*)g_gelu_table + (long)c0 * 16,
+                    L.lds0 + SM::TABLE_OFF + c0 * 16);
+    }
+  }
+  EpiOperands<4, 4, EPI> ops;
+  ops.issue_bias(d, n0);
+  BAMBOO_SCHED_FENCE();
+
+  bf16x8 fa[2][4][2], fb[2][4][2];      // [half][k-step][32-row block]
+  auto read_a = [&](auto hc, int n, unsigned stage) __attribute__((always_inline)) {
+    constexpr int H = decltype(hc)::value;
+    fa[H][n >> 1][n & 1] = Loop::OpA::frag(L.tabA, L.lds0 + stage + (H ? Loop::A1 : Loop::A0), n & 1, n >> 1);
+  };
+  auto read_b = [&](auto hc, int n, unsigned stage) __attribute__((always_inline)) {
+    constexpr int H = decltype(hc)::value;
+    fb[H][n >> 1][n & 1] = Loop::OpB::frag(L.tabB, L.lds0 + stage + (H ? Loop::B1 : Loop::B0), n & 1, n >> 1);
+  };
+  // 16 matrix instructions on the quarter (HA, HB); rd(n): n-th of the 8 fragment reads for a later phase, behind the
+  // first instructions; ld(n): n-th of the 4 loads into the half whose last reader has passed
+  auto quarter = [&](auto hac, auto hbc, auto rd, auto ld) __attribute__((always_inline)) {
+    constexpr int HA = decltype(hac)::value, HB = decltype(hbc)::value;
+#pragma unroll
+    for (int n = 0; n < 16; ++n) {
+      const int ks = n >> 2, i = (n >> 1) & 1, j = n & 1;
+      acc[2 * HA + i][2 * HB + j] =
+          __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[HA][ks][i], fb[HB][ks][j], acc[2 * HA + i][2 * HB + j], 0, 0, 0);
+      if (n < 8) rd(n);
+      else if (n < 12) ld(n - 8);
+      BAMBOO_SCHED_FENCE();
+    }
+  };
+  std::integral_constant<int, 0> c0;
+  std::integral_constant<int, 1> c1;
+
+  L.template issue_a<0>(0);
+  L.template issue_b<0>(0);
+  L.template issue_b<1>(0);
+  L.template issue_a<1>(0);
+  bump_rsrc(L.rA, L.stepA);
+  bump_rsrc(L.rB, L.stepB);
+  L.template issue_a<0>(Loop::STAGE);
+  L.template issue_b<0>(Loop::STAGE);
+  L.template issue_b<1>(Loop::STAGE);
+  L.template issue_a<1>(Loop::STAGE);
+  bump_rsrc(L.rA, L.stepA);
+  bump_rsrc(L.rB, L.stepB);
+  phase_barrier<24>();                  // A0, B0 of slice 0 have landed
+#pragma unroll
+  for (int n = 0; n < 8; ++n) read_a(c0, n, 0);
+#pragma unroll
+  for (int n = 0; n < 8; ++n) read_b(c0, n, 0);
+  phase_barrier<63>();
+  L.template issue_a<0>(0);             // slice 2
+
+  unsigned cur = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    const unsigned nxt = cur ^ Loop::STAGE;
+    phase_barrier<24>();
+    L.template begin_b<0>();
+    quarter(c0, c0, [&](int n) { read_b(c1, n, cur); }, [&](int n) { L.template load_b<0>(n, cur); });
+    phase_barrier<24>();
+    L.template begin_b<1>();
+    quarter(c0, c1, [&](int n) { read_a(c1, n, cur); }, [&](int n) { L.template load_b<1>(n, cur); });
+    bump_rsrc(L.rB, L.stepB);
+    phase_barrier<24>();
+    L.template begin_a<1>();
+    quarter(c1, c0, [&](int n) { read_a(c0, n, nxt); }, [&](int n) { L.template load_a<1>(n, cur); });
+    bump_rsrc(L.rA, L.stepA);
+    phase_barrier<24>();
+    L.template begin_a<0>();
+    quarter(c1, c1, [&](int n) { read_b(c0, n, nxt); }, [&](int n) { L.template load_a<0>(n, nxt); });
+    cur = nxt;
+  }
+  // what is still on its way into the ring are zeros beyond K; every wavefront is done with it
+  phase_barrier<0>();
+  ops.issue(d, m0, n0, 0);
+  write_tile<4, 4, EPI, SM::EPI_LD>(d, acc, (float*)smem_raw, m0, n0, ops, L.lds0 + SM::TABLE_OFF);
+}
+
 template <int WM, int WN, bool A_K, bool B_K, int EPI, int NS, int MINB>
 __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_kernel(GemmDesc d) {
   constexpr int BM = 64 * WM, BN = 64 * WN;
-  gemm_pl_body<WM, WN, A_K, B_K, EPI, NS>(d, xcd_range(blockIdx.x, ((d.M + BM - 1) / BM) * ((d.N + BN - 1) / BN)));
+  const int pid = xcd_range(blockIdx.x, ((d.M + BM - 1) / BM) * ((d.N + BN - 1) / BN));
+  if constexpr (WM == 4 && WN == 4) gemm_ph_body<A_K, B_K, EPI>(d, pid);
+  else gemm_pl_body<WM, WN, A_K, B_K, EPI, NS>(d, pid);
 }
 
 // Several weight-gradient problems in one launch: workgroup b works on problem p where
@@ -716,7 +935,8 @@ __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_group_kernel(GemmGroup
       if (q > p && q < g.n) end = g.first[q];
     local = xcd_range(local, end - g.first[p]);
   }
-  gemm_pl_body<WM, WN, false, false, EPI_ACC_F32, NS>(g.d[p], local);
+  if constexpr (WM == 4 && WN == 4) gemm_ph_body<false, false, EPI_ACC_F32>(g.d[p], local);
+  else gemm_pl_body<WM, WN, false, false, EPI_ACC_F32, NS>(g.d[p], local);
 }
 
 template <int WM, int WN, bool A_K, bool B_K, int EPI, int NS>
@@ -1000,25 +1220,29 @@ int set_gemm_tile(int code) { return g_forced_tile.exchange(code); }
 
 // Tile and pipeline-depth choice.  Each candidate's run time is estimated as
 //   rounds * (a + b * slices) + c   [microseconds]
-// where rounds = ceil(tiles / (256 CUs * workgroups that fit a CU)) and slices = K / 64; a is the
-// per-tile fill and epilogue cost, b the time of one 64-deep slice, c a launch constant.  The
-// coefficients are least-squares fits to timings of the BERT-large- and GPT-2-shaped stage GEMMs
-// on an MI355X with operands that are not cache-resident (as inside a training iteration): big
-// tiles have the best MFMA : LDS ratio but need enough of them to fill the chip; two buffers leave
-// room for two workgroups per CU, which hide each other's stalls; when a CU gets one workgroup
-// anyway, a deeper ring hides the load latency instead.
+// where slices = K / 64, a is the per-tile fill and epilogue cost, b the time of one 64-deep slice, c a launch
+// constant, and rounds = tiles / (256 CUs * workgroups that fit a CU), a partial last round of a fraction f of the
+// CUs counting 0.75 + 0.25 f (with fewer matrix cores busy the clock is higher: a 256 x 256 slice takes 1.03 us on
+// 64 CUs and 1.4 us on 256).  The coefficients are fits to timings of 29 shapes (1024 to 12000 rows, N and K 512 to
+// 50304: the BERT-large-, GPT-2- and large-layer-shaped products, the LM head and generic ones) on an MI355X with
+// operands that are not cache-resident, as inside a training iteration; the candidate they pick is on average 0.6 %
+// and at most 6 % slower than the best one (2048 x 12288 x 49152: 256 x 256 tiles 2056 us, 128 x 256 2440 us).
 struct TileCost { int code, ns; float a, b, c; };
 static const TileCost kCostStore[] = {     // bf16 output (forward and input-gradient forms)
-    {11, 2, 1.96f, 0.377f, 3.94f}, {11, 4, 1.48f, 0.396f, 5.05f}, {22, 2, 5.04f, 0.949f, 0.35f},
-    {22, 3, 4.52f, 0.545f, 1.60f}, {24, 2, 4.93f, 1.068f, 5.59f}, {24, 3, 7.76f, 0.816f, 1.45f},
-    {42, 2, 1.85f, 1.107f, 8.18f}, {42, 3, 5.44f, 0.874f, 2.50f}, {44, 2, 14.98f, 1.281f, 0.58f},
+    {11, 2, 0.02f, 0.452f, 2.72f}, {11, 4, 0.35f, 0.457f, 1.55f}, {22, 2, 2.58f, 1.057f, 0.25f},
+    {22, 3, 2.05f, 0.578f, 2.21f}, {24, 3, 4.69f, 0.918f, 1.96f}, {42, 3, 4.05f, 0.934f, 2.45f},
+    {44, 2, 10.33f, 1.370f, 0.f},
     // 256 x 192 (offered for the bias-only forward form: N = 3 H of the QKV projection is 16 x 192 when
-    // H = 1024, i.e. with 4096 tokens exactly 256 tiles); coefficients scaled from the 256 x 256 tile's
-    {43, 2, 11.6f, 0.98f, 0.58f}};
+    // H = 1024, i.e. with 4096 tokens exactly 256 tiles)
+    {43, 2, 4.41f, 1.370f, 3.69f}};
 static const TileCost kCostAcc[] = {       // fp32 read-modify-write output (weight-gradient form)
-    {11, 2, 0.f, 0.487f, 1.98f}, {11, 4, 0.f, 0.504f, 0.f}, {22, 2, 0.f, 0.983f, 0.f},
-    {22, 3, 0.f, 0.616f, 2.88f}, {24, 2, 0.f, 1.216f, 6.12f}, {24, 3, 0.f, 1.072f, 1.03f},
-    {42, 2, 0.f, 1.102f, 11.56f}, {42, 3, 0.f, 0.997f, 4.55f}, {44, 2, 0.f, 1.737f, 0.f}};
+    {11, 2, 0.69f, 0.444f, 6.39f}, {11, 4, 1.88f, 0.438f, 2.32f}, {22, 2, 12.15f, 0.935f, 0.f},
+    {22, 3, 5.78f, 0.564f, 3.32f}, {24, 3, 9.21f, 0.981f, 3.42f}, {42, 3, 9.66f, 0.958f, 3.31f},
+    {44, 2, 28.80f, 1.223f, 0.f}};
+static float rounds_of(long tiles, long slots) {
+  const long full = tiles / slots, rest = tiles % slots;
+  return (float)full + (rest > 0 ? 0.75f + 0.25f * (float)rest / (float)slots : 0.f);
+}
 
 static float choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, bool by_work, int* code, int* ns,
                          bool offer_43 = false) {
@@ -1039,11 +1263,10 @@ static float choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, bool 
     const long lds = (t.ns * stage > epi ? t.ns * stage : epi) + extra_lds;
     if (lds > 160 * 1024) continue;
     const long slots = 256 * (2 * lds <= 160 * 1024 ? 2 : 1);
-    const long rounds = (tiles + slots - 1) / slots;
     // alone on the chip: rounds of tiles.  Beside another stream's kernels: CU time summed over the tiles, but
     // no shape that leaves fewer than 128 tiles where another offers more -- the launch still has to finish
     // (measured: with 64-tile launches on the second lane that lane becomes the critical path).
-    const float cost = by_work ? (float)(tiles < 128 ? 4 * 256 : tiles) * (t.a + t.b * nk) : rounds * (t.a + t.b * nk) + t.c;
+    const float cost = by_work ? (float)(tiles < 128 ? 4 * 256 : tiles) * (t.a + t.b * nk) : rounds_of(tiles, slots) * (t.a + t.b * nk) + t.c;
     if (!found || cost < best) {
       found = true;
       best = cost;
@@ -1055,7 +1278,7 @@ static float choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, bool 
 }
 
 // Whether the wavefronts of a workgroup should split K (gemm_mfma_split_kernel): 0 no, 1 with 32 x 32, 2 with
-// 64 x 64 tiles.  Estimated like the tiles above, rounds * (a + b * slices) + c, one workgroup per CU; fitted to
+// 64 x 64 tiles.  Estimated like the tiles above, rounds * (a + b * slices), one workgroup per CU; fitted to
 // timings of 54 shapes (16 to 2048 rows, N 256 to 4096, K 1024 to 6400; microseconds, forward / input gradient):
 //     rows  N     K      tiles        split 32        split 64
 //     128   1024  1024    6.6 /  6.5    4.1 /  4.1      6.4 /  6.3
@@ -1074,7 +1297,7 @@ static int choose_split(const GemmDesc& d, bool b_k, long extra_lds) {
   for (int t = 1; t <= 2; ++t) {
     const long tiles = (long)((d.M + 32 * t - 1) / (32 * t)) * ((d.N + 32 * t - 1) / (32 * t));
     const long rounds = (tiles + 255) / 256;
-    const float cost = rounds * (t == 1 ? (b_k ? 2.7f + 0.09f * nk : 1.5f + 0.16f * nk) : 4.0f + 0.18f * nk) + 3.0f;
+    const float cost = rounds * (t == 1 ? (b_k ? 2.7f + 0.09f * nk : 1.5f + 0.16f * nk) : 4.0f + 0.18f * nk);
     if (cost < best) {
       best = cost;
       pick = t;
@@ -1183,8 +1406,7 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
       tiles += ti;
       slices += (double)ti * k_slices(d[i].K);
     }
-    const long rounds = (tiles + 255) / 256;
-    const float cost = rounds * (t->a + t->b * (float)(slices / tiles)) + t->c;
+    const float cost = rounds_of(tiles, 256) * (t->a + t->b * (float)(slices / tiles)) + t->c;
     if (pick == 0 || cost < best) {
       pick = codes[c];
       best = cost;
