@@ -215,6 +215,12 @@ hipError_t launch_xent_bwd(hipStream_t s, int dtype, int T, int V, const void* l
                            const float* lse, float scale, void* dlogits);
 hipError_t launch_ordered_sum(hipStream_t s, long n, const float* in, float scale, float* out);
 
+// Whether a pass over so many bytes of distinct memory should not keep them in the caches.  Up to about the 256 MiB of
+// the memory-side cache a part is found there again by the next pass: Adam on 16 M parameters (288 MB) 67 us kept,
+// 83 us streamed; on 32 M (576 MB) 179 kept, 163 streamed; a copy between 128 MB arrays 34 against 40 us, between
+// 907 MB arrays 312 against 278 us.
+inline bool streams_past_cache(long bytes) { return bytes > (384L << 20); }
+
 // ---- optimizer ------------------------------------------------------------------
 // Adam on n parameters (n a multiple of 4): fp32 gradient g, fp32 master weights and moments m, v
 // updated in place, w = storage-dtype copy of the new master weights.  step counts from 1.

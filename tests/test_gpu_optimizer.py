@@ -162,3 +162,41 @@ def test_optimizer_misuse_is_rejected(B):
     st.stage_sync_replica(st.shadow_w)                       # weights only is allowed
     st.stage_sync()
     st.stage_destroy()
+
+
+@pytest.mark.parametrize("n", [(384 << 20) // 18 // 4 * 4, (384 << 20) // 18 // 4 * 4 + 516])
+def test_adam_on_both_sides_of_the_streaming_limit(B, n):
+    """The accesses that bypass the caches start above 384 MiB of state (18 bytes per bf16 parameter): same update."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n)
+    act = torch.bfloat16
+    g, m, v = (torch.randn(n, generator=gen, device=DEV) * s for s in (1e-3, 1e-3, 1e-3))
+    v = v.abs_()
+    master = torch.randn(n, generator=gen, device=DEV) * 0.02
+    w = torch.empty(n, dtype=act, device=DEV)
+    mr = HP["beta1"] * m.double() + (1 - HP["beta1"]) * g.double()
+    vr = HP["beta2"] * v.double() + (1 - HP["beta2"]) * g.double() ** 2
+    wr = master.double() - HP["lr"] * (mr / (1 - HP["beta1"] ** 3)) / ((vr / (1 - HP["beta2"] ** 3)).sqrt() + HP["eps"])
+    B.bk_adam(g, master, m, v, w, 3, **HP)
+    torch.cuda.synchronize()
+    # a handful of fp32 roundings (2^-24) each; 1 - beta2 in fp32 is 2^-24 / 1e-3 = 6e-5 off, on a term of 1e-6 of v
+    assert ((m.double() - mr).abs() <= 1e-6 * (mr.abs() + 1e-3)).all()
+    assert ((v.double() - vr).abs() <= 1e-6 * (vr.abs() + 1e-6)).all()
+    assert ((master.double() - wr).abs() <= 1e-6 * (wr.abs() + HP["lr"] * 50)).all()
+    assert torch.equal(w, master.to(act))
+
+
+def test_replica_sync_copies_everything_above_the_streaming_limit(B):
+    sc = synth.StageConfig("opt_big", 0, 1, 1024, 16, 4096, 16, 1, 1, 2, 4, 1, 2, 3)
+    P = 4 * 1024 * 1024 + 2 * 1024 * 4096 + 9 * 1024 + 4096
+    own = torch.zeros(P, dtype=torch.bfloat16, device=DEV)
+    st = B.Stage(B.make_cfg(sc), own, torch.zeros(2 * P, dtype=torch.bfloat16, device=DEV))
+    st.stage_optimizer_init()
+    w = torch.randn(2 * P, device=DEV).to(torch.bfloat16)
+    opt = torch.randn(st.shadow_opt.shape, device=DEV)
+    assert 2 * opt.numel() * opt.element_size() > 384 << 20
+    torch.cuda.synchronize()
+    st.stage_sync_replica(w, opt)
+    torch.cuda.synchronize()
+    assert torch.equal(st.shadow_w, w) and torch.equal(st.shadow_opt, opt)
+    st.stage_destroy()
