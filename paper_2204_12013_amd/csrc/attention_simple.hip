@@ -2,8 +2,16 @@
 // sequence length, head size up to 128).  Used by the fp32 configuration and as
 // the fallback of the bf16 path.  Online softmax over key tiles; the forward
 // keeps only the per-row log-sum-exp, the backward recomputes the
-// probabilities from it.  No atomics: dQ and dK/dV come from two kernels that
-// each own their output rows, so results are bitwise reproducible.
+// probabilities from it.  No atomics: dQ and dK/dV come from two kinds of
+// workgroups, of one launch, that each own their output rows, so results are
+// bitwise reproducible.
+//
+// The fp32 configuration has a few dozen tokens: its launches are one or a few
+// workgroups whose time is a chain of memory round trips, so a thread requests
+// all it needs of a tile before it waits (8 tokens, 2 samples x 2 heads of 32:
+// forward 8.0 us with one load per trip), and the backward is one launch that
+// forms delta = rowsum(ctx * dctx) where it is needed (three launches of 5.6,
+// 8.6 and 13.0 us before).
 #include "common.h"
 
 namespace bamboo {
@@ -11,15 +19,34 @@ namespace bamboo {
 constexpr int QT = 16;  // rows owned by a block
 constexpr int KT = 32;  // rows streamed per tile
 
+// dst0/dst1[r][c] = src0/src1[(row0 + r) * stride + c] for r < nrows, zero from row_limit on: eight elements of each
+// per thread in flight.  Rows past the limit are read from the last valid one, so that no load sits behind a branch.
 template <typename T>
-__device__ __forceinline__ void load_tile(float* dst, int ld, const T* src, long row_stride, int row0, int nrows,
-                                          int row_limit, int D) {
-  // dst[r][c] = src[(row0 + r) * row_stride + c] for r < nrows, zero beyond row_limit
-  for (int idx = threadIdx.x; idx < nrows * D; idx += blockDim.x) {
-    const int r = idx / D, c = idx % D;
-    float v = 0.f;
-    if (row0 + r < row_limit) v = to_f32<T>(src[(long)(row0 + r) * row_stride + c]);
-    dst[r * ld + c] = v;
+__device__ __forceinline__ void load_tiles(float* dst0, const T* src0, long stride0, float* dst1, const T* src1,
+                                           long stride1, int ld, int row0, int nrows, int row_limit, int D) {
+  const int n = nrows * D, dr = 256 / D, dc = 256 % D;
+  int r = threadIdx.x / D, c = threadIdx.x % D;
+  for (int i0 = threadIdx.x; i0 < n; i0 += 8 * 256) {
+    T v0[8], v1[8];
+    int at[8];
+    bool live[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const long row = min(row0 + r, row_limit - 1);
+      v0[u] = src0[row * stride0 + c];
+      v1[u] = src1[row * stride1 + c];
+      at[u] = r * ld + c;
+      live[u] = row0 + r < row_limit;
+      r += dr;
+      c += dc;
+      if (c >= D) { c -= D; ++r; }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i0 + u * 256 < n) {
+        dst0[at[u]] = live[u] ? to_f32<T>(v0[u]) : 0.f;
+        dst1[at[u]] = live[u] ? to_f32<T>(v1[u]) : 0.f;
+      }
   }
 }
 
@@ -32,6 +59,24 @@ __device__ __forceinline__ float group16_sum(float v) {
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
+}
+
+// sum of x[c] y[c] over c = first, first + STEP, ... < n, four products in flight
+template <int STEP, typename T>
+__device__ __forceinline__ float strided_dot(const T* x, const T* y, int first, int n) {
+  float s = 0.f;
+  for (int c0 = first; c0 < n; c0 += 4 * STEP) {
+    T p[4], q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = min(c0 + u * STEP, n - 1);
+      p[u] = x[c];
+      q[u] = y[c];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s += c0 + u * STEP < n ? to_f32<T>(p[u]) * to_f32<T>(q[u]) : 0.f;
+  }
+  return s;
 }
 
 template <typename T>
@@ -47,14 +92,14 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnDesc a) {
   const int q = threadIdx.x / 16, t = threadIdx.x % 16;
   const T* base = (const T*)a.qkv + (long)b * a.S * 3 * H + h * D;
   const float scale = rsqrtf((float)D);
-  load_tile<T>(Qs, ld, base, 3 * H, q0, QT, a.S, D);
+  load_tiles<T>(Qs, base, 3 * H, Qs, base, 3 * H, ld, q0, QT, a.S, D);
   const int qrow = q0 + q;
   float m = -INFINITY, l = 0.f, o[8] = {};
   const int kend = a.causal ? min(a.S, q0 + QT) : a.S;
   for (int k0 = 0; k0 < kend; k0 += KT) {
     __syncthreads();
-    load_tile<T>(Ks, ld, base + H, 3 * H, k0, KT, a.S, D);
-    load_tile<T>(Vs, ld, base + 2 * H, 3 * H, k0, KT, a.S, D);
+    load_tiles<T>(Ks, base + H, 3 * H, Vs, base + 2 * H, 3 * H, ld, k0, min(KT, kend - k0), a.S, D);
+    const int jn = min(KT, kend - k0);              // keys of this tile that any of the block's queries sees
     __syncthreads();
     float sc[2];
 #pragma unroll
@@ -62,7 +107,10 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnDesc a) {
       const int j = t + 16 * jj, key = k0 + j;
       const bool valid = key < a.S && qrow < a.S && (!a.causal || key <= qrow);
       float dot = 0.f;
-      for (int c = 0; c < D; ++c) dot = fmaf(Qs[q * ld + c], Ks[j * ld + c], dot);
+      if (j < jn) {
+#pragma unroll 8
+        for (int c = 0; c < D; ++c) dot = fmaf(Qs[q * ld + c], Ks[j * ld + c], dot);
+      }
       sc[jj] = valid ? dot * scale : -INFINITY;
     }
     const float mnew = fmaxf(m, group16_max(fmaxf(sc[0], sc[1])));
@@ -82,7 +130,8 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnDesc a) {
       const int c = t + 16 * e;
       if (c < D) {
         float acc = o[e] * corr;
-        for (int j = 0; j < KT; ++j) acc = fmaf(Ps[q * (KT + 1) + j], Vs[j * ld + c], acc);
+#pragma unroll 8
+        for (int j = 0; j < jn; ++j) acc = fmaf(Ps[q * (KT + 1) + j], Vs[j * ld + c], acc);
         o[e] = acc;
       }
     }
@@ -99,28 +148,9 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnDesc a) {
   }
 }
 
-// delta[b,h,i] = sum_c dctx[i,c] * ctx[i,c] over the head's columns
-template <typename T>
-__global__ void attn_delta_kernel(AttnDesc a) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long total = (long)a.B * a.heads * a.S;
-  if (idx >= total) return;
-  const int i = idx % a.S;
-  const int h = (idx / a.S) % a.heads;
-  const int b = idx / ((long)a.S * a.heads);
-  const int H = a.heads * a.d;
-  const long off = ((long)b * a.S + i) * H + h * a.d;
-  const T* o = (const T*)a.ctx + off;
-  const T* dO = (const T*)a.dctx + off;
-  float s = 0.f;
-  for (int c = 0; c < a.d; ++c) s = fmaf(to_f32<T>(o[c]), to_f32<T>(dO[c]), s);
-  a.delta[idx] = s;
-}
-
 // dQ: a block owns QT query rows and streams the keys.
 template <typename T>
-__global__ __launch_bounds__(256) void attn_bwd_dq_simple_kernel(AttnDesc a) {
-  extern __shared__ float smem[];
+__device__ __forceinline__ void bwd_dq_block(const AttnDesc& a, int blk, float* smem) {
   const int D = a.d, ld = D + 1, H = a.heads * D;
   float* Qs = smem;
   float* dOs = Qs + QT * ld;
@@ -128,32 +158,39 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_simple_kernel(AttnDesc a) {
   float* Vs = Ks + KT * ld;
   float* dSs = Vs + KT * ld;  // [QT][KT+1]
   const int b = blockIdx.y / a.heads, h = blockIdx.y % a.heads;
-  const int q0 = blockIdx.x * QT;
+  const int q0 = blk * QT;
   const int q = threadIdx.x / 16, t = threadIdx.x % 16;
   const T* base = (const T*)a.qkv + (long)b * a.S * 3 * H + h * D;
   const T* dbase = (const T*)a.dctx + (long)b * a.S * H + h * D;
   const float scale = rsqrtf((float)D);
-  load_tile<T>(Qs, ld, base, 3 * H, q0, QT, a.S, D);
-  load_tile<T>(dOs, ld, dbase, H, q0, QT, a.S, D);
-  const int qrow = q0 + q;
-  const long sidx = ((long)b * a.heads + h) * a.S + qrow;
-  const float lse = qrow < a.S ? a.lse[sidx] : 0.f;
-  const float delta = qrow < a.S ? a.delta[sidx] : 0.f;
+  load_tiles<T>(Qs, base, 3 * H, dOs, dbase, H, ld, q0, QT, a.S, D);
+  const int qrow = q0 + q, qv = min(qrow, a.S - 1);
+  const float lse = a.lse[((long)b * a.heads + h) * a.S + qv];
+  // delta of the row: its sixteen threads take every sixteenth feature
+  float delta;
+  {
+    const T* o = (const T*)a.ctx + ((long)b * a.S + qv) * H + h * D;
+    const T* dO = dbase + (long)qv * H;
+    delta = group16_sum(strided_dot<16>(o, dO, t, D));
+  }
   float dq[8] = {};
   const int kend = a.causal ? min(a.S, q0 + QT) : a.S;
   for (int k0 = 0; k0 < kend; k0 += KT) {
     __syncthreads();
-    load_tile<T>(Ks, ld, base + H, 3 * H, k0, KT, a.S, D);
-    load_tile<T>(Vs, ld, base + 2 * H, 3 * H, k0, KT, a.S, D);
+    load_tiles<T>(Ks, base + H, 3 * H, Vs, base + 2 * H, 3 * H, ld, k0, min(KT, kend - k0), a.S, D);
+    const int jn = min(KT, kend - k0);              // keys of this tile that any of the block's queries sees
     __syncthreads();
 #pragma unroll
     for (int jj = 0; jj < 2; ++jj) {
       const int j = t + 16 * jj, key = k0 + j;
       const bool valid = key < a.S && qrow < a.S && (!a.causal || key <= qrow);
       float dot = 0.f, dp = 0.f;
-      for (int c = 0; c < D; ++c) {
-        dot = fmaf(Qs[q * ld + c], Ks[j * ld + c], dot);
-        dp = fmaf(dOs[q * ld + c], Vs[j * ld + c], dp);
+      if (j < jn) {
+#pragma unroll 8
+        for (int c = 0; c < D; ++c) {
+          dot = fmaf(Qs[q * ld + c], Ks[j * ld + c], dot);
+          dp = fmaf(dOs[q * ld + c], Vs[j * ld + c], dp);
+        }
       }
       const float p = valid ? __expf(dot * scale - lse) : 0.f;
       dSs[q * (KT + 1) + j] = p * (dp - delta);
@@ -164,7 +201,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_simple_kernel(AttnDesc a) {
       const int c = t + 16 * e;
       if (c < D) {
         float acc = dq[e];
-        for (int j = 0; j < KT; ++j) acc = fmaf(dSs[q * (KT + 1) + j], Ks[j * ld + c], acc);
+#pragma unroll 8
+        for (int j = 0; j < jn; ++j) acc = fmaf(dSs[q * (KT + 1) + j], Ks[j * ld + c], acc);
         dq[e] = acc;
       }
     }
@@ -181,8 +219,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_simple_kernel(AttnDesc a) {
 
 // dK, dV: a block owns QT key rows and streams the queries.
 template <typename T>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_simple_kernel(AttnDesc a) {
-  extern __shared__ float smem[];
+__device__ __forceinline__ void bwd_dkv_block(const AttnDesc& a, int blk, float* smem) {
   const int D = a.d, ld = D + 1, H = a.heads * D;
   float* Ks = smem;
   float* Vs = Ks + QT * ld;
@@ -190,36 +227,54 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simple_kernel(AttnDesc a) {
   float* dOs = Qs + KT * ld;
   float* Ps = dOs + KT * ld;      // [KT][QT+1]
   float* dSs = Ps + KT * (QT + 1);  // [KT][QT+1]
+  float* lse_s = dSs + KT * (QT + 1);  // [KT]
+  float* del_s = lse_s + KT;           // [KT]
   const int b = blockIdx.y / a.heads, h = blockIdx.y % a.heads;
-  const int k0 = blockIdx.x * QT;
+  const int k0 = blk * QT;
   const int j = threadIdx.x / 16, t = threadIdx.x % 16;
   const T* base = (const T*)a.qkv + (long)b * a.S * 3 * H + h * D;
   const T* dbase = (const T*)a.dctx + (long)b * a.S * H + h * D;
   const float scale = rsqrtf((float)D);
-  load_tile<T>(Ks, ld, base + H, 3 * H, k0, QT, a.S, D);
-  load_tile<T>(Vs, ld, base + 2 * H, 3 * H, k0, QT, a.S, D);
+  load_tiles<T>(Ks, base + H, 3 * H, Vs, base + 2 * H, 3 * H, ld, k0, QT, a.S, D);
   const int key = k0 + j;
   float dk[8] = {}, dv[8] = {};
   const int qbeg = a.causal ? (k0 / KT) * KT : 0;
   for (int q0 = qbeg; q0 < a.S; q0 += KT) {
     __syncthreads();
-    load_tile<T>(Qs, ld, base, 3 * H, q0, KT, a.S, D);
-    load_tile<T>(dOs, ld, dbase, H, q0, KT, a.S, D);
+    const int in = min(KT, a.S - q0);               // queries of this tile
+    {
+      // delta and the log-sum-exp of the tile's queries: eight threads a row, straight from memory, so that these
+      // loads travel with those of the tile
+      const int i = threadIdx.x >> 3, e = threadIdx.x & 7, row = min(q0 + i, a.S - 1);
+      const T* o = (const T*)a.ctx + ((long)b * a.S + row) * H + h * D;
+      const T* dO = dbase + (long)row * H;
+      const float lse = a.lse[((long)b * a.heads + h) * a.S + row];
+      float delta = strided_dot<8>(o, dO, e, D);
+#pragma unroll
+      for (int x = 4; x > 0; x >>= 1) delta += __shfl_xor(delta, x, 64);
+      if (e == 0) {
+        lse_s[i] = lse;
+        del_s[i] = delta;
+      }
+    }
+    load_tiles<T>(Qs, base, 3 * H, dOs, dbase, H, ld, q0, in, a.S, D);
     __syncthreads();
 #pragma unroll
     for (int ii = 0; ii < 2; ++ii) {
       const int i = t + 16 * ii, qrow = q0 + i;
       const bool valid = key < a.S && qrow < a.S && (!a.causal || key <= qrow);
       float dot = 0.f, dp = 0.f;
-      for (int c = 0; c < D; ++c) {
-        dot = fmaf(Qs[i * ld + c], Ks[j * ld + c], dot);
-        dp = fmaf(dOs[i * ld + c], Vs[j * ld + c], dp);
+      if (i < in) {
+#pragma unroll 8
+        for (int c = 0; c < D; ++c) {
+          dot = fmaf(Qs[i * ld + c], Ks[j * ld + c], dot);
+          dp = fmaf(dOs[i * ld + c], Vs[j * ld + c], dp);
+        }
       }
       float p = 0.f, ds = 0.f;
       if (valid) {
-        const long sidx = ((long)b * a.heads + h) * a.S + qrow;
-        p = __expf(dot * scale - a.lse[sidx]);
-        ds = p * (dp - a.delta[sidx]);
+        p = __expf(dot * scale - lse_s[i]);
+        ds = p * (dp - del_s[i]);
       }
       Ps[i * (QT + 1) + j] = p;
       dSs[i * (QT + 1) + j] = ds;
@@ -230,7 +285,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simple_kernel(AttnDesc a) {
       const int c = t + 16 * e;
       if (c < D) {
         float av = dv[e], ak = dk[e];
-        for (int i = 0; i < KT; ++i) {
+#pragma unroll 8
+        for (int i = 0; i < in; ++i) {
           av = fmaf(Ps[i * (QT + 1) + j], dOs[i * ld + c], av);
           ak = fmaf(dSs[i * (QT + 1) + j], Qs[i * ld + c], ak);
         }
@@ -252,6 +308,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simple_kernel(AttnDesc a) {
   }
 }
 
+// Both passes in one launch: workgroups 0 .. nblk-1 of a (sample, head) own query rows, the others key rows.
+template <typename T>
+__global__ __launch_bounds__(256) void attn_bwd_simple_kernel(AttnDesc a, int nblk) {
+  extern __shared__ float smem[];
+  if ((int)blockIdx.x < nblk) bwd_dq_block<T>(a, blockIdx.x, smem);
+  else bwd_dkv_block<T>(a, (int)blockIdx.x - nblk, smem);
+}
+
 template <typename T>
 static hipError_t fwd_impl(hipStream_t s, const AttnDesc& a) {
   const size_t sh = ((size_t)(QT + 2 * KT) * (a.d + 1) + QT * (KT + 1)) * sizeof(float);
@@ -262,13 +326,12 @@ static hipError_t fwd_impl(hipStream_t s, const AttnDesc& a) {
 
 template <typename T>
 static hipError_t bwd_impl(hipStream_t s, const AttnDesc& a) {
-  const long total = (long)a.B * a.heads * a.S;
-  hipLaunchKernelGGL(attn_delta_kernel<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a);
-  dim3 grid((a.S + QT - 1) / QT, a.B * a.heads);
-  const size_t sh1 = ((size_t)(2 * QT + 2 * KT) * (a.d + 1) + QT * (KT + 1)) * sizeof(float);
-  hipLaunchKernelGGL(attn_bwd_dq_simple_kernel<T>, grid, dim3(256), sh1, s, a);
-  const size_t sh2 = ((size_t)(2 * QT + 2 * KT) * (a.d + 1) + 2 * KT * (QT + 1)) * sizeof(float);
-  hipLaunchKernelGGL(attn_bwd_dkv_simple_kernel<T>, grid, dim3(256), sh2, s, a);
+  const int nblk = (a.S + QT - 1) / QT;
+  const size_t tiles = (size_t)(2 * QT + 2 * KT) * (a.d + 1);
+  constexpr size_t kOwn = 2 * KT * (QT + 1) + 2 * KT;      // scores and row statistics of a key owner
+  static_assert(kOwn >= QT * (KT + 1), "the key owners need the most LDS");
+  hipLaunchKernelGGL(attn_bwd_simple_kernel<T>, dim3(2 * nblk, a.B * a.heads), dim3(256),
+                     (tiles + kOwn) * sizeof(float), s, a, nblk);
   return hipGetLastError();
 }
 
