@@ -140,6 +140,7 @@ hipError_t prepare_gemm_tables(hipStream_t s);
 // launch, which find idle CUs while the last GEMM tiles run; *tail_done says whether the launch took them
 // (a path that does not leaves them to the caller's launch_grad_reduce).
 hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const GradReduceBatch* tail = nullptr);
+hipError_t launch_gemm_group_f32(hipStream_t s, const GemmDesc* d, int n, const GradReduceBatch* tail);
 hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* d, int n, const GradReduceBatch* tail = nullptr,
                              bool* tail_done = nullptr);
 // output tile of the MFMA kernel: 10*WM + WN forces (64*WM) x (64*WN), 0 = automatic; returns the previous code

@@ -9,7 +9,10 @@
 // tiles, and its time is the serial chain through K.  So the NW wavefronts of a workgroup share ONE tile and take
 // every NW-th step; their partial tiles are summed through LDS in wavefront order.  Larger outputs (more tiles than
 // wavefront slots) take one wavefront per tile instead.
+#include <string.h>
+
 #include "common.h"
+#include "reduce_device.h"
 
 namespace bamboo {
 
@@ -59,13 +62,12 @@ __device__ __forceinline__ void epilogue1(const GemmDesc& d, int m, int n, float
 constexpr int kStepK = 8;      // k of one step (four matrix instructions)
 constexpr int kAhead = 4;      // steps whose operands a wavefront requests together
 
-// SPLIT: the workgroup's NW wavefronts share one tile; otherwise each has a tile of its own.
+// SPLIT: the workgroup's NW wavefronts share one tile; otherwise each has a tile of its own.  blk: workgroup of the problem
 template <bool A_K, bool B_K, bool VEC, int NW, bool SPLIT>
-__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmDesc d) {
-  __shared__ float part[SPLIT ? NW : 1][SPLIT ? 32 * 33 : 1];
+__device__ __forceinline__ void gemm_f32_block(const GemmDesc& d, int blk, float (*part)[32 * 33]) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int tiles_n = (d.N + 31) / 32, tiles = ((d.M + 31) / 32) * tiles_n;
-  const int tile = SPLIT ? (int)blockIdx.x : (int)blockIdx.x * NW + wave;
+  const int tile = SPLIT ? blk : blk * NW + wave;
   if (!SPLIT && tile >= tiles) return;
   const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
   const float* A = (const float*)d.A;
@@ -108,10 +110,35 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmDesc d) {
   }
 }
 
+template <bool A_K, bool B_K, bool VEC, int NW, bool SPLIT>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmDesc d) {
+  __shared__ float part[SPLIT ? NW : 1][32 * 33];
+  gemm_f32_block<A_K, B_K, VEC, NW, SPLIT>(d, blockIdx.x, part);
+}
+
+constexpr long kSplitTiles = 1024;      // up to this many tiles a workgroup of eight wavefronts takes each
+
+// The weight gradients of a layer and the ordered sums of its partial rows in one launch (g.first as in GemmGroup):
+// with 32 tokens each of the five launches was 4 us of kernel for less than one step of work per wavefront.
+__global__ __launch_bounds__(512) void gemm_f32_group_kernel(GemmGroup g) {
+  __shared__ float part[8][32 * 33];
+  static_assert(8 * 32 * 33 >= kReduceLdsFloats, "the reductions use the partial tiles' area");
+  const int b = blockIdx.x, total = g.first[GemmGroup::MAX];
+  if (b >= total) {
+    colreduce_batch_block(g.tail, b - total, &part[0][0]);
+    return;
+  }
+  int p = 0;
+#pragma unroll
+  for (int q = 1; q < GemmGroup::MAX; ++q)
+    if (q < g.n && b >= g.first[q]) p = q;
+  gemm_f32_block<false, false, false, 8, true>(g.d[p], b - g.first[p], part);
+}
+
 template <bool A_K, bool B_K, bool VEC>
 static hipError_t launch(hipStream_t s, const GemmDesc& d) {
   const long tiles = (long)((d.M + 31) / 32) * ((d.N + 31) / 32);
-  if (tiles <= 1024) {
+  if (tiles <= kSplitTiles) {
     hipLaunchKernelGGL((gemm_f32_kernel<A_K, B_K, VEC, 8, true>), dim3((unsigned)tiles), dim3(512), 0, s, d);
   } else {
     hipLaunchKernelGGL((gemm_f32_kernel<A_K, B_K, VEC, 4, false>), dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, s, d);
@@ -130,6 +157,29 @@ hipError_t launch_gemm_f32(hipStream_t s, const GemmDesc& d) {
   if (a_k && b_k) return vec ? launch<true, true, true>(s, d) : launch<true, true, false>(s, d);
   if (!a_k && !b_k) return launch<false, false, false>(s, d);
   return launch<false, true, false>(s, d);
+}
+
+// n weight-gradient products (both operands with the contraction index strided) as one launch where each of them
+// would be one workgroup per tile; hipErrorNotSupported otherwise (the caller launches them singly)
+hipError_t launch_gemm_group_f32(hipStream_t s, const GemmDesc* d, int n, const GradReduceBatch* tail) {
+  if (n < 1 || n > GemmGroup::MAX) return hipErrorNotSupported;
+  GemmGroup g;
+  memset(&g, 0, sizeof(g));
+  g.n = n;
+  if (tail != nullptr) g.tail = *tail;
+  long total = 0;
+  for (int i = 0; i < n; ++i) {
+    if (d[i].M <= 0 || d[i].N <= 0 || d[i].a_sk == 1 || d[i].b_sk == 1 || d[i].a_sm != 1 || d[i].b_sn != 1)
+      return hipErrorNotSupported;
+    const long tiles = (long)((d[i].M + 31) / 32) * ((d[i].N + 31) / 32);
+    if (tiles > kSplitTiles) return hipErrorNotSupported;
+    g.d[i] = d[i];
+    g.first[i] = (int)total;
+    total += tiles;
+  }
+  for (int i = n; i <= GemmGroup::MAX; ++i) g.first[i] = (int)total;
+  hipLaunchKernelGGL(gemm_f32_group_kernel, dim3((unsigned)(total + grad_reduce_blocks(g.tail))), dim3(512), 0, s, g);
+  return hipGetLastError();
 }
 
 }  // namespace bamboo

@@ -578,3 +578,19 @@ def test_two_stages_driven_from_two_threads_give_the_results_of_sequential_runs(
         (acts_a, g_a, gs_a), (acts_t, g_t, gs_t) = alone[n], together[n]
         assert all(torch.equal(a, b) for a, b in zip(acts_a, acts_t)), n
         assert torch.equal(g_a, g_t) and torch.equal(gs_a, gs_t), n
+
+
+@pytest.mark.parametrize("hidden,heads,ffn", [(24, 1, 40), (544, 17, 2048)])
+def test_fp32_weight_gradients_as_one_launch_and_singly(B, hidden, heads, ffn):
+    """The fp32 weight gradients of a layer go out as one launch, with the sums behind its bias and LayerNorm gradients,
+    up to 1024 tiles of 32 x 32 per matrix (24 x 40: remainders in both dimensions), singly beyond (544 x 2048: 1088)."""
+    sc = synth.StageConfig("g32", 0, 0, hidden, heads, ffn, 21, 2, 2, 1, 4, 1, 2, 51)
+    inp, st, hz = _build(B, sc)
+    hz.begin_iteration()
+    hz.run(st.stage_schedule())
+    hz.sync()
+    ref = _oracle(sc, inp)
+    check_grads(st.own_g.cpu().numpy(), ref.G_own, sc.hidden, sc.ffn, TOL[sc.dtype], "own")
+    check_grads(hz.succ.own_g.cpu().numpy(), ref.G_succ, sc.hidden, sc.ffn, TOL[sc.dtype], "successor")
+    st.stage_destroy()
+    hz.succ.stage_destroy()
