@@ -36,9 +36,9 @@ constexpr int TILE = 64;   // rows streamed through LDS per step
 // heaviest, as for query owners; otherwise the lowest, as for key owners), so the dispatcher
 // hands out long workgroups first and the short ones fill the tail of the launch.
 template <bool CAUSAL, bool HEAVY_LAST>
-__device__ __forceinline__ void block_of(int nblk, int nbh, int* blk, int* bh) {
-  const int i = blockIdx.x / nbh;
-  *bh = blockIdx.x % nbh;
+__device__ __forceinline__ void block_of(int wg, int nblk, int nbh, int* blk, int* bh) {
+  const int i = wg / nbh;
+  *bh = wg % nbh;
   *blk = (CAUSAL && HEAVY_LAST) ? nblk - 1 - i : i;
 }
 
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 5;
   const int H = a.heads * D, S = a.S;
   int qblk, bh;
-  block_of<CAUSAL, true>((S + 127) / 128, a.B * a.heads, &qblk, &bh);
+  block_of<CAUSAL, true>(blockIdx.x, (S + 127) / 128, a.B * a.heads, &qblk, &bh);
   const int b = bh / a.heads, h = bh % a.heads;
   const int q0 = qblk * 128, qw0 = q0 + wave * 32;
   const long rs = 3L * H;
@@ -334,277 +334,308 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
 }
 
 // =============================================================== backward
-// dQ: a wavefront owns 32 queries (lane = query) and streams 64-key tiles.
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void attn_bwd_dq_mfma_kernel(AttnDesc a) {
+// Two passes, by one kernel template: PASS_DQ and PASS_DKV are launched one after the other; with PASS_BOTH the first
+// n workgroups own key rows (the longer pass) and the others query rows, side by side.
+enum BwdPass { PASS_DQ, PASS_DKV, PASS_BOTH };
+template <int D, bool CAUSAL, int PASS>
+__global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
   constexpr int LD = D + 8;
+  constexpr bool OWN_DELTA = PASS == PASS_BOTH;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16_t* Ks = (bf16_t*)smem_raw;                 // [2][64][LD]
-  bf16_t* Vs = Ks + 2 * TILE * LD;                // [2][64][LD]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int H = a.heads * D, S = a.S;
-  int qblk, bh;
-  block_of<CAUSAL, true>((S + 127) / 128, a.B * a.heads, &qblk, &bh);
-  const int b = bh / a.heads, h = bh % a.heads;
-  const int q0 = qblk * 128, qw0 = q0 + wave * 32;
-  const long rs = 3L * H;
-  const bf16_t* base = (const bf16_t*)a.qkv + (long)b * S * rs + h * D;
-  const bf16_t* dbase = (const bf16_t*)a.dctx + (long)b * S * H + h * D;
-  const float scale = rsqrtf((float)D), c = scale * kLog2e;
+  // dQ: a wavefront owns 32 queries (lane = query) and streams 64-key tiles.
+  if (PASS == PASS_DQ || (PASS == PASS_BOTH && (int)blockIdx.x >= n)) {
+    const int wg = PASS == PASS_BOTH ? (int)blockIdx.x - n : (int)blockIdx.x;
+    bf16_t* Ks = (bf16_t*)smem_raw;                 // [2][64][LD]
+    bf16_t* Vs = Ks + 2 * TILE * LD;                // [2][64][LD]
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int H = a.heads * D, S = a.S;
+    int qblk, bh;
+    block_of<CAUSAL, true>(wg, (S + 127) / 128, a.B * a.heads, &qblk, &bh);
+    const int b = bh / a.heads, h = bh % a.heads;
+    const int q0 = qblk * 128, qw0 = q0 + wave * 32;
+    const long rs = 3L * H;
+    const bf16_t* base = (const bf16_t*)a.qkv + (long)b * S * rs + h * D;
+    const bf16_t* dbase = (const bf16_t*)a.dctx + (long)b * S * H + h * D;
+    const float scale = rsqrtf((float)D), c = scale * kLog2e;
 
-  bf16x8 qf[D / 16], dof[D / 16];
-  load_row_frags<D>(qf, base, rs, qw0, S);
-  load_row_frags<D>(dof, dbase, H, qw0, S);
-  const int query = qw0 + (lane & 31);
-  const long sidx = ((long)b * a.heads + h) * S + min(query, S - 1);
-  const float lse2 = a.lse[sidx] * kLog2e;
-  // delta[q] = sum over the head's features of ctx * dctx: the two lanes of a query hold the two halves of
-  // every 16-feature group of dctx already; the same pieces of ctx are read once.  The dK/dV kernel, which
-  // runs after this one, takes delta from memory.
-  float delta = 0.f;
-  {
-    bf16x8 of[D / 16];
-    load_row_frags<D>(of, (const bf16_t*)a.ctx + (long)b * S * H + h * D, H, qw0, S);
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) delta += (float)of[ks][j] * (float)dof[ks][j];
-    delta += __shfl_xor(delta, 32, 64);
-    if (lane < 32 && query < S) a.delta[sidx] = delta;
-  }
-  f32x16 dq[D / 32];
-#pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dq[dt][r] = 0.f;
-  // the dP MFMAs start from -delta (a per-lane constant here: a lane owns a query), so their accumulator
-  // comes out as dP - delta
-  f32x16 neg_delta, zero16;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    neg_delta[r] = -delta;
-    zero16[r] = 0.f;
-  }
-
-  const int kend = CAUSAL ? min(S, q0 + 128) : S;
-  const int nt = (kend + TILE - 1) / TILE;
-  RowTile<D> kt_regs, vt_regs;
-  TileAddr<D> ta;
-  ta.init(rs, S);
-  kt_regs.fetch(base + H, ta, 0);
-  vt_regs.fetch(base + 2 * H, ta, 0);
-  kt_regs.stash(Ks, LD);
-  vt_regs.stash(Vs, LD);
-  __syncthreads();
-  for (int t = 0; t < nt; ++t) {
-    const bf16_t* ks_ = Ks + (t & 1) * TILE * LD;
-    const bf16_t* vs_ = Vs + (t & 1) * TILE * LD;
-    const int k0 = t * TILE;
-    if (t + 1 < nt) {
-      kt_regs.fetch(base + H, ta, t + 1);
-      vt_regs.fetch(base + 2 * H, ta, t + 1);
-    }
-    if (!CAUSAL || k0 <= qw0 + 31) {
-      f32x16 s[2], dp[2];
+    bf16x8 qf[D / 16], dof[D / 16];
+    load_row_frags<D>(qf, base, rs, qw0, S);
+    load_row_frags<D>(dof, dbase, H, qw0, S);
+    const int query = qw0 + (lane & 31);
+    const long sidx = ((long)b * a.heads + h) * S + min(query, S - 1);
+    const float lse2 = a.lse[sidx] * kLog2e;
+    // delta[q] = sum over the head's features of ctx * dctx: the two lanes of a query hold the two halves of
+    // every 16-feature group of dctx already; the same pieces of ctx are read once.  The dK/dV kernel, where it
+    // runs after this one, takes delta from memory.
+    float delta = 0.f;
+    {
+      bf16x8 of[D / 16];
+      load_row_frags<D>(of, (const bf16_t*)a.ctx + (long)b * S * H + h * D, H, qw0, S);
 #pragma unroll
       for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(ks_, LD, u * 32, ks), qf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
-          dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(vs_, LD, u * 32, ks), dof[ks], ks == 0 ? neg_delta : dp[u], 0,
-                                                          0, 0);
+        for (int j = 0; j < 8; ++j) delta += (float)of[ks][j] * (float)dof[ks][j];
+      delta += __shfl_xor(delta, 32, 64);
+      if (lane < 32 && query < S) a.delta[sidx] = delta;
+    }
+    f32x16 dq[D / 32];
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dq[dt][r] = 0.f;
+    // the dP MFMAs start from -delta (a per-lane constant here: a lane owns a query), so their accumulator
+    // comes out as dP - delta
+    f32x16 neg_delta, zero16;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      neg_delta[r] = -delta;
+      zero16[r] = 0.f;
+    }
+
+    const int kend = CAUSAL ? min(S, q0 + 128) : S;
+    const int nt = (kend + TILE - 1) / TILE;
+    RowTile<D> kt_regs, vt_regs;
+    TileAddr<D> ta;
+    ta.init(rs, S);
+    kt_regs.fetch(base + H, ta, 0);
+    vt_regs.fetch(base + 2 * H, ta, 0);
+    kt_regs.stash(Ks, LD);
+    vt_regs.stash(Vs, LD);
+    __syncthreads();
+    for (int t = 0; t < nt; ++t) {
+      const bf16_t* ks_ = Ks + (t & 1) * TILE * LD;
+      const bf16_t* vs_ = Vs + (t & 1) * TILE * LD;
+      const int k0 = t * TILE;
+      if (t + 1 < nt) {
+        kt_regs.fetch(base + H, ta, t + 1);
+        vt_regs.fetch(base + 2 * H, ta, t + 1);
+      }
+      if (!CAUSAL || k0 <= qw0 + 31) {
+        f32x16 s[2], dp[2];
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(ks_, LD, u * 32, ks), qf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
+            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(vs_, LD, u * 32, ks), dof[ks], ks == 0 ? neg_delta : dp[u], 0,
+                                                            0, 0);
+          }
+        const bool need_mask = (k0 + TILE > S) || (CAUSAL && k0 + TILE - 1 > qw0);
+        if (need_mask) {                            // uniform over the wavefront
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              float p = __builtin_amdgcn_exp2f(fmaf(s[u][r], c, -lse2));
+              const int key = k0 + u * 32 + acc_row(r);
+              if (key >= S || (CAUSAL && key > query)) p = 0.f;
+              s[u][r] = p * dp[u][r];               // dS^T
+            }
+        } else {
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[u][r] = __builtin_amdgcn_exp2f(fmaf(s[u][r], c, -lse2)) * dp[u][r];
         }
-      const bool need_mask = (k0 + TILE > S) || (CAUSAL && k0 + TILE - 1 > qw0);
-      if (need_mask) {                            // uniform over the wavefront
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const bf16x8 dsb = pack8(s[u >> 1], u & 1);
+#pragma unroll
+          for (int dt = 0; dt < D / 32; ++dt)
+            dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(ks_, LD, dt * 32, 16 * u), dsb, dq[dt], 0, 0, 0);
+        }
+      }
+      if (t + 1 < nt) {
+        kt_regs.stash(Ks + ((t + 1) & 1) * TILE * LD, LD);
+        vt_regs.stash(Vs + ((t + 1) & 1) * TILE * LD, LD);
+      }
+      __syncthreads();
+    }
+    bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
+    float* xch = (float*)((bf16_t*)smem_raw + 4 * 32 * (D + 8));     // behind the four staging areas
+    if (a.dqkv_colsum != nullptr) {                                  // uniform over the grid
+      float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      store_rows_sum<D>(dq, scale, stage, (bf16_t*)a.dqkv + (long)b * S * rs + h * D, rs, qw0, S, cs);
+      float* part = a.dqkv_colsum + ((long)b * ((S + 127) / 128) + qblk) * rs;
+      block_colsum_write<D>(cs, xch, part + h * D);
+    } else {
+      store_rows<D>(dq, scale, stage, (bf16_t*)a.dqkv + (long)b * S * rs + h * D, rs, qw0, S);
+    }
+    return;
+  }
+  if constexpr (PASS != PASS_DQ) {
+    // dK, dV: a wavefront owns 32 keys (lane = key) and streams 64-query tiles.
+    // OWN_DELTA: delta of the sample's and head's queries is formed here, ahead of the tiles, into LDS behind the rest
+    // (S floats), in the order of the additions of the dQ pass; otherwise it comes from memory.
+    const int wg = blockIdx.x;
+    bf16_t* Qs = (bf16_t*)smem_raw;                 // [2][64][LD]
+    bf16_t* dOs = Qs + 2 * TILE * LD;               // [2][64][LD]
+    float* lse_s = (float*)(dOs + 2 * TILE * LD);   // [2][64]  (log2 domain)
+    float* del_s = lse_s + 2 * TILE;                // [2][64]
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 5;
+    const int H = a.heads * D, S = a.S;
+    int kblk, bh;
+    block_of<CAUSAL, false>(wg, (S + 127) / 128, a.B * a.heads, &kblk, &bh);
+    const int b = bh / a.heads, h = bh % a.heads;
+    const int kb0 = kblk * 128, kw0 = kb0 + wave * 32;
+    const long rs = 3L * H;
+    const bf16_t* base = (const bf16_t*)a.qkv + (long)b * S * rs + h * D;
+    const bf16_t* dbase = (const bf16_t*)a.dctx + (long)b * S * H + h * D;
+    const float* lse_g = a.lse + ((long)b * a.heads + h) * S;
+    const float* del_g = a.delta + ((long)b * a.heads + h) * S;
+    const float scale = rsqrtf((float)D), c = scale * kLog2e;
+
+    bf16x8 kf[D / 16], vf[D / 16];
+    load_row_frags<D>(kf, base + H, rs, kw0, S);
+    load_row_frags<D>(vf, base + 2 * H, rs, kw0, S);
+    const int key = kw0 + (lane & 31);
+    f32x16 dk[D / 32], dv[D / 32];
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { dk[dt][r] = 0.f; dv[dt][r] = 0.f; }
+
+    const int qbeg = CAUSAL ? (kb0 / TILE) * TILE : 0;
+    const int nt = (S - qbeg + TILE - 1) / TILE;
+    float* own_delta = del_s + 2 * TILE;             // [S]
+    if (OWN_DELTA) {
+      // two threads a query, as the two lanes of a query share its features in the dQ pass
+      const bf16_t* cbase = (const bf16_t*)a.ctx + (long)b * S * H + h * D + (threadIdx.x & 1) * 8;
+      const bf16_t* gbase = dbase + (threadIdx.x & 1) * 8;
+      for (int q = qbeg + (threadIdx.x >> 1); q - (int)(threadIdx.x >> 1) < S; q += 128) {
+        const long row = (long)min(q, S - 1) * H;
+        bf16x8 of[D / 16], gf[D / 16];
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+          of[ks] = *(const bf16x8*)(cbase + row + ks * 16);
+          gf[ks] = *(const bf16x8*)(gbase + row + ks * 16);
+        }
+        float d = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) d += (float)of[ks][j] * (float)gf[ks][j];
+        d += __shfl_xor(d, 1, 64);
+        if ((threadIdx.x & 1) == 0 && q < S) own_delta[q] = d;
+      }
+      __syncthreads();
+    }
+    RowTile<D> q_regs, do_regs;
+    float lse_r = 0.f, del_r = 0.f;
+    auto fetch_stats = [&](int q0t) {
+      if (threadIdx.x < TILE) {
+        const int q = q0t + threadIdx.x;
+        lse_r = q < S ? lse_g[q] * kLog2e : 0.f;
+        if (OWN_DELTA) del_r = q < S ? -own_delta[q] : 0.f;
+        else del_r = q < S ? -del_g[q] : 0.f;        // negated: the dP accumulators start from it
+      }
+    };
+    auto stash_stats = [&](int buf) {
+      if (threadIdx.x < TILE) {
+        lse_s[buf * TILE + threadIdx.x] = lse_r;
+        del_s[buf * TILE + threadIdx.x] = del_r;
+      }
+    };
+    TileAddr<D> ta_q, ta_do;
+    ta_q.init(rs, S);
+    ta_do.init(H, S);
+    q_regs.fetch(base, ta_q, qbeg / TILE);
+    do_regs.fetch(dbase, ta_do, qbeg / TILE);
+    fetch_stats(qbeg);
+    q_regs.stash(Qs, LD);
+    do_regs.stash(dOs, LD);
+    stash_stats(0);
+    __syncthreads();
+    for (int t = 0; t < nt; ++t) {
+      const int buf = t & 1;
+      const bf16_t* qs_ = Qs + buf * TILE * LD;
+      const bf16_t* dos_ = dOs + buf * TILE * LD;
+      const int q0t = qbeg + t * TILE;
+      if (t + 1 < nt) {
+        q_regs.fetch(base, ta_q, qbeg / TILE + t + 1);
+        do_regs.fetch(dbase, ta_do, qbeg / TILE + t + 1);
+        fetch_stats(q0t + TILE);
+      }
+      if (!CAUSAL || q0t + TILE - 1 >= kw0) {       // wave-uniform: some query at or after the wave's first key
+        // the queries' -delta runs along the accumulator registers here and comes from LDS with the tile: the
+        // dP accumulators start from it and come out as dP - delta
+        f32x16 s[2], dp[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            float p = __builtin_amdgcn_exp2f(fmaf(s[u][r], c, -lse2));
-            const int key = k0 + u * 32 + acc_row(r);
-            if (key >= S || (CAUSAL && key > query)) p = 0.f;
-            s[u][r] = p * dp[u][r];               // dS^T
+          for (int a4 = 0; a4 < 4; ++a4) {
+            const f32x4 d4 = *(const f32x4*)(del_s + buf * TILE + u * 32 + 8 * a4 + 4 * g);
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) dp[u][4 * a4 + cc] = d4[cc];
           }
-      } else {
+        const f32x16 zero16 = {};
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(qs_, LD, u * 32, ks), kf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
+            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(dos_, LD, u * 32, ks), vf[ks], dp[u], 0, 0, 0);
+          }
+        const bool need_mask = (q0t + TILE > S) || (kw0 + 32 > S) || (CAUSAL && q0t < kw0 + 31);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) s[u][r] = __builtin_amdgcn_exp2f(fmaf(s[u][r], c, -lse2)) * dp[u][r];
-      }
+          for (int a4 = 0; a4 < 4; ++a4) {
+            const int row = u * 32 + 8 * a4 + 4 * g;   // first of 4 consecutive query rows of this lane
+            const f32x4 l4 = *(const f32x4*)(lse_s + buf * TILE + row);
+            if (need_mask) {                        // uniform over the wavefront
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bf16x8 dsb = pack8(s[u >> 1], u & 1);
+              for (int cc = 0; cc < 4; ++cc) {
+                const int r = 4 * a4 + cc;
+                float p = __builtin_amdgcn_exp2f(fmaf(s[u][r], c, -l4[cc]));
+                const int query = q0t + row + cc;
+                if (query >= S || key >= S || (CAUSAL && key > query)) p = 0.f;
+                s[u][r] = p;
+                dp[u][r] *= p;                      // dS
+              }
+            } else {
 #pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-          dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(ks_, LD, dt * 32, 16 * u), dsb, dq[dt], 0, 0, 0);
-      }
-    }
-    if (t + 1 < nt) {
-      kt_regs.stash(Ks + ((t + 1) & 1) * TILE * LD, LD);
-      vt_regs.stash(Vs + ((t + 1) & 1) * TILE * LD, LD);
-    }
-    __syncthreads();
-  }
-  bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
-  float* xch = (float*)((bf16_t*)smem_raw + 4 * 32 * (D + 8));     // behind the four staging areas
-  if (a.dqkv_colsum != nullptr) {                                  // uniform over the grid
-    float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    store_rows_sum<D>(dq, scale, stage, (bf16_t*)a.dqkv + (long)b * S * rs + h * D, rs, qw0, S, cs);
-    float* part = a.dqkv_colsum + ((long)b * ((S + 127) / 128) + qblk) * rs;
-    block_colsum_write<D>(cs, xch, part + h * D);
-  } else {
-    store_rows<D>(dq, scale, stage, (bf16_t*)a.dqkv + (long)b * S * rs + h * D, rs, qw0, S);
-  }
-}
-
-// dK, dV: a wavefront owns 32 keys (lane = key) and streams 64-query tiles.
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(AttnDesc a) {
-  constexpr int LD = D + 8;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16_t* Qs = (bf16_t*)smem_raw;                 // [2][64][LD]
-  bf16_t* dOs = Qs + 2 * TILE * LD;               // [2][64][LD]
-  float* lse_s = (float*)(dOs + 2 * TILE * LD);   // [2][64]  (log2 domain)
-  float* del_s = lse_s + 2 * TILE;                // [2][64]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 5;
-  const int H = a.heads * D, S = a.S;
-  int kblk, bh;
-  block_of<CAUSAL, false>((S + 127) / 128, a.B * a.heads, &kblk, &bh);
-  const int b = bh / a.heads, h = bh % a.heads;
-  const int kb0 = kblk * 128, kw0 = kb0 + wave * 32;
-  const long rs = 3L * H;
-  const bf16_t* base = (const bf16_t*)a.qkv + (long)b * S * rs + h * D;
-  const bf16_t* dbase = (const bf16_t*)a.dctx + (long)b * S * H + h * D;
-  const float* lse_g = a.lse + ((long)b * a.heads + h) * S;
-  const float* del_g = a.delta + ((long)b * a.heads + h) * S;
-  const float scale = rsqrtf((float)D), c = scale * kLog2e;
-
-  bf16x8 kf[D / 16], vf[D / 16];
-  load_row_frags<D>(kf, base + H, rs, kw0, S);
-  load_row_frags<D>(vf, base + 2 * H, rs, kw0, S);
-  const int key = kw0 + (lane & 31);
-  f32x16 dk[D / 32], dv[D / 32];
-#pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dk[dt][r] = 0.f; dv[dt][r] = 0.f; }
-
-  const int qbeg = CAUSAL ? (kb0 / TILE) * TILE : 0;
-  const int nt = (S - qbeg + TILE - 1) / TILE;
-  RowTile<D> q_regs, do_regs;
-  float lse_r = 0.f, del_r = 0.f;
-  auto fetch_stats = [&](int q0t) {
-    if (threadIdx.x < TILE) {
-      const int q = q0t + threadIdx.x;
-      lse_r = q < S ? lse_g[q] * kLog2e : 0.f;
-      del_r = q < S ? -del_g[q] : 0.f;             // negated: the dP accumulators start from it
-    }
-  };
-  auto stash_stats = [&](int buf) {
-    if (threadIdx.x < TILE) {
-      lse_s[buf * TILE + threadIdx.x] = lse_r;
-      del_s[buf * TILE + threadIdx.x] = del_r;
-    }
-  };
-  TileAddr<D> ta_q, ta_do;
-  ta_q.init(rs, S);
-  ta_do.init(H, S);
-  q_regs.fetch(base, ta_q, qbeg / TILE);
-  do_regs.fetch(dbase, ta_do, qbeg / TILE);
-  fetch_stats(qbeg);
-  q_regs.stash(Qs, LD);
-  do_regs.stash(dOs, LD);
-  stash_stats(0);
-  __syncthreads();
-  for (int t = 0; t < nt; ++t) {
-    const int buf = t & 1;
-    const bf16_t* qs_ = Qs + buf * TILE * LD;
-    const bf16_t* dos_ = dOs + buf * TILE * LD;
-    const int q0t = qbeg + t * TILE;
-    if (t + 1 < nt) {
-      q_regs.fetch(base, ta_q, qbeg / TILE + t + 1);
-      do_regs.fetch(dbase, ta_do, qbeg / TILE + t + 1);
-      fetch_stats(q0t + TILE);
-    }
-    if (!CAUSAL || q0t + TILE - 1 >= kw0) {       // wave-uniform: some query at or after the wave's first key
-      // the queries' -delta runs along the accumulator registers here and comes from LDS with the tile: the
-      // dP accumulators start from it and come out as dP - delta
-      f32x16 s[2], dp[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int a4 = 0; a4 < 4; ++a4) {
-          const f32x4 d4 = *(const f32x4*)(del_s + buf * TILE + u * 32 + 8 * a4 + 4 * g);
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) dp[u][4 * a4 + cc] = d4[cc];
-        }
-      const f32x16 zero16 = {};
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(qs_, LD, u * 32, ks), kf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
-          dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(dos_, LD, u * 32, ks), vf[ks], dp[u], 0, 0, 0);
-        }
-      const bool need_mask = (q0t + TILE > S) || (kw0 + 32 > S) || (CAUSAL && q0t < kw0 + 31);
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int a4 = 0; a4 < 4; ++a4) {
-          const int row = u * 32 + 8 * a4 + 4 * g;   // first of 4 consecutive query rows of this lane
-          const f32x4 l4 = *(const f32x4*)(lse_s + buf * TILE + row);
-          if (need_mask) {                        // uniform over the wavefront
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) {
-              const int r = 4 * a4 + cc;
-              float p = __builtin_amdgcn_exp2f(fmaf(s[u][r], c, -l4[cc]));
-              const int query = q0t + row + cc;
-              if (query >= S || key >= S || (CAUSAL && key > query)) p = 0.f;
-              s[u][r] = p;
-              dp[u][r] *= p;                      // dS
-            }
-          } else {
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) {
-              const int r = 4 * a4 + cc;
-              const float p = __builtin_amdgcn_exp2f(fmaf(s[u][r], c, -l4[cc]));
-              s[u][r] = p;
-              dp[u][r] *= p;                      // dS
+              for (int cc = 0; cc < 4; ++cc) {
+                const int r = 4 * a4 + cc;
+                const float p = __builtin_amdgcn_exp2f(fmaf(s[u][r], c, -l4[cc]));
+                s[u][r] = p;
+                dp[u][r] *= p;                      // dS
+              }
             }
           }
-        }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bf16x8 pb = pack8(s[u >> 1], u & 1);
-        const bf16x8 dsb = pack8(dp[u >> 1], u & 1);
+        for (int u = 0; u < 4; ++u) {
+          const bf16x8 pb = pack8(s[u >> 1], u & 1);
+          const bf16x8 dsb = pack8(dp[u >> 1], u & 1);
 #pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt) {
-          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(dos_, LD, dt * 32, 16 * u), pb, dv[dt], 0, 0, 0);
-          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(qs_, LD, dt * 32, 16 * u), dsb, dk[dt], 0, 0, 0);
+          for (int dt = 0; dt < D / 32; ++dt) {
+            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(dos_, LD, dt * 32, 16 * u), pb, dv[dt], 0, 0, 0);
+            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(qs_, LD, dt * 32, 16 * u), dsb, dk[dt], 0, 0, 0);
+          }
         }
       }
+      if (t + 1 < nt) {
+        q_regs.stash(Qs + (buf ^ 1) * TILE * LD, LD);
+        do_regs.stash(dOs + (buf ^ 1) * TILE * LD, LD);
+        stash_stats(buf ^ 1);
+      }
+      __syncthreads();
     }
-    if (t + 1 < nt) {
-      q_regs.stash(Qs + (buf ^ 1) * TILE * LD, LD);
-      do_regs.stash(dOs + (buf ^ 1) * TILE * LD, LD);
-      stash_stats(buf ^ 1);
+    bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
+    bf16_t* out = (bf16_t*)a.dqkv + (long)b * S * rs + h * D;
+    float* xch = (float*)((bf16_t*)smem_raw + 4 * 32 * (D + 8));     // behind the four staging areas
+    if (a.dqkv_colsum != nullptr) {                                  // uniform over the grid
+      float* part = a.dqkv_colsum + ((long)b * ((S + 127) / 128) + kblk) * rs;
+      float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      store_rows_sum<D>(dk, scale, stage, out + H, rs, kw0, S, cs);
+      block_colsum_write<D>(cs, xch, part + H + h * D);
+      float cv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      store_rows_sum<D>(dv, 1.f, stage, out + 2 * H, rs, kw0, S, cv);
+      block_colsum_write<D>(cv, xch, part + 2 * H + h * D);
+    } else {
+      store_rows<D>(dk, scale, stage, out + H, rs, kw0, S);
+      store_rows<D>(dv, 1.f, stage, out + 2 * H, rs, kw0, S);
     }
-    __syncthreads();
-  }
-  bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
-  bf16_t* out = (bf16_t*)a.dqkv + (long)b * S * rs + h * D;
-  float* xch = (float*)((bf16_t*)smem_raw + 4 * 32 * (D + 8));     // behind the four staging areas
-  if (a.dqkv_colsum != nullptr) {                                  // uniform over the grid
-    float* part = a.dqkv_colsum + ((long)b * ((S + 127) / 128) + kblk) * rs;
-    float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    store_rows_sum<D>(dk, scale, stage, out + H, rs, kw0, S, cs);
-    block_colsum_write<D>(cs, xch, part + H + h * D);
-    float cv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    store_rows_sum<D>(dv, 1.f, stage, out + 2 * H, rs, kw0, S, cv);
-    block_colsum_write<D>(cv, xch, part + 2 * H + h * D);
-  } else {
-    store_rows<D>(dk, scale, stage, out + H, rs, kw0, S);
-    store_rows<D>(dv, 1.f, stage, out + 2 * H, rs, kw0, S);
   }
 }
 
@@ -627,18 +658,38 @@ static hipError_t fwd_launch(hipStream_t s, const AttnDesc& a) {
   return hipGetLastError();
 }
 
+// Both backward passes as one launch where the chip holds their workgroups together (two per CU at head size 64, one
+// at 128): the second pass need not wait for the first, which leaves most CUs idle, and a launch is saved; it costs the
+// key owners their own delta.  Backward in us, two launches / one (samples, tokens, heads, size):
+//   1 x 128 x 16 x 64: 13.0 / 8.1    3 x 333 x 16 x 64: 25.7 / 19.1    4 x 512 x 16 x 64 (512 workgroups): 32.9 / 27.2
+//   8 x 512 x 16 x 64 (1024): 48.6 / 50.6    1 x 700 x 24 x 128 (288): 67.2 / 51.3    2 x 512 x 24 x 128 (384): 55.6 / 55.5
+constexpr int kBothMaxSeq = 1024;      // deltas of a sequence in LDS
+template <int D>
+static bool side_by_side(const AttnDesc& a, unsigned wgs) {
+  return a.S <= kBothMaxSeq && 2 * wgs <= (D == 64 ? 512u : 320u);
+}
+
 template <int D, bool CAUSAL>
 static hipError_t bwd_launch(hipStream_t s, const AttnDesc& a) {
   constexpr int BYTES_DQ = 4 * TILE * (D + 8) * 2;
   constexpr int BYTES_DKV = 4 * TILE * (D + 8) * 2 + 4 * TILE * 4;
-  constexpr auto kq = attn_bwd_dq_mfma_kernel<D, CAUSAL>;
-  constexpr auto kkv = attn_bwd_dkv_mfma_kernel<D, CAUSAL>;
+  constexpr auto kq = attn_bwd_mfma_kernel<D, CAUSAL, PASS_DQ>;
+  constexpr auto kkv = attn_bwd_mfma_kernel<D, CAUSAL, PASS_DKV>;
   hipError_t e = ensure_lds_attribute<kq, BYTES_DQ>();
   if (e == hipSuccess) e = ensure_lds_attribute<kkv, BYTES_DKV>();
   if (e != hipSuccess) return e;
   dim3 grid(((a.S + 127) / 128) * a.B * a.heads);
-  hipLaunchKernelGGL(kq, grid, dim3(256), BYTES_DQ, s, a);
-  hipLaunchKernelGGL(kkv, grid, dim3(256), BYTES_DKV, s, a);
+  if (side_by_side<D>(a, grid.x)) {
+    constexpr int BYTES_BOTH = BYTES_DKV + kBothMaxSeq * 4;
+    constexpr auto kboth = attn_bwd_mfma_kernel<D, CAUSAL, PASS_BOTH>;
+    e = ensure_lds_attribute<kboth, BYTES_BOTH>();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kboth, dim3(2 * grid.x), dim3(256), BYTES_DKV + a.S * 4, s, a, (int)grid.x);
+    if (a.dqkv_colsum != nullptr && a.dqkv_colsum_parts != nullptr) *a.dqkv_colsum_parts = a.B * ((a.S + 127) / 128);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(kq, grid, dim3(256), BYTES_DQ, s, a, 0);
+  hipLaunchKernelGGL(kkv, grid, dim3(256), BYTES_DKV, s, a, 0);
   if (a.dqkv_colsum != nullptr && a.dqkv_colsum_parts != nullptr) *a.dqkv_colsum_parts = a.B * ((a.S + 127) / 128);
   return hipGetLastError();
 }

@@ -320,6 +320,33 @@ def test_attention_forward_backward(B, dtype, impl, causal, batch, seq, heads, d
         assert_close(got[:, sl], dqkv_ref[:, sl], TOL[dtype], "kernels got[:, sl] %s" % (name,), floor=floor)
 
 
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("seq,heads,d", [(1024, 1, 64), (1025, 1, 64), (1023, 2, 128)])
+def test_attention_at_the_longest_sequence_of_the_one_launch_backward(B, causal, seq, heads, d):
+    test_attention_forward_backward(B, 1, 2, causal, 1, seq, heads, d)
+
+
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("batch,seq,heads,d", [(8, 129, 16, 64), (8, 129, 17, 64), (3, 200, 27, 128)])
+def test_attention_backward_in_one_launch_and_in_two_is_the_same(B, causal, batch, seq, heads, d):
+    """A whole batch (256 workgroups a pass: one launch; 272 and 162: two) against its samples one by one (one launch)."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seq + heads)
+    H, T = heads * d, batch * seq
+    qkv = torch.randn(T, 3 * H, generator=gen, device=DEV).bfloat16()
+    dctx = torch.randn(T, H, generator=gen, device=DEV).bfloat16()
+    ctx, dqkv = _empty((T, H), 1), _empty((T, 3 * H), 1)
+    lse = torch.empty(batch * heads * seq, device=DEV)
+    B.bk_attention_fwd(qkv, ctx, lse, batch, seq, heads, causal, impl=2)
+    B.bk_attention_bwd(qkv, ctx, lse, dctx, dqkv, batch, seq, heads, causal, impl=2)
+    one = _empty((seq, 3 * H), 1)
+    for b in range(batch):
+        rows = slice(b * seq, (b + 1) * seq)
+        B.bk_attention_bwd(qkv[rows], ctx[rows], lse[b * heads * seq:(b + 1) * heads * seq], dctx[rows], one, 1, seq,
+                           heads, causal, impl=2)
+        assert torch.equal(one, dqkv[rows]), b
+
+
 @pytest.mark.parametrize("T,K,N", [(1, 1, 1), (31, 33, 65), (32, 64, 256), (100, 72, 200), (513, 130, 2049)])
 def test_fp32_matrix_core_gemm(B, T, K, N):
     """The fp32 kernel at tile and step edges, unaligned lengths (no 16-byte loads) and on both sides of its split of K
