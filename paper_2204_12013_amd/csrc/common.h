@@ -113,12 +113,17 @@ struct GemmDesc {
 struct GradReduceSeg { const float* p0; float* out0; const float* p1; float* out1; int N, parts, block0; };
 struct GradReduceBatch { GradReduceSeg seg[8]; int n; };
 
-// up to MAX independent GEMMs for one launch; first[p] = index of problem p's first workgroup.
-// Workgroups from first[MAX] on (there are grad_reduce_blocks(tail) of them) do the reductions of `tail`.
+// up to MAX independent GEMMs for one launch; first[p] = index of problem p's first tile, counted over all problems.
+// The first `chains` workgroups take the half-width tiles at the problems' edges (strip0 counts them like first),
+// `chain` of them each, one after the other; one workgroup per tile follows, and behind them
+// grad_reduce_blocks(tail) workgroups do the reductions of `tail`.
 struct GemmGroup {
   static constexpr int MAX = 4;
   GemmDesc d[MAX];
   int first[MAX + 1];
+  int tiles_m[MAX], tiles_n[MAX];   // tiles that are not edge strips
+  int strip0[MAX + 1];
+  int chain, chains;
   int n;
   int whole_launch_ranges;   // 1: the XCD ranges are cut from the concatenated tile sequences of all problems
   GradReduceBatch tail;

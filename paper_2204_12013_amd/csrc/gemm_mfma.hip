@@ -7,7 +7,7 @@
 //
 // A workgroup of 4 wavefronts (2 x 2) owns a (64*WM) x (64*WN) output tile and
 // walks K in slices of 64 that stream global -> LDS directly through a ring of
-// buffers, under a hand-ordered, software-pipelined loop (see gemm_pl_body).
+// buffers, under a hand-ordered, software-pipelined loop (see gemm_pl_tile).
 // Row counts and the contraction length may be anything (the last slice's
 // missing part is loaded as zeros by the buffer range check); only the
 // contiguous dimension of every operand has to be a multiple of 8.  Operands whose contraction index is contiguous
@@ -18,8 +18,10 @@
 // registers or re-laid-out in HBM.  The accumulators leave through a
 // wavefront-private LDS staging area so that bias / residual / GELU inputs are
 // read and results written with 16-byte row-contiguous accesses.
+#include <math.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -585,21 +587,18 @@ __device__ __forceinline__ void wait_loads_and_lds() {
 
 // Slices are kept in NS LDS buffers used round-robin; the global -> LDS loads of slice kt + NS - 1 ... are
 // in flight while slice kt feeds the MFMAs, i.e. a load has NS - 1 slices of MFMA time to land.
-// pid: position of this workgroup's tile in the tile sequence of problem d (the caller has applied xcd_range)
+// The tile whose first row and column are m0 and n0.
 template <int WM, int WN, bool A_K, bool B_K, int EPI, int NS>
-__device__ __forceinline__ void gemm_pl_body(const GemmDesc& d, int pid) {
+__device__ __forceinline__ void gemm_pl_tile(const GemmDesc& d, int m0, int n0) {
   typedef SmemPl<WM, WN, NS, EPI == EPI_BIAS_GELU> SM;
   typedef PlLoop<WM, WN, A_K, B_K> Loop;
-  constexpr int BM = SM::BM, BN = SM::BN, NL = Loop::NL;
+  constexpr int NL = Loop::NL;
   constexpr unsigned STAGE = SM::STAGE_BYTES, RING = NS * STAGE;
   static_assert((NS - 1) * NL + (WM * WN <= 8 ? EpiOperands<WM, WN, EPI>::NLOADS : 0) < 64,
                 "too many loads in flight for the vmcnt counter");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  int tile_m, tile_n;
-  tile_walk(pid, (d.M + BM - 1) / BM, (d.N + BN - 1) / BN, &tile_m, &tile_n);
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
   const long lda = A_K ? d.a_sm : d.a_sk;
   const long ldb = B_K ? d.b_sn : d.b_sk;
 
@@ -777,16 +776,13 @@ __device__ __forceinline__ void phase_barrier() {
 }
 
 template <bool A_K, bool B_K, int EPI>
-__device__ __forceinline__ void gemm_ph_body(const GemmDesc& d, int pid) {
+__device__ __forceinline__ void gemm_ph_tile(const GemmDesc& d, int m0, int n0) {
   typedef SmemPl<4, 4, 2, EPI == EPI_BIAS_GELU> SM;
   typedef PhLoop<A_K, B_K> Loop;
   static_assert(SM::MAIN_BYTES == 2 * Loop::STAGE, "");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  int tile_m, tile_n;
-  tile_walk(pid, (d.M + 255) / 256, (d.N + 255) / 256, &tile_m, &tile_n);
-  const int m0 = tile_m * 256, n0 = tile_n * 256;
   const long lda = A_K ? d.a_sm : d.a_sk;
   const long ldb = B_K ? d.b_sn : d.b_sk;
 
@@ -902,8 +898,10 @@ template <int WM, int WN, bool A_K, bool B_K, int EPI, int NS, int MINB>
 __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_kernel(GemmDesc d) {
   constexpr int BM = 64 * WM, BN = 64 * WN;
   const int pid = xcd_range(blockIdx.x, ((d.M + BM - 1) / BM) * ((d.N + BN - 1) / BN));
-  if constexpr (WM == 4 && WN == 4) gemm_ph_body<A_K, B_K, EPI>(d, pid);
-  else gemm_pl_body<WM, WN, A_K, B_K, EPI, NS>(d, pid);
+  int tile_m, tile_n;
+  tile_walk(pid, (d.M + BM - 1) / BM, (d.N + BN - 1) / BN, &tile_m, &tile_n);
+  if constexpr (WM == 4 && WN == 4) gemm_ph_tile<A_K, B_K, EPI>(d, tile_m * BM, tile_n * BN);
+  else gemm_pl_tile<WM, WN, A_K, B_K, EPI, NS>(d, tile_m * BM, tile_n * BN);
 }
 
 // Several weight-gradient problems in one launch: workgroup b works on problem p where
@@ -911,18 +909,42 @@ __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_kernel(GemmDesc d) {
 // most of them do not fill a whole number of rounds of the 256 CUs on their own (1024 x 1024 outputs
 // are 64 tiles of 128 x 128); launched together their tiles pack, and a CU goes from one problem's
 // tile to the next one's without the chip draining in between.
+// With 256 x 256 tiles a remainder of up to 128 rows or columns at a matrix' edge is covered by 128 x 256 or 256 x 128
+// tiles (see edge_strips): a launch of 1600-wide matrices has 456 tiles and 76 strips instead of 532 tiles, i.e. two
+// rounds of the 256 CUs instead of three.  4096 tokens, 1600 x 6400 layers: 286 us, 293 us as 128 x 256 tiles; the rounds
+// are 143 us each, 90 us of them main loop at the clock that 256 busy CUs leave, the rest fp32 reads and writes.
 template <int WM, int WN, int NS, int MINB>
 __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_group_kernel(GemmGroup g) {
-  const int total = g.first[GemmGroup::MAX];
-  if ((int)blockIdx.x >= total) {                  // behind the GEMM tiles: the reductions riding along
+  const int total = g.first[GemmGroup::MAX], wg = (int)blockIdx.x - g.chains;
+  if (wg >= total) {                               // behind the GEMM tiles: the reductions riding along
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    colreduce_batch_block(g.tail, (int)blockIdx.x - total, (float*)smem_raw);
+    colreduce_batch_block(g.tail, wg - total, (float*)smem_raw);
     return;
+  }
+  if constexpr (WM == 4 && WN == 4) {
+    if (wg < 0) {
+      const int begin = (int)blockIdx.x * g.chain, end = min(begin + g.chain, g.strip0[GemmGroup::MAX]);
+      for (int i = begin; i < end; ++i) {
+        int p = 0;
+#pragma unroll
+        for (int q = 1; q < GemmGroup::MAX; ++q)
+          if (q < g.n && i >= g.strip0[q]) p = q;
+        const GemmDesc& d = g.d[p];
+        const int along_n = g.tiles_m[p] * 256 < d.M ? (d.N + 255) / 256 : 0;   // strips of the last rows come first
+        const int j = i - g.strip0[p];
+        // the loads of a tile are counted from nothing in flight, and its LDS is free in every wavefront
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        __syncthreads();
+        if (j < along_n) gemm_pl_tile<2, 4, false, false, EPI_ACC_F32, 3>(d, g.tiles_m[p] * 256, j * 256);
+        else gemm_pl_tile<4, 2, false, false, EPI_ACC_F32, 3>(d, (j - along_n) * 256, g.tiles_n[p] * 256);
+      }
+      return;
+    }
   }
   // g.whole_launch_ranges: every XCD takes one contiguous range of the CONCATENATED tile sequences, so that
   // a problem's operands go to the L2s of the two or three XCDs its range spans instead of to all eight
   // (launches of one round); otherwise each problem is spread over all XCDs, a range per XCD inside it.
-  const int b = g.whole_launch_ranges ? xcd_range(blockIdx.x, total) : (int)blockIdx.x;
+  const int b = g.whole_launch_ranges ? xcd_range(wg, total) : wg;
   int p = 0;
 #pragma unroll
   for (int q = 1; q < GemmGroup::MAX; ++q)
@@ -935,8 +957,10 @@ __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_group_kernel(GemmGroup
       if (q > p && q < g.n) end = g.first[q];
     local = xcd_range(local, end - g.first[p]);
   }
-  if constexpr (WM == 4 && WN == 4) gemm_ph_body<false, false, EPI_ACC_F32>(g.d[p], local);
-  else gemm_pl_body<WM, WN, false, false, EPI_ACC_F32, NS>(g.d[p], local);
+  int tile_m, tile_n;
+  tile_walk(local, g.tiles_m[p], g.tiles_n[p], &tile_m, &tile_n);
+  if constexpr (WM == 4 && WN == 4) gemm_ph_tile<false, false, EPI_ACC_F32>(g.d[p], tile_m * 256, tile_n * 256);
+  else gemm_pl_tile<WM, WN, false, false, EPI_ACC_F32, NS>(g.d[p], tile_m * 64 * WM, tile_n * 64 * WN);
 }
 
 template <int WM, int WN, bool A_K, bool B_K, int EPI, int NS>
@@ -1345,26 +1369,58 @@ static hipError_t launch_form(hipStream_t s, const GemmDesc& d) {
   }
 }
 
+// How a launch of 256 x 256 tiles covers an M x N output: tm x tn of them, and strips half as wide along an edge whose
+// remainder needs no more.
+static int edge_strips(int M, int N, int* tm, int* tn) {
+  const bool low = M > 256 && M % 256 > 0 && M % 256 <= 128, right = N > 256 && N % 256 > 0 && N % 256 <= 128;
+  *tm = low ? M / 256 : (M + 255) / 256;
+  *tn = right ? N / 256 : (N + 255) / 256;
+  return (low ? (N + 255) / 256 : 0) + (right ? *tm : 0);
+}
+// What a strip of a launch of 256 x 256 tiles takes of a tile's time: 0.67 at 64 slices (from the coefficients above)
+static float strip_share(float slices) { return (9.5f + 0.97f * slices) / (28.8f + 1.223f * slices); }
+
 template <int WM, int WN, int NS>
 static hipError_t launch_group_cfg(hipStream_t s, GemmGroup& g) {
   typedef SmemPl<WM, WN, NS, false> SM;
-  constexpr auto kern = gemm_mfma_pl_group_kernel<WM, WN, NS, (2 * SM::BYTES <= 160 * 1024 ? 2 : 1)>;
-  const hipError_t e = ensure_lds_attribute<kern, SM::BYTES>();
+  constexpr bool STRIPS = WM == 4 && WN == 4;
+  constexpr int BYTES = STRIPS && SmemPl<2, 4, 3>::BYTES > SM::BYTES ? SmemPl<2, 4, 3>::BYTES : SM::BYTES;
+  static_assert(!STRIPS || (SmemPl<4, 2, 3>::BYTES <= BYTES && BYTES <= 160 * 1024), "");
+  constexpr auto kern = gemm_mfma_pl_group_kernel<WM, WN, NS, (2 * BYTES <= 160 * 1024 ? 2 : 1)>;
+  const hipError_t e = ensure_lds_attribute<kern, BYTES>();
   if (e != hipSuccess) return e;
-  int total = 0;
+  int total = 0, strips = 0;
+  long slices = 0;
   for (int i = 0; i < g.n; ++i) {
     g.first[i] = total;
-    total += ((g.d[i].M + 64 * WM - 1) / (64 * WM)) * ((g.d[i].N + 64 * WN - 1) / (64 * WN));
+    g.strip0[i] = strips;
+    if (STRIPS) {
+      strips += edge_strips(g.d[i].M, g.d[i].N, &g.tiles_m[i], &g.tiles_n[i]);
+    } else {
+      g.tiles_m[i] = (g.d[i].M + 64 * WM - 1) / (64 * WM);
+      g.tiles_n[i] = (g.d[i].N + 64 * WN - 1) / (64 * WN);
+    }
+    total += g.tiles_m[i] * g.tiles_n[i];
+    slices += k_slices(g.d[i].K);
   }
-  for (int i = g.n; i <= GemmGroup::MAX; ++i) g.first[i] = total;
+  for (int i = g.n; i <= GemmGroup::MAX; ++i) {
+    g.first[i] = total;
+    g.strip0[i] = strips;
+  }
+  // As many strips in a row as fit the rounds of the launch (three in two rounds), started first: the CUs that take
+  // them finish with the others, where strips left for the end would have added a round of their own.
+  const float share = strip_share((float)slices / g.n);
+  const float rounds = ceilf(((float)total + share * (float)strips) / 256.f);
+  g.chain = strips > 0 ? std::max(1, (int)(rounds / share + 0.05f)) : 1;
+  g.chains = (strips + g.chain - 1) / g.chain;
   // One round of tiles: XCD ranges over the whole launch halve what the L2s fetch (measured at the
   // BERT-large-shaped stage: 231 instead of 440 MiB per launch, 1.3 x the operands) at the same run time.
   // Over several rounds the per-problem ranges are faster (GPT-2-shaped stage: 288 against 302 us), so
   // they stay there.
-  g.whole_launch_ranges = total <= 256 * (2 * SM::BYTES <= 160 * 1024 ? 2 : 1) ? 1 : 0;
-  static_assert(SM::BYTES >= kReduceLdsFloats * 4, "the tail workgroups use the front of the tile ring");
-  total += grad_reduce_blocks(g.tail);
-  hipLaunchKernelGGL(kern, dim3(total), dim3(256), SM::BYTES, s, g);
+  g.whole_launch_ranges = total <= 256 * (2 * BYTES <= 160 * 1024 ? 2 : 1) ? 1 : 0;
+  static_assert(BYTES >= kReduceLdsFloats * 4, "the tail workgroups use the front of the tile ring");
+  total += g.chains + grad_reduce_blocks(g.tail);
+  hipLaunchKernelGGL(kern, dim3(total), dim3(256), BYTES, s, g);
   return hipGetLastError();
 }
 
@@ -1402,7 +1458,12 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
     long tiles = 0;
     double slices = 0;
     for (int i = 0; i < n; ++i) {
-      const long ti = (long)((d[i].M + 64 * wm - 1) / (64 * wm)) * ((d[i].N + 64 * wn - 1) / (64 * wn));
+      long ti = (long)((d[i].M + 64 * wm - 1) / (64 * wm)) * ((d[i].N + 64 * wn - 1) / (64 * wn));
+      if (codes[c] == 44) {
+        int tm, tn;
+        const int strips = edge_strips(d[i].M, d[i].N, &tm, &tn);
+        ti = (long)tm * tn + (long)ceilf(strips * strip_share((float)k_slices(d[i].K)));
+      }
       tiles += ti;
       slices += (double)ti * k_slices(d[i].K);
     }

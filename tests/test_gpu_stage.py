@@ -594,3 +594,32 @@ def test_fp32_weight_gradients_as_one_launch_and_singly(B, hidden, heads, ffn):
     check_grads(hz.succ.own_g.cpu().numpy(), ref.G_succ, sc.hidden, sc.ffn, TOL[sc.dtype], "successor")
     st.stage_destroy()
     hz.succ.stage_destroy()
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,seq", [(264, 3, 1288, 96), (320, 5, 640, 333), (640, 10, 1288, 200), (1600, 25, 6400, 64)])
+def test_weight_gradients_with_edge_strips_are_those_of_the_small_tiles(B, hidden, heads, ffn, seq):
+    """256 x 256 tiles leave remainders of 8, 64 and 128 rows or columns to strips of half the width (alone, in a corner,
+    and several to a workgroup: 1600 x 6400); the matrices' gradients must have the bits of a run with 64 x 64 tiles."""
+    sc = synth.StageConfig("strip", 0, 1, hidden, heads, ffn, seq, 1, 1, 1, 4, 1, 2, 61)
+    grads = []
+    for tile in (44, 11):
+        B.bk_gemm_tile(tile)
+        try:
+            inp, st, hz = _build(B, sc)
+            hz.begin_iteration()
+            hz.run(st.stage_schedule())
+            hz.sync()
+        finally:
+            B.bk_gemm_tile(0)
+        parts, at = {}, 0
+        for name in synth.PARAM_NAMES:
+            shape = synth.param_shapes(hidden, ffn)[name]
+            numel = int(np.prod(shape))
+            parts[name] = st.own_g.reshape(-1)[at:at + numel].clone()
+            at += numel
+        grads.append(parts)
+        st.stage_destroy()
+        hz.succ.stage_destroy()
+    assert at == st.own_g.numel()
+    for name in ("Wqkv", "Wo", "W1", "W2"):
+        assert grads[0][name].abs().max() > 0 and torch.equal(grads[0][name], grads[1][name]), name
