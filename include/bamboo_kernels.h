@@ -107,7 +107,8 @@ int bk_adam(int dtype, int64_t n, const float* g, float* master, float* m, float
 int bk_embedding_fwd(int dtype, int T, int seq, int H, int V, const int32_t* ids, const void* E_tok, const void* E_pos,
                      void* out, void* stream);
 /* dE_tok[V,H] (fp32) += rows of g[T,H] scattered by ids, dE_pos[seq,H] (fp32) += rows of g summed over
- * the samples.  No atomics: rows hit by several tokens are added in token order. */
+ * the samples.  No atomics: rows hit by several tokens are added in token order.  Any H and any alignment
+ * (H a multiple of 8 with g 32-byte aligned is faster). */
 int bk_embedding_bwd(int dtype, int T, int seq, int H, int V, const int32_t* ids, const void* g, float* dE_tok,
                      float* dE_pos, void* stream);
 /* Back: per token t, lse[t] = log sum_v exp(logits[t,v]) and loss_tok[t] = lse[t] - logits[t,labels[t]]

@@ -41,14 +41,31 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(int Tn, int S, int H, in
 // token; the workgroup of the first occurrence of an id does the whole sum, the others leave at once.
 // The time is the chain of the most frequent id: with Zipf-distributed ids one row of the table collects a tenth of
 // the tokens.  So the tokens of an id are first listed in LDS (in order), then their rows are fetched 16 at a time
-// before the first is added; a thread owns 8 columns (16-byte loads), so one pass covers 2048 of them.  4096 tokens x
+// before the first is added; a thread owns 8 columns, so one pass covers 2048 of them.  4096 tokens x
 // 1600 columns, vocabulary 50304: 1117 us before (256 columns per pass, one row in flight), 86 us now.
+// VEC: H a multiple of 8 and g aligned to a vector of 8, a thread's columns are neighbours and come in one load.
+// Otherwise (any H, any alignment) they lie 256 apart and come one by one, as many loads in flight for fewer rows.
 constexpr int kEmbList = 4096;      // tokens listed at a time
-constexpr int kEmbAhead = 16;       // rows in flight per thread
-template <typename T>
+template <typename T, bool VEC>
+struct EmbColumns {
+  typedef typename V8<T>::type vec;
+  static constexpr int AHEAD = VEC ? 16 : 4;       // rows in flight per thread
+  __device__ static __forceinline__ int at(int c0, int e) {
+    return c0 + (VEC ? (int)threadIdx.x * 8 + e : (int)threadIdx.x + 256 * e);
+  }
+  __device__ static __forceinline__ vec load(const T* row, int c0, int H) {
+    if constexpr (VEC) return *(const vec*)(row + at(c0, 0));
+    vec x;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = row[min(at(c0, e), H - 1)];
+    return x;
+  }
+};
+template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void embed_bwd_tok_kernel(int Tn, int H, int V, const int* __restrict__ ids,
                                                             const T* __restrict__ g, float* __restrict__ dEtok) {
-  typedef typename V8<T>::type vec;
+  typedef EmbColumns<T, VEC> Cols;
+  typedef typename Cols::vec vec;
   __shared__ int list[kEmbList];
   __shared__ int count[2][4];
   const int t = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -57,8 +74,7 @@ __global__ __launch_bounds__(256) void embed_bwd_tok_kernel(int Tn, int H, int V
   for (int u = tid; u < t; u += 256) earlier |= clamp_id(ids[u], V) == id;
   if (__syncthreads_or(earlier)) return;
   for (int c0 = 0; c0 < H; c0 += 2048) {
-    const int c = c0 + tid * 8;
-    const bool live = c < H;                       // H is a multiple of 8
+    const bool live = Cols::at(c0, 0) < H;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int first = t; first < Tn; first += kEmbList) {
       const int last = min(Tn, first + kEmbList);
@@ -77,17 +93,17 @@ __global__ __launch_bounds__(256) void embed_bwd_tok_kernel(int Tn, int H, int V
       __syncthreads();
       if (live) {
         int i = 0;
-        for (; i + kEmbAhead <= n; i += kEmbAhead) {
-          vec x[kEmbAhead];
+        for (; i + Cols::AHEAD <= n; i += Cols::AHEAD) {
+          vec x[Cols::AHEAD];
 #pragma unroll
-          for (int j = 0; j < kEmbAhead; ++j) x[j] = *(const vec*)(g + (long)list[i + j] * H + c);
+          for (int j = 0; j < Cols::AHEAD; ++j) x[j] = Cols::load(g + (long)list[i + j] * H, c0, H);
 #pragma unroll
-          for (int j = 0; j < kEmbAhead; ++j)
+          for (int j = 0; j < Cols::AHEAD; ++j)
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] += to_f32<T>(x[j][e]);
         }
         for (; i < n; ++i) {
-          const vec x = *(const vec*)(g + (long)list[i] * H + c);
+          const vec x = Cols::load(g + (long)list[i] * H, c0, H);
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc[e] += to_f32<T>(x[e]);
         }
@@ -95,9 +111,10 @@ __global__ __launch_bounds__(256) void embed_bwd_tok_kernel(int Tn, int H, int V
       __syncthreads();                             // the list is free for the next stretch
     }
     if (live) {
-      float* o = dEtok + (long)id * H + c;
+      float* o = dEtok + (long)id * H;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] += acc[e];
+      for (int e = 0; e < 8; ++e)
+        if (VEC || Cols::at(c0, e) < H) o[Cols::at(c0, e)] += acc[e];
     }
   }
 }
@@ -222,11 +239,14 @@ hipError_t launch_embed_bwd(hipStream_t s, int dtype, int T, int S, int H, int V
                             float* dEtok, float* dEpos) {
   if (T <= 0) return hipSuccess;
   const dim3 gp(S < T ? S : T, (H + 255) / 256);
+  const bool vec = H % 8 == 0 && ((uintptr_t)g & (dtype == 1 ? 15 : 31)) == 0;
   if (dtype == 1) {
-    hipLaunchKernelGGL(embed_bwd_tok_kernel<bf16_t>, dim3(T), dim3(256), 0, s, T, H, V, ids, (const bf16_t*)g, dEtok);
+    const auto kern = vec ? embed_bwd_tok_kernel<bf16_t, true> : embed_bwd_tok_kernel<bf16_t, false>;
+    hipLaunchKernelGGL(kern, dim3(T), dim3(256), 0, s, T, H, V, ids, (const bf16_t*)g, dEtok);
     hipLaunchKernelGGL(embed_bwd_pos_kernel<bf16_t>, gp, dim3(256), 0, s, T, S, H, (const bf16_t*)g, dEpos);
   } else {
-    hipLaunchKernelGGL(embed_bwd_tok_kernel<float>, dim3(T), dim3(256), 0, s, T, H, V, ids, (const float*)g, dEtok);
+    const auto kern = vec ? embed_bwd_tok_kernel<float, true> : embed_bwd_tok_kernel<float, false>;
+    hipLaunchKernelGGL(kern, dim3(T), dim3(256), 0, s, T, H, V, ids, (const float*)g, dEtok);
     hipLaunchKernelGGL(embed_bwd_pos_kernel<float>, gp, dim3(256), 0, s, T, S, H, (const float*)g, dEpos);
   }
   return hipGetLastError();

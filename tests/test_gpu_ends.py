@@ -147,3 +147,30 @@ def test_embedding_gradient_beyond_one_list_and_one_column_pass(B, dtype, V, S, 
 @pytest.mark.parametrize("dtype,T,V", [(1, 3, 8), (0, 2, 2056), (1, 5, 8200)])
 def test_softmax_cross_entropy_at_the_edges_of_its_vector_passes(B, dtype, T, V):
     test_softmax_cross_entropy(B, dtype, T, V)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("H", [1, 13, 255, 2051, 24])
+def test_embedding_gradient_of_any_width_and_alignment(B, dtype, H):
+    """Widths that are no multiple of 8 (one, two and nine columns to a thread) and a gradient that starts in the middle
+    of a 16-byte line: right sums, in token order, and nothing written behind either table."""
+    rng = np.random.default_rng(H + dtype)
+    V, S, Bsz = 11, 7, 9
+    T = S * Bsz
+    ids = synth.zipf_ids(rng, V, T)
+    ids[-1] = V - 1                                      # the last row of both g and the table
+    g = synth.round_to_storage(rng.normal(0, 1, (T, H)), dtype)
+    for shift in (0, 1):
+        act = torch.bfloat16 if dtype == 1 else torch.float32
+        buf = torch.zeros(T * H + 16, dtype=act, device=DEV)
+        buf[shift:shift + T * H] = B.to_device(g, dtype).reshape(-1)
+        d_g = buf[shift:shift + T * H].view(T, H)
+        gt, gp = torch.full((V + 2, H), 3.0, device=DEV), torch.full((S + 2, H), 3.0, device=DEV)
+        B.bk_embedding_bwd(_dev_ids(ids), d_g, gt[:V], gp[:S])
+        want_t, want_p = np.full((V, H), 3.0), np.full((S, H), 3.0)
+        np.add.at(want_t, ids, g.astype(np.float64))
+        np.add.at(want_p, np.arange(T) % S, g.astype(np.float64))
+        # sums of at most T values of magnitude below 6 in fp32
+        assert np.abs(gt[:V].cpu().numpy() - want_t).max() < T * 2.0 ** -24 * 6 * T
+        assert np.abs(gp[:S].cpu().numpy() - want_p).max() < T * 2.0 ** -24 * 6 * T
+        assert bool((gt[V:] == 3.0).all()) and bool((gp[S:] == 3.0).all())
