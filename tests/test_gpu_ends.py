@@ -174,3 +174,40 @@ def test_embedding_gradient_of_any_width_and_alignment(B, dtype, H):
         assert np.abs(gt[:V].cpu().numpy() - want_t).max() < T * 2.0 ** -24 * 6 * T
         assert np.abs(gp[:S].cpu().numpy() - want_p).max() < T * 2.0 ** -24 * 6 * T
         assert bool((gt[V:] == 3.0).all()) and bool((gp[S:] == 3.0).all())
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("V,first,count", [(64, 0, 8), (4104, 0, 8), (4104, 1000, 1048), (8200, 0, 8192), (16400, 8, 16000)])
+def test_softmax_cross_entropy_with_masked_logits(B, dtype, V, first, count):
+    """-inf logits (masked ids) in front, in the middle and in all but the last vector of a row add nothing to its sum.
+    Bound: the sum of V exponentials in fp32 is off by a few ulps, its logarithm by as much absolutely; 1e-5 is 80 ulps of
+    1 and, for the final addition, more than one of 16."""
+    rng = np.random.default_rng(V + first)
+    T = 3
+    x = synth.round_to_storage(rng.normal(0, 3.0, (T, V)), dtype).astype(np.float64)
+    x[:, first:first + count] = -np.inf
+    labels = np.full(T, (first + count) % V, dtype=np.int32)
+    m = x.max(axis=1)
+    lse = m + np.log(np.exp(x - m[:, None]).sum(axis=1))
+    logits = torch.from_numpy(x).to(DEV).to(torch.bfloat16 if dtype == 1 else torch.float32)
+    got, tok = torch.empty(T, device=DEV), torch.empty(T, device=DEV)
+    B.bk_softmax_xent_fwd(logits, _dev_ids(labels), got, tok)
+    assert np.abs(got.cpu().numpy() - lse).max() < 1e-5
+    assert np.abs(tok.cpu().numpy() - (lse - x[np.arange(T), labels])).max() < 2e-5
+    B.bk_softmax_xent_bwd(logits, _dev_ids(labels), got, 1.0, logits)
+    assert bool(torch.isfinite(logits).all()) and bool((logits[:, first:first + count] == 0).all())
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("V", [64, 4104])
+def test_softmax_cross_entropy_of_rows_without_a_finite_value_or_with_nan(B, dtype, V):
+    """A NaN logit must not get lost (alone, as one thread's whole share, as the whole row); rows whose maximum is not
+    finite have no finite loss either."""
+    x = torch.randn(6, V, device=DEV).to(torch.bfloat16 if dtype == 1 else torch.float32)
+    x[1, 5] = x[2, 8:16] = x[3] = float("nan")
+    x[4] = -float("inf")
+    x[5, 3] = float("inf")
+    got, tok = torch.zeros(6, device=DEV), torch.zeros(6, device=DEV)
+    B.bk_softmax_xent_fwd(x, _dev_ids([1] * 6), got, tok)
+    assert bool(torch.isfinite(got[0])) and bool(torch.isfinite(tok[0]))
+    assert bool(torch.isnan(got[1:]).all()) and bool(torch.isnan(tok[1:]).all())
