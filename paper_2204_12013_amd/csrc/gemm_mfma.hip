@@ -341,6 +341,19 @@ typedef __attribute__((address_space(3))) short4_t* lds_short4_ptr;
 typedef __attribute__((ext_vector_type(4))) unsigned buf_rsrc;   // 128-bit buffer descriptor, wavefront-uniform
 constexpr unsigned kBufRange = 0x80000000u;                       // bytes addressable from a descriptor's base
 constexpr unsigned kBufOutside = 0x80000000u;                     // an offset beyond them: the load delivers zeros
+// Whether the offsets of a bm x bn output tile stay inside that range.  They count from the tile's first row: rows
+// are a leading dimension apart where the contraction index is contiguous (256 of them reach 2 GiB at 4.2 M elements a
+// row), otherwise the 64 steps of a slice are.  A tile that reaches beyond would be given zeros for its last rows, so it
+// is not offered for such operands; smaller ones are, and at last the vector-ALU kernel.
+static bool tile_in_reach(const GemmDesc& d, int bm, int bn) {
+  auto reach = [&](bool k_contiguous, long ld, int rows, int tile) {
+    const long steps = k_contiguous ? std::min(rows, tile) : std::min(d.K, BK);
+    return (steps - 1) * ld * 2 + (k_contiguous ? BK : tile) * 2;
+  };
+  const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1;
+  return reach(a_k, a_k ? d.a_sm : d.a_sk, d.M, bm) <= (long)kBufRange &&
+         reach(b_k, b_k ? d.b_sn : d.b_sk, d.N, bn) <= (long)kBufRange;
+}
 
 __device__ __forceinline__ buf_rsrc make_rsrc(const void* base) {
   const unsigned long b = (unsigned long)base;
@@ -1271,6 +1284,7 @@ static float rounds_of(long tiles, long slots) {
   return (float)full + (rest > 0 ? 0.75f + 0.25f * (float)rest / (float)slots : 0.f);
 }
 
+// *code = 0: no tile's loads reach that far
 static float choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, bool by_work, int* code, int* ns,
                          bool offer_43 = false) {
   const int nk = k_slices(d.K);
@@ -1278,13 +1292,14 @@ static float choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, bool 
   const int ntab = acc_form ? (int)(sizeof(kCostAcc) / sizeof(kCostAcc[0])) : (int)(sizeof(kCostStore) / sizeof(kCostStore[0]));
   float best = 0.f;
   bool found = false;
-  *code = 22;
+  *code = 0;
   *ns = 2;
   for (int i = 0; i < ntab; ++i) {
     const TileCost& t = tab[i];
     if (t.ns > nk && t.ns > 2) continue;
     if (t.code == 43 && !offer_43) continue;
     const int wm = t.code / 10, wn = t.code % 10;
+    if (!tile_in_reach(d, 64 * wm, 64 * wn)) continue;
     const long tiles = (long)((d.M + 64 * wm - 1) / (64 * wm)) * ((d.N + 64 * wn - 1) / (64 * wn));
     const long stage = (long)(wm + wn) * 64 * BK * 2, epi = 4L * 32 * (32 * wn + 4) * 4;
     const long lds = (t.ns * stage > epi ? t.ns * stage : epi) + extra_lds;
@@ -1324,8 +1339,9 @@ static int choose_split(const GemmDesc& d, bool b_k, long extra_lds) {
   for (int t = 1; t <= 2; ++t) {
     const long tiles = (long)((d.M + 32 * t - 1) / (32 * t)) * ((d.N + 32 * t - 1) / (32 * t));
     const long rounds = (tiles + 255) / 256;
+    if (!tile_in_reach(d, 32 * t, 32 * t)) continue;
     const float cost = rounds * (t == 1 ? (b_k ? 2.7f + 0.09f * nk : 1.5f + 0.16f * nk) : 4.0f + 0.18f * nk);
-    if (cost < best) {
+    if (cost < best || (code == 0 && pick == 0)) {
       best = cost;
       pick = t;
     }
@@ -1349,11 +1365,12 @@ static hipError_t launch_form(hipStream_t s, const GemmDesc& d) {
   int pick, ns;
   constexpr bool HAS_43 = A_K && !B_K && EPI == EPI_BIAS;
   choose_tile(d, EPI == EPI_ACC_F32, EPI == EPI_BIAS_GELU ? kGeluBytes : 0, d.shared_chip != 0, &pick, &ns, HAS_43 && !g_forced_stages);
-  if (g_forced_tile) {
-    pick = g_forced_tile;
+  const int forced = g_forced_tile == 43 && !HAS_43 ? 44 : (int)g_forced_tile;   // 256 x 192 where this form has it
+  if (forced && tile_in_reach(d, 64 * (forced / 10), 64 * (forced % 10))) {
+    pick = forced;
     ns = 2;
-    if (pick == 43 && !HAS_43) pick = 44;     // 256 x 192 where this form has it, the next larger tile otherwise
   }
+  if (pick == 0) return hipErrorNotSupported;
   if (EPI == EPI_MUL && d.tile_colsum != nullptr && d.tile_colsum_parts != nullptr)
     *d.tile_colsum_parts = (d.M + 64 * (pick / 10) - 1) / (64 * (pick / 10));   // one row of column sums per tile row
   if constexpr (HAS_43) {
@@ -1458,6 +1475,9 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
       if (e.code == codes[c] && e.ns == nss[c]) t = &e;
     if (!t) continue;
     const int wm = codes[c] / 10, wn = codes[c] % 10;
+    bool reached = true;
+    for (int i = 0; i < n; ++i) reached = reached && tile_in_reach(d[i], 64 * wm, 64 * wn);
+    if (!reached) continue;
     long tiles = 0;
     double slices = 0;
     for (int i = 0; i < n; ++i) {
@@ -1476,8 +1496,14 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
       best = cost;
     }
   }
-  if (g_forced_tile == 22 || g_forced_tile == 44 || g_forced_tile == 24 || g_forced_tile == 42) pick = g_forced_tile;
-  else if (g_forced_tile || g_forced_stages) return hipErrorNotSupported;   // a forced shape this launch does not offer
+  if (pick == 0) return hipErrorNotSupported;
+  if (g_forced_tile == 22 || g_forced_tile == 44 || g_forced_tile == 24 || g_forced_tile == 42) {
+    for (int i = 0; i < n; ++i)
+      if (!tile_in_reach(d[i], 64 * (g_forced_tile / 10), 64 * (g_forced_tile % 10))) return hipErrorNotSupported;
+    pick = g_forced_tile;
+  } else if (g_forced_tile || g_forced_stages) {
+    return hipErrorNotSupported;   // a forced shape this launch does not offer
+  }
   switch (pick) {
     case 44: return launch_group_cfg<4, 4, 2>(s, g);
     case 24: return launch_group_cfg<2, 4, 3>(s, g);

@@ -184,6 +184,34 @@ def test_any_row_count_and_contraction_tail(B, T, K, N):
         B.bk_gemm_tile(0)
 
 
+def test_operands_whose_rows_are_millions_long(B):
+    """A tile's loads count their offsets from its first row, and 256 rows of 4.26 M elements span more than the 2 GiB
+    that such a load reaches; with rows of 17.2 M 64 of them do, and only the 32-row tiles are left.  The last row must
+    count like the first, in both forms with contiguous rows.  Sums of powers of two: exact up to the rounding to bf16."""
+    for rows, cols, unit, tiles in ((256, 65 * 65536, 2.0 ** -10, (0, 44, 43)), (64, 262 * 65536, 2.0 ** -12, (0,))):
+        A = torch.zeros(rows, cols, dtype=torch.bfloat16, device=DEV)
+        A[0] = A[rows - 1] = 1
+        u = torch.full((8 * cols,), unit, dtype=torch.bfloat16, device=DEV)
+        bias = torch.zeros(8, dtype=torch.bfloat16, device=DEV)
+        for tile in tiles:
+            Y, dX = _empty((rows, 8), 1), _empty((8, rows), 1)
+            B.bk_gemm_tile(tile)
+            try:
+                B.bk_linear_fwd(A, u.view(cols, 8), bias, Y, impl=2 if tile else 0)      # Y = A W
+                B.bk_linear_bwd_input(u.view(8, cols), A, dX, impl=2 if tile else 0)     # dX = dY A^T
+            finally:
+                B.bk_gemm_tile(0)
+            for got in (Y, dX.t()):
+                assert torch.allclose(got[[0, -1]].float(), torch.tensor(cols * unit, device=DEV), rtol=2.0 ** -8), (rows, tile)
+                assert bool((got[1:-1] == 0).all()), (rows, tile)
+        if rows == 64:
+            with pytest.raises(B.BambooError) as e:
+                B.bk_linear_fwd(A, u.view(cols, 8), bias, Y, impl=2)       # the smallest tile without a split of K has 64 rows
+            assert e.value.status == B.E_STATE
+        del A, u
+        torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("dtype,impl", IMPLS)
 @pytest.mark.parametrize("T,N,K", GEMM_SHAPES)
 def test_linear_backward_variants(B, dtype, impl, T, N, K):
