@@ -173,7 +173,11 @@ def test_any_row_count_and_contraction_tail(B, T, K, N):
             B.bk_linear_fwd(Xd, Wd, bd, Y[:T])
             assert rel_l2(B.to_host(Y[:T]), h) < 2.0 ** -8 and bool((Y[T] == 7).all())
             B.bk_linear_fwd(Xd, Wd, bd, Y[:T], gelu_out=G[:T])
-            assert rel_l2(B.to_host(G[:T]), L.gelu(h)) < 2.0 ** -7 and bool((G[T] == 7).all())   # and the table's bf16 argument
+            # evaluated at the fp32 pre-activation: what a rounding of the exact values to bf16 costs, and fp32 errors
+            # (1e-5 of h at most), twice where they move a value over a rounding boundary
+            for got, want in ((G, L.gelu(h)), (Y, L.gelu_grad(h))):
+                rounded = synth.round_to_storage(want.astype(np.float32), 1).astype(np.float64)
+                assert rel_l2(B.to_host(got[:T]), want) < rel_l2(rounded, want) + 2e-5 and bool((got[T] == 7).all())
             B.bk_linear_bwd_input(dYd, Wd, dX[:T], mul=Md)
             assert rel_l2(B.to_host(dX[:T]), dx * Mu) < 2.0 ** -8 and bool((dX[T] == 7).all())
             B.bk_linear_bwd_weight(Xd, dYd, dW)
