@@ -76,7 +76,7 @@ uint64_t bk_colsum_static_max_floats(void);
 int bk_attention_fwd(int dtype, int impl, int batch, int seq, int heads, int d, int causal, const void* qkv, void* ctx,
                      float* lse, void* stream);
 /* dqkv[T,3H] from dctx[T,H], recomputing the probabilities from lse.
- * delta: fp32 scratch [batch,heads,seq]. */
+ * delta: fp32 [batch,heads,seq], set to rowsum(ctx * dctx) of each head. */
 int bk_attention_bwd(int dtype, int impl, int batch, int seq, int heads, int d, int causal, const void* qkv,
                      const void* ctx, const float* lse, const void* dctx, void* dqkv, float* delta, void* stream);
 

@@ -509,6 +509,7 @@ def bk_attention_fwd(qkv, ctx, lse, batch, seq, heads, causal, impl=0, stream=No
 
 
 def bk_attention_bwd(qkv, ctx, lse, dctx, dqkv, batch, seq, heads, causal, impl=0, stream=None):
+    """dqkv from dctx; returns delta = rowsum(ctx * dctx) per sample, head and position (fp32)."""
     import torch
     d = qkv.shape[1] // 3 // heads
     delta = torch.empty(batch * heads * seq, dtype=torch.float32, device=qkv.device)

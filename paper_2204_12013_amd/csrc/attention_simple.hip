@@ -172,6 +172,7 @@ __device__ __forceinline__ void bwd_dq_block(const AttnDesc& a, int blk, float* 
     const T* o = (const T*)a.ctx + ((long)b * a.S + qv) * H + h * D;
     const T* dO = dbase + (long)qv * H;
     delta = group16_sum(strided_dot<16>(o, dO, t, D));
+    if (t == 0 && qrow < a.S) a.delta[((long)b * a.heads + h) * a.S + qrow] = delta;   // for the caller
   }
   float dq[8] = {};
   const int kend = a.causal ? min(a.S, q0 + QT) : a.S;

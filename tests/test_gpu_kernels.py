@@ -352,6 +352,25 @@ def test_attention_forward_backward(B, dtype, impl, causal, batch, seq, heads, d
         assert_close(got[:, sl], dqkv_ref[:, sl], TOL[dtype], "kernels got[:, sl] %s" % (name,), floor=floor)
 
 
+@pytest.mark.parametrize("dtype,impl,seq,d", [(0, 0, 1, 32), (0, 0, 40, 64), (1, 0, 77, 40), (1, 1, 33, 64), (1, 0, 200, 64),
+                                             (1, 0, 3000, 64)])
+def test_attention_backward_returns_delta(B, dtype, impl, seq, d):
+    """The rows' sums of ctx * dctx come back from every path: the vector-ALU kernels, the matrix-core passes in one launch
+    and in two.  Bound: 128 products at most in fp32."""
+    act = torch.bfloat16 if dtype == 1 else torch.float32
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seq + d)
+    heads, batch = 2, 2
+    H, T = heads * d, batch * seq
+    qkv, dctx = (torch.randn(T, n, generator=gen, device=DEV).to(act) for n in (3 * H, H))
+    ctx, dqkv, lse = _empty((T, H), dtype), _empty((T, 3 * H), dtype), torch.empty(batch * heads * seq, device=DEV)
+    B.bk_attention_fwd(qkv, ctx, lse, batch, seq, heads, 0, impl=impl)
+    delta = B.bk_attention_bwd(qkv, ctx, lse, dctx, dqkv, batch, seq, heads, 0, impl=impl)
+    want = (ctx.double() * dctx.double()).view(batch, seq, heads, d).sum(-1).permute(0, 2, 1).reshape(-1)
+    size = (ctx.double() * dctx.double()).abs().view(batch, seq, heads, d).sum(-1).permute(0, 2, 1).reshape(-1)
+    assert ((delta.double() - want).abs() <= 128 * 2.0 ** -24 * size).all()
+
+
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("seq,heads,d", [(1024, 1, 64), (1025, 1, 64), (1023, 2, 128)])
 def test_attention_at_the_longest_sequence_of_the_one_launch_backward(B, causal, seq, heads, d):
