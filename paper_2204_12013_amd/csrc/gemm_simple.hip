@@ -114,11 +114,33 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& d) {
   return hipSuccess;
 }
 
+// Whether the products of a group may run side by side: none writes what another one reads or writes.  (Two gradients
+// added to the same matrix, one after the other, are a valid use of the group call.)
+static bool side_by_side(const GemmDesc* d, int n, long esize) {
+  struct Span { uintptr_t lo, hi; };
+  auto span = [](const void* p, long elements, long size) {
+    return Span{(uintptr_t)p, (uintptr_t)p + (uintptr_t)(elements * size)};
+  };
+  auto meet = [](const Span& x, const Span& y) { return x.lo < y.hi && y.lo < x.hi; };
+  for (int i = 0; i < n; ++i) {
+    const Span c = span(d[i].C, (long)d[i].M * d[i].N, 4);       // fp32 gradients
+    for (int j = 0; j < n; ++j) {
+      if (j == i) continue;
+      const GemmDesc& o = d[j];
+      if (meet(c, span(o.C, (long)o.M * o.N, 4)) ||
+          meet(c, span(o.A, (o.M - 1) * o.a_sm + (o.K - 1) * o.a_sk + 1, esize)) ||
+          meet(c, span(o.B, (o.N - 1) * o.b_sn + (o.K - 1) * o.b_sk + 1, esize)))
+        return false;
+    }
+  }
+  return true;
+}
+
 hipError_t launch_gemm_group(hipStream_t s, int dtype, const GemmDesc* d, int n, const GradReduceBatch* tail,
                              bool* tail_done) {
   if (tail_done) *tail_done = false;
   if (n > 1) {
-    bool plain = true;
+    bool plain = side_by_side(d, n, dtype == 1 ? 2 : 4);
     for (int i = 0; i < n; ++i) plain = plain && d[i].colsum_out == nullptr;
     if (plain) {
       const GradReduceBatch* riding = tail_done ? tail : nullptr;

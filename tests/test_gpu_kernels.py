@@ -137,6 +137,22 @@ def test_grouped_weight_gradients_equal_the_single_launches_bitwise(B, shapes):
     assert_close(single[0].cpu().numpy(), want, 1e-5, "kernels single[0].cpu().numpy()")
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_grouped_weight_gradients_into_the_same_matrix_are_added_in_order(B, dtype):
+    """Two problems that add to one matrix (and a third that adds to rows of it) are the single launches one after the other."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(dtype)
+    act = torch.bfloat16 if dtype == 1 else torch.float32
+    T, K, N = 96, 128, 72
+    Xs, dYs = ([torch.randn(T, n, generator=gen, device=DEV).to(act) for n in ns] for ns in ((K, K, 64), (N, N, N)))
+    init = torch.randn(K, N, generator=gen, device=DEV)
+    single, grouped = init.clone(), init.clone()
+    for X, dY, dW in zip(Xs, dYs, (single, single, single[32:96])):
+        B.bk_linear_bwd_weight(X, dY, dW)
+    B.bk_linear_bwd_weight_group(Xs, dYs, [grouped, grouped, grouped[32:96]])
+    assert torch.equal(single, grouped)
+
+
 def test_mfma_kernel_refuses_what_it_does_not_cover(B):
     X, W, b = _empty((12, 16), 1), _empty((16, 24), 1), _empty((24,), 1)
     with pytest.raises(B.BambooError) as e:
