@@ -1357,7 +1357,8 @@ static float choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, bool 
 //     512   3072  1024   11.0 / 10.8   22.9 / 18.4     12.9 / 12.1
 // i.e. splitting pays where one round of small tiles covers the output, and more the longer K is.  The choice depends
 // on the shape alone (not on the stream, nor on a forced tile): the sums are taken in another order than the tiles'.
-static int choose_split(const GemmDesc& d, bool b_k, long extra_lds) {
+// row_sums: the kernel may be asked for column sums, one row per tile row: not with more of them than the buffers hold.
+static int choose_split(const GemmDesc& d, bool b_k, long extra_lds, bool row_sums) {
   int code, ns;
   float best = choose_tile(d, false, extra_lds, false, &code, &ns);
   const int nk = k_slices(d.K);
@@ -1366,6 +1367,7 @@ static int choose_split(const GemmDesc& d, bool b_k, long extra_lds) {
     const long tiles = (long)((d.M + 32 * t - 1) / (32 * t)) * ((d.N + 32 * t - 1) / (32 * t));
     const long rounds = (tiles + 255) / 256;
     if (!tile_in_reach(d, 32 * t, 32 * t)) continue;
+    if (row_sums && (size_t)((d.M + 32 * t - 1) / (32 * t)) > reduce_max_partials()) continue;
     const float cost = rounds * (t == 1 ? (b_k ? 2.7f + 0.09f * nk : 1.5f + 0.16f * nk) : 4.0f + 0.18f * nk);
     if (cost < best || (code == 0 && pick == 0)) {
       best = cost;
@@ -1376,13 +1378,13 @@ static int choose_split(const GemmDesc& d, bool b_k, long extra_lds) {
 }
 
 template <bool A_K, bool B_K, int EPI>
-static hipError_t launch_form(hipStream_t s, const GemmDesc& d) {
+static hipError_t launch_form(hipStream_t s, GemmDesc d) {
   if (is_gelu(EPI)) {
     const hipError_t e = ensure_gelu_table(s);
     if (e != hipSuccess) return e;
   }
   if constexpr (EPI != EPI_ACC_F32) {
-    switch (d.tiled_only ? 0 : choose_split(d, B_K, is_gelu(EPI) ? kGeluBytes : 0)) {
+    switch (d.tiled_only ? 0 : choose_split(d, B_K, is_gelu(EPI) ? kGeluBytes : 0, EPI == EPI_MUL)) {
       case 1: return launch_split<1, 8, B_K, EPI>(s, d);
       case 2: return launch_split<2, 4, B_K, EPI>(s, d);
       default: break;
@@ -1397,8 +1399,11 @@ static hipError_t launch_form(hipStream_t s, const GemmDesc& d) {
     ns = 2;
   }
   if (pick == 0) return hipErrorNotSupported;
-  if (EPI == EPI_MUL && d.tile_colsum != nullptr && d.tile_colsum_parts != nullptr)
-    *d.tile_colsum_parts = (d.M + 64 * (pick / 10) - 1) / (64 * (pick / 10));   // one row of column sums per tile row
+  if (EPI == EPI_MUL && d.tile_colsum != nullptr && d.tile_colsum_parts != nullptr) {
+    const int rows = (d.M + 64 * (pick / 10) - 1) / (64 * (pick / 10));         // one row of column sums per tile row
+    if ((size_t)rows <= reduce_max_partials()) *d.tile_colsum_parts = rows;
+    else d.tile_colsum = nullptr;                                               // left to launch_gemm
+  }
   if constexpr (HAS_43) {
     if (pick == 43) {
       const int tiles = ((d.M + 255) / 256) * ((d.N + 191) / 192);

@@ -102,14 +102,12 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const GemmDesc& d) {
     hipError_t e = launch_colsum_acc(s, dtype, d.K, d.N, d.B, d.colsum_out, d.colsum_partial);
     if (e != hipSuccess) return e;
   }
-  if (dtype == 1) {
-    hipError_t e = launch_gemm_mfma(s, d);
-    if (e != hipErrorNotSupported) return e;
-  }
-  hipError_t e = dtype == 0 ? launch_gemm_f32(s, d) : hipErrorNotSupported;
+  const bool sums = d.tile_colsum != nullptr && d.tile_colsum_parts != nullptr;
+  if (sums) *d.tile_colsum_parts = 0;
+  hipError_t e = dtype == 1 ? launch_gemm_mfma(s, d) : launch_gemm_f32(s, d);
   if (e == hipErrorNotSupported) e = launch_gemm_simple(s, dtype, d);
   if (e != hipSuccess) return e;
-  if (d.tile_colsum != nullptr && d.tile_colsum_parts != nullptr)   // the MFMA epilogue would have summed the columns
+  if (sums && *d.tile_colsum_parts == 0)   // no epilogue summed the columns: fp32, vector ALU, too many rows of tiles
     return launch_colsum_partials(s, dtype, d.M, d.N, d.C, d.tile_colsum, d.tile_colsum_parts);
   return hipSuccess;
 }

@@ -475,21 +475,14 @@ int run_backward(bamboo_stage* st, int kind, int lane_id, int slot, const void* 
     // f = g W2 + b2
     d = gemm_nt(df, P(st->po.W2), dh, T, F, H, EPI_MUL);   // through the activation: times GELU'(h)
     d.aux_in = rec + r.dg;
-    // the column sums of dh (the gradient of b1) come out of the same kernel, one partial row per tile row
-    // (as long as the smallest tile's rows, T / 64, fit the partial buffer)
-    const bool fused_sum = (size_t)((T + 63) / 64) <= reduce_max_partials();
+    // the column sums of dh (the gradient of b1) come out of the same kernel, one partial row per tile row, where these
+    // fit the partial buffer, and from a pass of their own behind it otherwise
     int dh_parts = 0;
-    if (fused_sum) {
-      d.tile_colsum = (float*)(ws + w.p_dh);
-      d.tile_colsum_parts = &dh_parts;
-    }
+    d.tile_colsum = (float*)(ws + w.p_dh);
+    d.tile_colsum_parts = &dh_parts;
     BBCHK(p_gemm(st, s, K_DGRAD_FFN2, d));
-    if (fused_sum) {
-      if (!grad_reduce_add(&batch, F, dh_parts, (const float*)(ws + w.p_dh), G + st->po.b1, nullptr, nullptr))
-        return BAMBOO_E_STATE;
-    } else {
-      BBCHK(p_colsum(st, s, ws, T, F, dh, G + st->po.b1, w.p_dh, &batch));
-    }
+    if (!grad_reduce_add(&batch, F, dh_parts, (const float*)(ws + w.p_dh), G + st->po.b1, nullptr, nullptr))
+      return BAMBOO_E_STATE;
     // The four weight gradients of the layer wait until its end: their operands (df, dh, da, dqkv and the
     // record) all live that long, nothing in the layer depends on them, and launched together their tiles
     // share the rounds of the chip.

@@ -623,3 +623,18 @@ def test_weight_gradients_with_edge_strips_are_those_of_the_small_tiles(B, hidde
     assert at == st.own_g.numel()
     for name in ("Wqkv", "Wo", "W1", "W2"):
         assert grads[0][name].abs().max() > 0 and torch.equal(grads[0][name], grads[1][name]), name
+
+
+@pytest.mark.parametrize("seq,mb", [(512, 16), (514, 16), (1028, 16)])
+def test_column_sums_of_more_tile_rows_than_partial_rows(B, seq, mb):
+    """The bias gradient behind the activation's backward leaves one partial row per row of output tiles, 256 at most: 8192
+    tokens are that many 32-row tiles, 16384 that many 64-row ones.  On both sides of the limits the gradients are right
+    and nothing is written behind the partial rows (the reductions that follow in the workspace would show it)."""
+    sc = synth.StageConfig("rows", 0, 1, 64, 1, 72, seq, mb, 1, 1, 4, 1, 2, 71)
+    inp, st, hz = _build(B, sc)
+    hz.begin_iteration()
+    hz.run(st.stage_schedule())
+    hz.sync()
+    check_grads(st.own_g.cpu().numpy(), _oracle(sc, inp).G_own, sc.hidden, sc.ffn, TOL[sc.dtype], "own")
+    st.stage_destroy()
+    hz.succ.stage_destroy()
