@@ -63,12 +63,16 @@ int bk_copy(const void* src, void* dst, uint64_t bytes, void* stream);
 /* Choose the output tile of the MFMA GEMM kernel for all later calls in this process.
  * code = 10*WM + WN selects a (64*WM) x (64*WN) tile, one of 44, 43, 42, 24, 22, 11; 0 restores the
  * automatic choice.  Returns the previous code, or BAMBOO_E_ARG for a code that is not offered.
+ * Products that the automatic choice (impl = 0) gives to the kernel whose wavefronts split K (a few hundred rows and
+ * less) keep that kernel, since it takes the sums in another order than the tiles; impl = 2 or a forced ring depth
+ * (bk_gemm_stages) gives the tile for every product.  A tile that cannot address its operands (rows of millions of
+ * elements) is passed over.
  * Process-wide: the caller must not change it while another thread launches. */
 int bk_gemm_tile(int code);
 
 /* Force the depth of the LDS slice ring of the pipelined MFMA GEMM kernel (2, 3 or 4 buffers; a
  * depth that does not fit the tile's LDS budget or exceeds the number of K slices falls back to the
- * next smaller one); 0 restores the automatic choice.  Returns the previous value, or BAMBOO_E_ARG.
+ * next smaller one); no product splits K over wavefronts meanwhile.  0 restores the automatic choice.  Returns the previous value, or BAMBOO_E_ARG.
  * Process-wide, like bk_gemm_tile. */
 int bk_gemm_stages(int n);
 

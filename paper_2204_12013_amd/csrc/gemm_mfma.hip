@@ -1356,7 +1356,8 @@ static float choose_tile(const GemmDesc& d, bool acc_form, long extra_lds, bool 
 //     1536  1024  4096   32.7 / 32.5   50.8 / 39.3     28.9 / 27.9
 //     512   3072  1024   11.0 / 10.8   22.9 / 18.4     12.9 / 12.1
 // i.e. splitting pays where one round of small tiles covers the output, and more the longer K is.  The choice depends
-// on the shape alone (not on the stream, nor on a forced tile): the sums are taken in another order than the tiles'.
+// on the shape alone (not on the stream, nor on a forced tile; a forced ring depth rules the split out): the sums are
+// taken in another order than the tiles'.
 // row_sums: the kernel may be asked for column sums, one row per tile row: not with more of them than the buffers hold.
 static int choose_split(const GemmDesc& d, bool b_k, long extra_lds, bool row_sums) {
   int code, ns;
@@ -1384,7 +1385,8 @@ static hipError_t launch_form(hipStream_t s, GemmDesc d) {
     if (e != hipSuccess) return e;
   }
   if constexpr (EPI != EPI_ACC_F32) {
-    switch (d.tiled_only ? 0 : choose_split(d, B_K, is_gelu(EPI) ? kGeluBytes : 0, EPI == EPI_MUL)) {
+    // a forced ring depth is one of the tiled kernel's
+    switch (d.tiled_only || g_forced_stages ? 0 : choose_split(d, B_K, is_gelu(EPI) ? kGeluBytes : 0, EPI == EPI_MUL)) {
       case 1: return launch_split<1, 8, B_K, EPI>(s, d);
       case 2: return launch_split<2, 4, B_K, EPI>(s, d);
       default: break;

@@ -104,6 +104,22 @@ def test_mfma_tiles_and_pipeline_depths_agree_bitwise(B, T, N, K):
         B.bk_gemm_stages(0)
 
 
+def test_a_forced_ring_depth_holds_for_products_that_would_split_K(B):
+    T, K, N = 512, 4096, 1024
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(1)
+    X, W, b = (torch.randn(*s, generator=gen, device=DEV).bfloat16() for s in ((T, K), (K, N), (N,)))
+    tiled, auto, forced = (_empty((T, N), 1) for _ in range(3))
+    B.bk_linear_fwd(X, W, b, tiled, impl=2)
+    B.bk_linear_fwd(X, W, b, auto)
+    B.bk_gemm_stages(3)
+    try:
+        B.bk_linear_fwd(X, W, b, forced)
+    finally:
+        B.bk_gemm_stages(0)
+    assert torch.equal(forced, tiled) and not torch.equal(auto, tiled)
+
+
 @pytest.mark.parametrize("shapes", [
     # (T, K, N) per problem: ragged edges, different contraction lengths, one to four problems
     [(512, 136, 264), (192, 128, 128)],
