@@ -126,7 +126,7 @@ def test_a_forced_ring_depth_holds_for_products_that_would_split_K(B):
     [(448, 1024, 392), (448, 64, 72), (320, 520, 8), (1024, 256, 256)],
     [(4096, 1024, 1024), (4096, 1024, 3072)],
     [(256, 200, 96)],
-    [(100, 64, 64), (256, 64, 64)],            # a contraction length the grouped kernel does not take
+    [(100, 64, 64), (256, 64, 64)],            # a contraction length that ends inside a 64-deep slice
 ])
 def test_grouped_weight_gradients_equal_the_single_launches_bitwise(B, shapes):
     rng = np.random.default_rng(len(shapes) * 7 + shapes[0][0])
@@ -197,11 +197,12 @@ def test_any_row_count_and_contraction_tail(B, T, K, N):
     h = X.astype(np.float64) @ W.astype(np.float64) + b
     dx = dY.astype(np.float64) @ W.astype(np.float64).T
     dw = X.astype(np.float64).T @ dY.astype(np.float64)
+    dYs = [dYd, _dev(B, _mk(rng, (T, N), 1), 1)]
     try:
         for tile in (0, 11, 22, 24, 42, 44):
             B.bk_gemm_tile(tile)
+            B.bk_gemm_stages(2 if tile else 0)           # with a forced depth no product goes to the kernels that split K
             Y, G, dX = (torch.full((T + 1, n), 7.0, device=DEV).to(torch.bfloat16) for n in (N, N, K))
-            dW, dWg = torch.zeros(K, N, device=DEV), torch.zeros(K, N, device=DEV)
             B.bk_linear_fwd(Xd, Wd, bd, Y[:T])
             assert rel_l2(B.to_host(Y[:T]), h) < 2.0 ** -8 and bool((Y[T] == 7).all())
             B.bk_linear_fwd(Xd, Wd, bd, Y[:T], gelu_out=G[:T])
@@ -212,12 +213,17 @@ def test_any_row_count_and_contraction_tail(B, T, K, N):
                 assert rel_l2(B.to_host(got[:T]), want) < rel_l2(rounded, want) + 2e-5 and bool((got[T] == 7).all())
             B.bk_linear_bwd_input(dYd, Wd, dX[:T], mul=Md)
             assert rel_l2(B.to_host(dX[:T]), dx * Mu) < 2.0 ** -8 and bool((dX[T] == 7).all())
-            B.bk_linear_bwd_weight(Xd, dYd, dW)
-            assert rel_l2(dW.cpu().numpy(), dw) < 1e-5
-            B.bk_linear_bwd_weight_group([Xd], [dYd], [dWg])
-            assert torch.equal(dWg, dW)
+            single, grouped = ([torch.zeros(K, N, device=DEV) for _ in dYs] for _ in range(2))
+            for g, dW in zip(dYs, single):
+                B.bk_linear_bwd_weight(Xd, g, dW)
+            assert rel_l2(single[0].cpu().numpy(), dw) < 1e-5
+            B.bk_gemm_stages(0)                          # a forced depth takes the group apart
+            B.bk_linear_bwd_weight_group([Xd, Xd], dYs, grouped)
+            for a, b in zip(grouped, single):
+                assert torch.equal(a, b), tile
     finally:
         B.bk_gemm_tile(0)
+        B.bk_gemm_stages(0)
 
 
 def test_operands_whose_rows_are_millions_long(B):
