@@ -132,7 +132,7 @@ struct GemmGroup {
 // dtype: 0 fp32, 1 bf16 (enum bamboo_dtype).  All launchers return hipError_t
 // from the launch and never synchronise.
 hipError_t launch_gemm_simple(hipStream_t s, int dtype, const GemmDesc& d);
-// fp32 MFMA path; hipErrorNotSupported when neither stride of an operand is 1
+// fp32 MFMA path; hipErrorNotSupported when neither stride of an operand is 1 and where launch_gemm_simple is faster
 hipError_t launch_gemm_f32(hipStream_t s, const GemmDesc& d);
 // bf16 MFMA path; returns hipErrorNotSupported when the shape is not covered.
 hipError_t launch_gemm_mfma(hipStream_t s, const GemmDesc& d);

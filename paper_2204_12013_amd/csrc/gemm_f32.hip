@@ -146,6 +146,21 @@ static hipError_t launch(hipStream_t s, const GemmDesc& d) {
   return hipGetLastError();
 }
 
+// Where the vector-ALU kernel, whose 64 x 64 tiles reuse their operands in LDS, is the faster one for the forward and
+// input-gradient forms: outputs that give every CU several of its tiles, fewer where the operands here come one float at a
+// time.  Vector ALU / this kernel in us, forward / input gradient (rows, K, N; tiles of 64 x 64):
+//   16-byte loads  4096 x 1024 x 1024 (1024)  215 / 152, 194 / 148     8192 x 1024 x 1024 (2048)  282 / 302, 277 / 305
+//                  8192 x  512 x 2048 (4096)  279 / 298, 274 / 304     8192 x 1024 x 4096 (8192)  984 / 1108, 1050 / 1178
+//                  4096 x  128 x 4096 (4096)   82 / 78,  79 / 88
+//   4-byte loads   2048 x 1023 x 1025 (544)   211 / 174, 203 / 171     4096 x 1023 x 1025 (1088 / 1024)  218 / 305, 216 / 360
+//                  4096 x  513 x 1025 (1088 / 576)  124 / 163, 220 / 260
+// Weight gradients (both operands row-contiguous) are faster here at every size.
+static bool vector_alu_is_faster(const GemmDesc& d, bool b_k, bool vec) {
+  const long tiles = (long)((d.M + 63) / 64) * ((d.N + 63) / 64);
+  if (vec) return tiles >= 2048 && (d.K >= 512 || (b_k && tiles >= 4096));
+  return tiles >= (b_k ? 560 : 800);
+}
+
 // any M, N, K and the operand strides of the three forms a layer needs
 hipError_t launch_gemm_f32(hipStream_t s, const GemmDesc& d) {
   if (d.M <= 0 || d.N <= 0) return hipSuccess;
@@ -153,6 +168,7 @@ hipError_t launch_gemm_f32(hipStream_t s, const GemmDesc& d) {
   if ((!a_k && d.a_sm != 1) || (!b_k && d.b_sn != 1)) return hipErrorNotSupported;
   const bool vec = d.K % 4 == 0 && (!a_k || (d.a_sm % 4 == 0 && ((uintptr_t)d.A & 15) == 0)) &&
                    (!b_k || (d.b_sn % 4 == 0 && ((uintptr_t)d.B & 15) == 0));
+  if (a_k && vector_alu_is_faster(d, b_k, vec)) return hipErrorNotSupported;
   if (a_k && !b_k) return vec ? launch<true, false, true>(s, d) : launch<true, false, false>(s, d);
   if (a_k && b_k) return vec ? launch<true, true, true>(s, d) : launch<true, true, false>(s, d);
   if (!a_k && !b_k) return launch<false, false, false>(s, d);
