@@ -10,7 +10,8 @@
  * 1 bf16 storage with fp32 accumulation.  impl: 0 automatic (MFMA kernel when it
  * covers the shape, vector-ALU kernel otherwise), 1 vector-ALU kernel,
  * 2 bf16 MFMA kernel, matrix products with one K chain per output tile (BAMBOO_E_STATE if it does not cover the
- * shape; matrix products: every dimension a multiple of 8).  fp32 matrix products run on the matrix cores too (impl 0).
+ * shape; matrix products: every dimension a multiple of 8).  fp32 matrix products run on the matrix cores too (impl 0),
+ * except large ones that the vector ALU does faster.
  * Return: 0 or a negative bamboo_status (see bamboo_stage.h).
  * Tensors are row-major; "tokens" T = batch * seq.
  */

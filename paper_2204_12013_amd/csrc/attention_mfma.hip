@@ -658,12 +658,16 @@ static hipError_t fwd_launch(hipStream_t s, const AttnDesc& a) {
   return hipGetLastError();
 }
 
-// Both backward passes as one launch where the chip holds their workgroups together (two per CU at head size 64, one
-// at 128): the second pass need not wait for the first, which leaves most CUs idle, and a launch is saved; it costs the
-// key owners their own delta.  Backward in us, two launches / one (samples, tokens, heads, size):
+// Both backward passes as one launch up to 512 workgroups at head size 64 (what the chip holds at once, two per CU) and up
+// to 320 at 128, where it holds 256: the second pass need not wait for the first, which leaves most CUs idle, and a
+// launch is saved; it costs the key owners their own delta.  The limit at 128 is where the two were measured to meet,
+// between 320 and 384.  Backward in us, two launches / one (samples, tokens, heads, size):
 //   1 x 128 x 16 x 64: 13.0 / 8.1    3 x 333 x 16 x 64: 25.7 / 19.1    4 x 512 x 16 x 64 (512 workgroups): 32.9 / 27.2
 //   8 x 512 x 16 x 64 (1024): 48.6 / 50.6    1 x 700 x 24 x 128 (288): 67.2 / 51.3    2 x 512 x 24 x 128 (384): 55.6 / 55.5
-constexpr int kBothMaxSeq = 1024;      // deltas of a sequence in LDS
+//   1 x 1024 x 4 x 64 (64): 48.3 / 33.4    2 x 512 x 20 x 128 (320): 52.3 / 44.7
+// Longer sequences keep two launches: the deltas of a sequence are held in LDS, 4 KB of it here (few heads of more
+// tokens were not measured).
+constexpr int kBothMaxSeq = 1024;
 template <int D>
 static bool side_by_side(const AttnDesc& a, unsigned wgs) {
   return a.S <= kBothMaxSeq && 2 * wgs <= (D == 64 ? 512u : 320u);

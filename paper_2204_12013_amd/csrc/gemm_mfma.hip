@@ -952,9 +952,9 @@ __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_kernel(GemmDesc d) {
 // tile to the next one's without the chip draining in between.
 // With 256 x 256 tiles a remainder of up to 128 rows or columns at a matrix' edge is covered by 128 x 256 or 256 x 128
 // tiles (see edge_strips): a launch of 1600-wide matrices has 456 tiles and 76 strips instead of 532 tiles, i.e. two
-// rounds of the 256 CUs instead of three.  4096 tokens, 1600 x 6400 layers: 286 us, 293 us as 128 x 256 tiles (266 us with
-// the gradients past the caches, see epilogue8); the rounds
-// are 143 us each, 90 us of them main loop at the clock that 256 busy CUs leave, the rest fp32 reads and writes.
+// rounds of the 256 CUs instead of three.  4096 tokens, 1600 x 6400 layers: 293 us as 128 x 256 tiles, 286 us like this,
+// 266 us with the gradients past the caches (see epilogue8): 133 us a round, 90 us of them main loop at the clock that
+// 256 busy CUs leave, the rest fp32 reads and writes.
 template <int WM, int WN, int NS, int MINB>
 __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_group_kernel(GemmGroup g) {
   const int total = g.first[GemmGroup::MAX], wg = (int)blockIdx.x - g.chains;

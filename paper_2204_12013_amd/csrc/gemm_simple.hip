@@ -1,7 +1,8 @@
-// Generic strided GEMM on the vector ALUs with fp32 accumulation: the fp32
-// configuration's GEMM and the fallback for bf16 shapes the MFMA kernel does
-// not cover.  64x64 output tile, 16-deep k-slices staged in LDS, 4x4 outputs
-// per thread; every access is bounds-checked so any M, N, K works.
+// Generic strided GEMM on the vector ALUs with fp32 accumulation: the fallback
+// for bf16 shapes the MFMA kernel does not cover, and large fp32 products (the
+// others run in gemm_f32.hip).  64x64 output tile, 16-deep k-slices staged in
+// LDS, 4x4 outputs per thread; every access is bounds-checked so any M, N, K
+// works.  Also the choice between the kernels.
 #include "common.h"
 
 namespace bamboo {
