@@ -437,7 +437,8 @@ def test_attention_backward_in_one_launch_and_in_two_is_the_same(B, causal, batc
 
 
 @pytest.mark.parametrize("T,K,N", [(1, 1, 1), (31, 33, 65), (32, 64, 256), (100, 72, 200), (513, 130, 2049),
-                                   (2100, 67, 1601), (2048, 1026, 1281)])          # the last two on the vector ALU in part
+                                   # on the vector ALU: the forward, the input gradient, the forward with 16-byte loads
+                                   (2100, 67, 1601), (2112, 1026, 1281), (2880, 512, 2944)])
 def test_fp32_matrix_core_gemm(B, T, K, N):
     """The fp32 kernel at tile and step edges, unaligned lengths (no 16-byte loads) and on both sides of its split of K
     over wavefronts.  Bound: a sum of n products in fp32 is off by at most n 2^-24 of the sum of magnitudes, far less in
