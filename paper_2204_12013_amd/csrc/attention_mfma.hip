@@ -42,65 +42,95 @@ __device__ __forceinline__ void block_of(int wg, int nblk, int nbh, int* blk, in
   *blk = (CAUSAL && HEAVY_LAST) ? nblk - 1 - i : i;
 }
 
-// ---- cooperative copy of 64 rows x D (bf16) global -> registers -> LDS -------------
+// ---- cooperative copy of 64 rows x D (bf16) global -> LDS ---------------------------
+// The tiles go straight to LDS (global_load_lds_dwordx4: 16 bytes per lane to consecutive addresses behind a
+// wavefront-uniform base), so nothing waits in registers and no LDS store is issued.  Rows are not padded; the 16-byte
+// chunk ch of row r sits at position ch ^ swz(r) of its row, which every lane applies to the chunk that it FETCHES.  The
+// placement serves both ways a tile is read: 16 consecutive rows of one chunk (frag_k) and 4 rows x 64 bytes (frag_tr)
+// each cover the 64 banks once.  With the rows padded to D + 8 (D + 16 for the values of the forward pass) and staged
+// through registers the second kind, half of the backward's reads, met its own banks twice.  Forward / backward in us,
+// before and now (samples x tokens x heads x size):
+//   8 x 512 x 16 x 64    16.8 -> 16.2, 46.1 -> 43.3     1 x 8192 x 16 x 64 causal  171 -> 168, 534 -> 507
+//   4 x 512 x 16 x 64    11.1 -> 10.6, 24.4 -> 23.5     1 x 2048 x 96 x 128 causal 126 -> 125, 614 -> 531
+// What bounds both passes is still a wavefront's own chain of matrix and vector instructions, at two wavefronts per SIMD.
 // Rows at or beyond row_lim are read from row row_lim - 1 (finite values that the consumers' masks turn
 // into exact zeros), so no load sits behind a branch.  A thread's byte offsets inside a tile and their
 // upper limits (the same chunk in the last valid row) are computed once; per tile and chunk an add and a
 // min remain.  Offsets are 32-bit: the launcher checks that a sequence stays below 4 GiB.
+// The loads are inline assembly, which the compiler's wait counts do not see: wait_tiles() before the barrier that
+// publishes a tile.
 template <int D>
-struct TileAddr {
+__device__ __forceinline__ int swz(int r) {
+  return D == 64 ? ((r & 2) << 1) | ((r >> 2) & 3)       // rows of 128 bytes: two to a line of the 64 banks
+                 : ((r & 3) << 2) | ((r >> 2) & 3);      // rows of 256 bytes
+}
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+__device__ __forceinline__ unsigned lds_address(const void* p) { return (unsigned)(uintptr_t)(lds_void_ptr)p; }
+template <int D>
+struct TileCopy {
   static constexpr int N = TILE * D / 8 / 256;   // 16-byte chunks per thread
+  static constexpr int BYTES = TILE * D * 2;
   unsigned ofs[N], last[N];
   unsigned tile_bytes;                           // 64 rows
+  unsigned wave_lds;
   __device__ __forceinline__ void init(long row_stride, int row_lim) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int c = threadIdx.x + i * 256;
-      const unsigned col = (unsigned)((c % (D / 8)) * 8) * 2u;
-      ofs[i] = (unsigned)(c / (D / 8)) * (unsigned)row_stride * 2u + col;
+      const int c = threadIdx.x + i * 256, r = c / (D / 8);
+      const unsigned col = (unsigned)(((c % (D / 8)) ^ swz<D>(r)) * 8) * 2u;
+      ofs[i] = (unsigned)r * (unsigned)row_stride * 2u + col;
       last[i] = (unsigned)(row_lim - 1) * (unsigned)row_stride * 2u + col;
     }
     tile_bytes = (unsigned)TILE * (unsigned)row_stride * 2u;
+    wave_lds = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024;
+  }
+  // tile: index of the 64-row tile counted from g; lds: where it goes (all uniform)
+  __device__ __forceinline__ void issue(const bf16_t* g, int tile, unsigned lds) const {
+    const unsigned t0 = (unsigned)tile * tile_bytes;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                   :
+                   : "v"(min(t0 + ofs[i], last[i])), "s"(g), "s"(lds + wave_lds + i * 4096)
+                   : "memory", "m0");
   }
 };
-template <int D>
-struct RowTile {
-  static constexpr int N = TileAddr<D>::N;
-  bf16x8 v[N];
-  // tile: index of the 64-row tile counted from g (uniform)
-  __device__ __forceinline__ void fetch(const bf16_t* g, const TileAddr<D>& ta, int tile) {
-    const unsigned t0 = (unsigned)tile * ta.tile_bytes;
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = *(const bf16x8*)((const char*)g + min(t0 + ta.ofs[i], ta.last[i]));
-  }
-  __device__ __forceinline__ void stash(bf16_t* s, int ld) const {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int c = threadIdx.x + i * 256;
-      *(bf16x8*)(s + (c / (D / 8)) * ld + (c % (D / 8)) * 8) = v[i];
-    }
-  }
-};
+// vmcnt(N): at most the N youngest of this wavefront's loads are still on their way
+template <int N>
+__device__ __forceinline__ void wait_tiles() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
-// Operand fragment with the contraction index contiguous in LDS: lane l holds
-// row row_base + l%32, contraction elements 16*ks + 8*(l/32) .. +7.
-__device__ __forceinline__ bf16x8 frag_k(const bf16_t* s, int ld, int row_base, int ks) {
-  const int l = threadIdx.x & 63;
-  return *(const bf16x8*)(s + (row_base + (l & 31)) * ld + ks * 16 + (l >> 5) * 8);
-}
-// Operand fragment with the contraction index running over LDS rows (transposing
-// load): lane l holds column col_base + l%32; its 8 contraction slots are rows
-// kbase + 4*(l/32) + {0..3} and kbase + 8 + 4*(l/32) + {0..3} -- the order in
-// which a 32x32 accumulator tile hands 8 of a lane's 16 values to the next MFMA.
-__device__ __forceinline__ bf16x8 frag_tr(const bf16_t* s, int ld, int col_base, int kbase) {
-  const int l = threadIdx.x & 63, i = l & 15;
-  const bf16_t* p = s + (kbase + 4 * (l >> 5) + (i >> 2)) * ld + col_base + ((l >> 4) & 1) * 16 + (i & 3) * 4;
-  typedef __attribute__((address_space(3))) short4_t* lds_ptr;
-  union { short4_t s4[2]; bf16x8 b; } u;
-  u.s4[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-  u.s4[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 8 * ld));
-  return u.b;
-}
+// Addresses of a tile's operand fragments, relative to the tile (256-byte aligned).
+template <int D>
+struct FragAddr {
+  unsigned k;        // frag_k at row 0, k-step 0
+  unsigned tr[2];    // frag_tr at column 0, row 0: its two halves
+  __device__ __forceinline__ void init() {
+    const int l = threadIdx.x & 63, i = l & 15, q = 4 * (l >> 5) + (i >> 2);
+    k = (l & 31) * D * 2 + (((l >> 5) ^ swz<D>(l & 31)) << 4);
+    const int ch = ((l >> 4) & 1) * 2 + ((i & 3) >> 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) tr[h] = (q + 8 * h) * D * 2 + ((ch ^ swz<D>(q + 8 * h)) << 4) + (i & 1) * 8;
+  }
+  // Operand fragment with the contraction index contiguous in LDS: lane l holds
+  // row row_base + l%32, contraction elements 16*ks + 8*(l/32) .. +7.
+  __device__ __forceinline__ bf16x8 frag_k(unsigned tile, int row_base, int ks) const {
+    typedef __attribute__((address_space(3))) const bf16x8* lds_ptr;
+    return *(lds_ptr)(((tile + k) ^ (ks << 5)) + row_base * D * 2);
+  }
+  // Operand fragment with the contraction index running over LDS rows (transposing
+  // load): lane l holds column col_base + l%32; its 8 contraction slots are rows
+  // kbase + 4*(l/32) + {0..3} and kbase + 8 + 4*(l/32) + {0..3} -- the order in
+  // which a 32x32 accumulator tile hands 8 of a lane's 16 values to the next MFMA.
+  __device__ __forceinline__ bf16x8 frag_tr(unsigned tile, int col_base, int kbase) const {
+    typedef __attribute__((address_space(3))) short4_t* lds_ptr;
+    union { short4_t s4[2]; bf16x8 b; } u;
+    u.s4[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(((tile + tr[0]) ^ (col_base << 1)) + kbase * D * 2));
+    u.s4[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(((tile + tr[1]) ^ (col_base << 1)) + kbase * D * 2));
+    return u.b;
+  }
+};
 // registers 8*half .. 8*half+7 of an accumulator tile as a bf16 operand fragment
 __device__ __forceinline__ bf16x8 pack8(const f32x16& t, int half) {
   bf16x8 o;
@@ -208,12 +238,12 @@ __device__ __forceinline__ void block_colsum_write(float (&cs)[8], float* xch, f
 }
 
 // =============================================================== forward
-template <int D, bool CAUSAL>
+// NR: tiles of keys and values in LDS (see fwd_launch)
+template <int D, bool CAUSAL, int NR>
 __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
-  constexpr int LDK = D + 8, LDV = D + 16;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16_t* Ks = (bf16_t*)smem_raw;                 // [2][64][LDK]
-  bf16_t* Vs = Ks + 2 * TILE * LDK;               // [2][64][LDV]
+  constexpr unsigned TB = TileCopy<D>::BYTES;
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem_raw[];
+  const unsigned ring = lds_address(smem_raw);    // [NR][keys, values]
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 5;
   const int H = a.heads * D, S = a.S;
   int qblk, bh;
@@ -236,22 +266,28 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
 
   const int kend = CAUSAL ? min(S, q0 + 128) : S;
   const int nt = (kend + TILE - 1) / TILE;
-  RowTile<D> kt_regs, vt_regs;
-  TileAddr<D> ta;
-  ta.init(rs, S);
-  kt_regs.fetch(base + H, ta, 0);
-  vt_regs.fetch(base + 2 * H, ta, 0);
-  kt_regs.stash(Ks, LDK);
-  vt_regs.stash(Vs, LDV);
-  __syncthreads();
+  TileCopy<D> copy;
+  copy.init(rs, S);
+  FragAddr<D> fr;
+  fr.init();
+  auto fetch = [&](int t, unsigned at) __attribute__((always_inline)) {
+    copy.issue(base + H, t, at);
+    copy.issue(base + 2 * H, t, at + TB);
+  };
+  constexpr unsigned RING = NR * 2 * TB;
+  // the NR - 1 tiles after t are on their way while tile t is worked on
+  fetch(0, ring);
+  if (NR > 2 && nt > 1) fetch(1, ring + 2 * TB);
+  unsigned cur = 0;
   for (int t = 0; t < nt; ++t) {
-    const bf16_t* ks_ = Ks + (t & 1) * TILE * LDK;
-    const bf16_t* vs_ = Vs + (t & 1) * TILE * LDV;
+    const unsigned ks_ = ring + cur, vs_ = ks_ + TB;
+    const unsigned free_slot = cur == 0 ? RING - 2 * TB : cur - 2 * TB;      // of tile t - 1
+    if (NR > 2 && t + 1 < nt) wait_tiles<2 * TileCopy<D>::N>();              // tile t has landed,
+    else wait_tiles<0>();
+    __syncthreads();                              // everywhere, and tile t - 1 has been read everywhere
+    if (t + NR - 1 < nt) fetch(t + NR - 1, ring + free_slot);
+    cur = cur + 2 * TB == RING ? 0 : cur + 2 * TB;
     const int k0 = t * TILE;
-    if (t + 1 < nt) {
-      kt_regs.fetch(base + H, ta, t + 1);
-      vt_regs.fetch(base + 2 * H, ta, t + 1);
-    }
     if (!CAUSAL || k0 <= qw0 + 31) {              // wave-uniform: tile not entirely above the diagonal
       f32x16 s[2];
 #pragma unroll
@@ -262,7 +298,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
       for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
         for (int u = 0; u < 2; ++u)
-          s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(ks_, LDK, u * 32, ks), qf[ks], s[u], 0, 0, 0);
+          s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(ks_, u * 32, ks), qf[ks], s[u], 0, 0, 0);
       // Online softmax in the log2 domain.  The running maximum m_i is only raised when some row's
       // maximum has grown by more than 8 (a factor 256, harmless in fp32 and bf16): softmax is
       // invariant to the shift, and the rescaling of the running output then happens on a few
@@ -317,15 +353,11 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
         for (int j = 0; j < 8; ++j) l_i += s[u >> 1][8 * (u & 1) + j];
 #pragma unroll
         for (int dt = 0; dt < D / 32; ++dt)
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(vs_, LDV, dt * 32, 16 * u), pb, o[dt], 0, 0, 0);
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(vs_, dt * 32, 16 * u), pb, o[dt], 0, 0, 0);
       }
     }
-    if (t + 1 < nt) {
-      kt_regs.stash(Ks + ((t + 1) & 1) * TILE * LDK, LDK);
-      vt_regs.stash(Vs + ((t + 1) & 1) * TILE * LDV, LDV);
-    }
-    __syncthreads();
   }
+  __syncthreads();                                // the tiles' place takes the results
   const float l_tot = l_i + __shfl_xor(l_i, 32, 64);
   const float inv = 1.f / l_tot;
   bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
@@ -337,16 +369,19 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
 // Two passes, by one kernel template: PASS_DQ and PASS_DKV are launched one after the other; with PASS_BOTH the first
 // n workgroups own key rows (the longer pass) and the others query rows, side by side.
 enum BwdPass { PASS_DQ, PASS_DKV, PASS_BOTH };
+// At head size 128 the dQ pass fits two wavefronts per SIMD since its tiles no longer pass through registers, with 16 to 28
+// bytes spilled (1 x 2048 x 96 x 128 causal: backward 570 us with one, 531 with two); the other pass holds 72 registers more.
 template <int D, bool CAUSAL, int PASS>
-__global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
-  constexpr int LD = D + 8;
+__global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
+  constexpr unsigned TB = TileCopy<D>::BYTES;
   constexpr bool OWN_DELTA = PASS == PASS_BOTH;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem_raw[];
+  const unsigned ring = lds_address(smem_raw);      // [2][two tiles]
+  FragAddr<D> fr;
+  fr.init();
   // dQ: a wavefront owns 32 queries (lane = query) and streams 64-key tiles.
   if (PASS == PASS_DQ || (PASS == PASS_BOTH && (int)blockIdx.x >= n)) {
     const int wg = PASS == PASS_BOTH ? (int)blockIdx.x - n : (int)blockIdx.x;
-    bf16_t* Ks = (bf16_t*)smem_raw;                 // [2][64][LD]
-    bf16_t* Vs = Ks + 2 * TILE * LD;                // [2][64][LD]
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int H = a.heads * D, S = a.S;
     int qblk, bh;
@@ -394,21 +429,18 @@ __global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
 
     const int kend = CAUSAL ? min(S, q0 + 128) : S;
     const int nt = (kend + TILE - 1) / TILE;
-    RowTile<D> kt_regs, vt_regs;
-    TileAddr<D> ta;
-    ta.init(rs, S);
-    kt_regs.fetch(base + H, ta, 0);
-    vt_regs.fetch(base + 2 * H, ta, 0);
-    kt_regs.stash(Ks, LD);
-    vt_regs.stash(Vs, LD);
+    TileCopy<D> copy;
+    copy.init(rs, S);
+    copy.issue(base + H, 0, ring);
+    copy.issue(base + 2 * H, 0, ring + TB);
+    wait_tiles<0>();
     __syncthreads();
     for (int t = 0; t < nt; ++t) {
-      const bf16_t* ks_ = Ks + (t & 1) * TILE * LD;
-      const bf16_t* vs_ = Vs + (t & 1) * TILE * LD;
+      const unsigned ks_ = ring + (t & 1) * 2 * TB, vs_ = ks_ + TB;
       const int k0 = t * TILE;
       if (t + 1 < nt) {
-        kt_regs.fetch(base + H, ta, t + 1);
-        vt_regs.fetch(base + 2 * H, ta, t + 1);
+        copy.issue(base + H, t + 1, ring + ((t + 1) & 1) * 2 * TB);
+        copy.issue(base + 2 * H, t + 1, ring + ((t + 1) & 1) * 2 * TB + TB);
       }
       if (!CAUSAL || k0 <= qw0 + 31) {
         f32x16 s[2], dp[2];
@@ -416,8 +448,8 @@ __global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
         for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(ks_, LD, u * 32, ks), qf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
-            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(vs_, LD, u * 32, ks), dof[ks], ks == 0 ? neg_delta : dp[u], 0,
+            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(ks_, u * 32, ks), qf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
+            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(vs_, u * 32, ks), dof[ks], ks == 0 ? neg_delta : dp[u], 0,
                                                             0, 0);
           }
         const bool need_mask = (k0 + TILE > S) || (CAUSAL && k0 + TILE - 1 > qw0);
@@ -442,13 +474,10 @@ __global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
           const bf16x8 dsb = pack8(s[u >> 1], u & 1);
 #pragma unroll
           for (int dt = 0; dt < D / 32; ++dt)
-            dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(ks_, LD, dt * 32, 16 * u), dsb, dq[dt], 0, 0, 0);
+            dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(ks_, dt * 32, 16 * u), dsb, dq[dt], 0, 0, 0);
         }
       }
-      if (t + 1 < nt) {
-        kt_regs.stash(Ks + ((t + 1) & 1) * TILE * LD, LD);
-        vt_regs.stash(Vs + ((t + 1) & 1) * TILE * LD, LD);
-      }
+      wait_tiles<0>();
       __syncthreads();
     }
     bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
@@ -468,9 +497,7 @@ __global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
     // OWN_DELTA: delta of the sample's and head's queries is formed here, ahead of the tiles, into LDS behind the rest
     // (S floats), in the order of the additions of the dQ pass; otherwise it comes from memory.
     const int wg = blockIdx.x;
-    bf16_t* Qs = (bf16_t*)smem_raw;                 // [2][64][LD]
-    bf16_t* dOs = Qs + 2 * TILE * LD;               // [2][64][LD]
-    float* lse_s = (float*)(dOs + 2 * TILE * LD);   // [2][64]  (log2 domain)
+    float* lse_s = (float*)(smem_raw + 4 * TB);     // [2][64]  (log2 domain), behind the tiles
     float* del_s = lse_s + 2 * TILE;                // [2][64]
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 5;
     const int H = a.heads * D, S = a.S;
@@ -520,7 +547,6 @@ __global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
       }
       __syncthreads();
     }
-    RowTile<D> q_regs, do_regs;
     float lse_r = 0.f, del_r = 0.f;
     auto fetch_stats = [&](int q0t) {
       if (threadIdx.x < TILE) {
@@ -536,25 +562,23 @@ __global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
         del_s[buf * TILE + threadIdx.x] = del_r;
       }
     };
-    TileAddr<D> ta_q, ta_do;
-    ta_q.init(rs, S);
-    ta_do.init(H, S);
-    q_regs.fetch(base, ta_q, qbeg / TILE);
-    do_regs.fetch(dbase, ta_do, qbeg / TILE);
+    TileCopy<D> copy_q, copy_do;
+    copy_q.init(rs, S);
+    copy_do.init(H, S);
+    copy_q.issue(base, qbeg / TILE, ring);
+    copy_do.issue(dbase, qbeg / TILE, ring + TB);
     fetch_stats(qbeg);
-    q_regs.stash(Qs, LD);
-    do_regs.stash(dOs, LD);
     stash_stats(0);
+    wait_tiles<0>();
     __syncthreads();
     for (int t = 0; t < nt; ++t) {
       const int buf = t & 1;
-      const bf16_t* qs_ = Qs + buf * TILE * LD;
-      const bf16_t* dos_ = dOs + buf * TILE * LD;
+      const unsigned qs_ = ring + buf * 2 * TB, dos_ = qs_ + TB;
       const int q0t = qbeg + t * TILE;
       if (t + 1 < nt) {
-        q_regs.fetch(base, ta_q, qbeg / TILE + t + 1);
-        do_regs.fetch(dbase, ta_do, qbeg / TILE + t + 1);
         fetch_stats(q0t + TILE);
+        copy_q.issue(base, qbeg / TILE + t + 1, ring + (buf ^ 1) * 2 * TB);
+        copy_do.issue(dbase, qbeg / TILE + t + 1, ring + (buf ^ 1) * 2 * TB + TB);
       }
       if (!CAUSAL || q0t + TILE - 1 >= kw0) {       // wave-uniform: some query at or after the wave's first key
         // the queries' -delta runs along the accumulator registers here and comes from LDS with the tile: the
@@ -573,8 +597,8 @@ __global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
         for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(qs_, LD, u * 32, ks), kf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
-            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_k(dos_, LD, u * 32, ks), vf[ks], dp[u], 0, 0, 0);
+            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(qs_, u * 32, ks), kf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
+            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(dos_, u * 32, ks), vf[ks], dp[u], 0, 0, 0);
           }
         const bool need_mask = (q0t + TILE > S) || (kw0 + 32 > S) || (CAUSAL && q0t < kw0 + 31);
 #pragma unroll
@@ -609,16 +633,13 @@ __global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
           const bf16x8 dsb = pack8(dp[u >> 1], u & 1);
 #pragma unroll
           for (int dt = 0; dt < D / 32; ++dt) {
-            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(dos_, LD, dt * 32, 16 * u), pb, dv[dt], 0, 0, 0);
-            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(qs_, LD, dt * 32, 16 * u), dsb, dk[dt], 0, 0, 0);
+            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(dos_, dt * 32, 16 * u), pb, dv[dt], 0, 0, 0);
+            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(qs_, dt * 32, 16 * u), dsb, dk[dt], 0, 0, 0);
           }
         }
       }
-      if (t + 1 < nt) {
-        q_regs.stash(Qs + (buf ^ 1) * TILE * LD, LD);
-        do_regs.stash(dOs + (buf ^ 1) * TILE * LD, LD);
-        stash_stats(buf ^ 1);
-      }
+      if (t + 1 < nt) stash_stats(buf ^ 1);
+      wait_tiles<0>();
       __syncthreads();
     }
     bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
@@ -648,20 +669,32 @@ static bool covered(const AttnDesc& a) {
   return !(misaligned(a.qkv) || misaligned(a.ctx) || misaligned(a.dctx) || misaligned(a.dqkv));
 }
 
-template <int D, bool CAUSAL>
-static hipError_t fwd_launch(hipStream_t s, const AttnDesc& a) {
-  constexpr int BYTES = 2 * TILE * (D + 8) * 2 + 2 * TILE * (D + 16) * 2;
-  constexpr auto kern = attn_fwd_mfma_kernel<D, CAUSAL>;
+template <int D, bool CAUSAL, int NR>
+static hipError_t fwd_launch_ring(hipStream_t s, const AttnDesc& a, unsigned grid) {
+  constexpr int BYTES = NR * 2 * TileCopy<D>::BYTES;
+  static_assert(BYTES >= 4 * 32 * (D + 8) * 2, "the four staging areas");
+  constexpr auto kern = attn_fwd_mfma_kernel<D, CAUSAL, NR>;
   const hipError_t e = ensure_lds_attribute<kern, BYTES>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(((a.S + 127) / 128) * a.B * a.heads), dim3(256), BYTES, s, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), BYTES, s, a);
   return hipGetLastError();
+}
+// Three tiles in LDS, as a step takes less than a trip to memory, except at head size 128 where they leave room for one
+// workgroup per CU instead of two and the launch has more than that.
+template <int D, bool CAUSAL>
+static hipError_t fwd_launch(hipStream_t s, const AttnDesc& a) {
+  const unsigned grid = (unsigned)(((a.S + 127) / 128) * a.B * a.heads);
+  if constexpr (D == 128) {
+    if (grid > 256) return fwd_launch_ring<D, CAUSAL, 2>(s, a, grid);
+  }
+  return fwd_launch_ring<D, CAUSAL, 3>(s, a, grid);
 }
 
 // Both backward passes as one launch up to 512 workgroups at head size 64 (what the chip holds at once, two per CU) and up
 // to 320 at 128, where it holds 256: the second pass need not wait for the first, which leaves most CUs idle, and a
 // launch is saved; it costs the key owners their own delta.  The limit at 128 is where the two were measured to meet,
 // between 320 and 384.  Backward in us, two launches / one (samples, tokens, heads, size):
+// (timed before tiles went straight to LDS)
 //   1 x 128 x 16 x 64: 13.0 / 8.1    3 x 333 x 16 x 64: 25.7 / 19.1    4 x 512 x 16 x 64 (512 workgroups): 32.9 / 27.2
 //   8 x 512 x 16 x 64 (1024): 48.6 / 50.6    1 x 700 x 24 x 128 (288): 67.2 / 51.3    2 x 512 x 24 x 128 (384): 55.6 / 55.5
 //   1 x 1024 x 4 x 64 (64): 48.3 / 33.4    2 x 512 x 20 x 128 (320): 52.3 / 44.7
@@ -675,8 +708,9 @@ static bool side_by_side(const AttnDesc& a, unsigned wgs) {
 
 template <int D, bool CAUSAL>
 static hipError_t bwd_launch(hipStream_t s, const AttnDesc& a) {
-  constexpr int BYTES_DQ = 4 * TILE * (D + 8) * 2;
-  constexpr int BYTES_DKV = 4 * TILE * (D + 8) * 2 + 4 * TILE * 4;
+  constexpr int BYTES_DQ = 4 * TileCopy<D>::BYTES;
+  constexpr int BYTES_DKV = 4 * TileCopy<D>::BYTES + 4 * TILE * 4;
+  static_assert(BYTES_DQ >= 4 * 32 * (D + 8) * 2 + 4 * D * 4, "the four staging areas and the column sums behind them");
   constexpr auto kq = attn_bwd_mfma_kernel<D, CAUSAL, PASS_DQ>;
   constexpr auto kkv = attn_bwd_mfma_kernel<D, CAUSAL, PASS_DKV>;
   hipError_t e = ensure_lds_attribute<kq, BYTES_DQ>();

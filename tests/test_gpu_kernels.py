@@ -416,6 +416,16 @@ def test_attention_at_the_longest_sequence_of_the_one_launch_backward(B, causal,
 
 
 @pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("batch,seq,heads,d", [(1, 1, 3, 64), (2, 64, 2, 64), (1, 65, 2, 128), (2, 128, 2, 128), (1, 129, 2, 64),
+                                               (1, 192, 2, 128), (1, 193, 3, 64), (2, 257, 2, 128), (1, 129, 128, 128),
+                                               (1, 129, 129, 128)])
+def test_attention_at_the_ends_of_its_tile_ring(B, causal, batch, seq, heads, d):
+    """One to five tiles of 64 rows through a ring of two or three, a last tile of one row, and at head size 128 both
+    sides of the 256 workgroups from which on the ring is the shorter one."""
+    test_attention_forward_backward(B, 1, 2, causal, batch, seq, heads, d)
+
+
+@pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("batch,seq,heads,d", [(8, 129, 16, 64), (8, 129, 17, 64), (3, 200, 27, 128)])
 def test_attention_backward_in_one_launch_and_in_two_is_the_same(B, causal, batch, seq, heads, d):
     """A whole batch (256 workgroups a pass: one launch; 272 and 162: two) against its samples one by one (one launch)."""
