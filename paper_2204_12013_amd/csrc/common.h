@@ -210,6 +210,29 @@ size_t colsum_partial_floats(int N);
 size_t ln_bwd_partial_floats(int H);
 hipError_t launch_bubble(hipStream_t s, float microseconds);
 
+// ---- whole layers of the fp32 configuration ----------------------------------------
+// Forward of the n layers whose records follow each other from `rec` on, or the backward of the one there.  Offsets:
+// bytes inside a record, elements inside a layer's parameters.
+struct SmallLayers {
+  int S, H, heads, F, n, pre_ln;
+  float eps;
+  char* rec;
+  const float* w;
+  long rec_bytes, w_stride;
+  long x, ain, qkv, ctx, r1, fin, g, dg, r2, lse, ln1, ln2;
+  long Wqkv, bqkv, Wo, bo, g1, be1, W1, b1, W2, b2, g2, be2;
+  const float* in;      // forward: x; backward: dy
+  float* out;           // forward: y; backward: dx
+};
+// Buffers a layer's backward leaves for its weight gradients, and partial rows (one per sample) of the column sums
+struct SmallBackward {
+  float *dh, *d1, *d2, *d3, *dctx, *dqkv;
+  float *p_ln[2][3], *p_dh, *p_dqkv, *p_df;
+};
+bool small_layers_fit(int B, int S, int H, int heads, int F, const void* w);
+hipError_t launch_small_fwd(hipStream_t s, int B, const SmallLayers& a);
+hipError_t launch_small_bwd(hipStream_t s, int B, const SmallLayers& a, const SmallBackward& b);
+
 // ---- model ends (wrap-around stage) ---------------------------------------------
 hipError_t launch_embed_fwd(hipStream_t s, int dtype, int T, int S, int H, int V, const int* ids, const void* Etok,
                             const void* Epos, void* out);

@@ -365,6 +365,36 @@ GemmDesc gemm_tn(const void* X, const void* dY, float* dW, int T, int Kw, int Nw
   return d;
 }
 
+// Whether the stage's layers go through the kernels that take a sample through them in one launch.  Decided by the
+// configuration and the parameters' alignment alone; with per-launch timing on, every launch is made singly, as the sites
+// that are timed are the single kernels.
+bool small_layers(const bamboo_stage* st, int kind) {
+  const bamboo_cfg_t& c = st->cfg;
+  return c.dtype == BAMBOO_F32 && !st->prof_on &&
+         small_layers_fit(c.micro_batch, c.seq, c.hidden, c.heads, c.ffn, st->w[kind]);
+}
+SmallLayers small_args(const bamboo_stage* st, int kind, int slot, int layer, int n, const void* in, void* out) {
+  const bamboo_cfg_t& c = st->cfg;
+  const RecordLayout& r = st->rl;
+  const ParamOffsets& p = st->po;
+  const int layers = kind == 0 ? c.n_own : c.n_shadow;
+  SmallLayers a;
+  memset(&a, 0, sizeof(a));
+  a.S = c.seq; a.H = c.hidden; a.heads = c.heads; a.F = c.ffn; a.n = n;
+  a.pre_ln = c.arch == BAMBOO_ARCH_PRE_LN_CAUSAL;
+  a.eps = c.ln_eps;
+  a.rec = st->stash[kind] + ((uint64_t)slot * layers + layer) * r.bytes;
+  a.w = (const float*)st->w[kind] + (uint64_t)layer * p.count;
+  a.rec_bytes = r.bytes; a.w_stride = p.count;
+  a.x = r.x; a.ain = r.ain; a.qkv = r.qkv; a.ctx = r.ctx; a.r1 = r.r1; a.fin = r.fin; a.g = r.g; a.dg = r.dg;
+  a.r2 = r.r2; a.lse = r.lse; a.ln1 = r.ln1; a.ln2 = r.ln2;
+  a.Wqkv = p.Wqkv; a.bqkv = p.bqkv; a.Wo = p.Wo; a.bo = p.bo; a.g1 = p.g1; a.be1 = p.be1; a.W1 = p.W1; a.b1 = p.b1;
+  a.W2 = p.W2; a.b2 = p.b2; a.g2 = p.g2; a.be2 = p.be2;
+  a.in = (const float*)in;
+  a.out = (float*)out;
+  return a;
+}
+
 // forward of one layer stack; kind 0 own, 1 shadow
 int run_forward(bamboo_stage* st, int kind, int lane_id, int slot, const void* x, void* y) {
   const bamboo_cfg_t& c = st->cfg;
@@ -375,6 +405,10 @@ int run_forward(bamboo_stage* st, int kind, int lane_id, int slot, const void* x
   (void)hipGetLastError();  // do not inherit an unrelated earlier error of this thread
   const RecordLayout& r = st->rl;
   char* rec0 = st->stash[kind] + (uint64_t)slot * n * r.bytes;
+  if (small_layers(st, kind)) {
+    HIPCHK(launch_small_fwd(s, c.micro_batch, small_args(st, kind, slot, 0, n, x, y)));
+    return BAMBOO_OK;
+  }
   HIPCHK(hipMemcpyAsync(rec0 + r.x, x, (uint64_t)T * H * es, hipMemcpyDeviceToDevice, s));
   for (int l = 0; l < n; ++l) {
     char* rec = rec0 + (uint64_t)l * r.bytes;
@@ -425,6 +459,37 @@ int run_forward(bamboo_stage* st, int kind, int lane_id, int slot, const void* x
   return BAMBOO_OK;
 }
 
+// The input-gradient chain of layer `layer` as one launch: what it leaves in the workspace, and the sums behind the
+// layer's partial rows (as run_backward queues them).
+int small_backward(bamboo_stage* st, int kind, hipStream_t s, char* ws, const LaneScratch& w, int slot, int layer,
+                   const void* dy, void* dx, float* G, GradReduceBatch* batch) {
+  const bamboo_cfg_t& c = st->cfg;
+  const ParamOffsets& p = st->po;
+  const int H = c.hidden, F = c.ffn, B = c.micro_batch;
+  SmallBackward b;
+  b.dh = (float*)(ws + w.dh); b.d1 = (float*)(ws + w.d1); b.d2 = (float*)(ws + w.d2); b.d3 = (float*)(ws + w.d3);
+  b.dctx = (float*)(ws + w.dctx); b.dqkv = (float*)(ws + w.dqkv);
+  for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 3; ++j) b.p_ln[i][j] = (float*)(ws + w.p_ln[i][j]);
+  b.p_dh = (float*)(ws + w.p_dh); b.p_dqkv = (float*)(ws + w.p_dqkv); b.p_df = (float*)(ws + w.p_df);
+  HIPCHK(launch_small_bwd(s, B, small_args(st, kind, slot, layer, 1, dy, dx), b));
+  bool ok;
+  if (c.arch == BAMBOO_ARCH_POST_LN_ENCODER) {
+    ok = grad_reduce_add(batch, H, B, b.p_ln[1][0], G + p.g2, b.p_ln[1][1], G + p.be2) &&
+         grad_reduce_add(batch, H, B, b.p_ln[1][2], G + p.b2, nullptr, nullptr) &&
+         grad_reduce_add(batch, H, B, b.p_ln[0][0], G + p.g1, b.p_ln[0][1], G + p.be1) &&
+         grad_reduce_add(batch, H, B, b.p_ln[0][2], G + p.bo, nullptr, nullptr);
+  } else {
+    ok = grad_reduce_add(batch, H, B, b.p_df, G + p.b2, nullptr, nullptr) &&
+         grad_reduce_add(batch, H, B, b.p_ln[1][0], G + p.g2, b.p_ln[1][1], G + p.be2) &&
+         grad_reduce_add(batch, H, B, b.p_ln[1][2], G + p.bo, nullptr, nullptr) &&
+         grad_reduce_add(batch, H, B, b.p_ln[0][0], G + p.g1, b.p_ln[0][1], G + p.be1);
+  }
+  ok = ok && grad_reduce_add(batch, F, B, b.p_dh, G + p.b1, nullptr, nullptr) &&
+       grad_reduce_add(batch, 3 * H, B, b.p_dqkv, G + p.bqkv, nullptr, nullptr);
+  return ok ? BAMBOO_OK : BAMBOO_E_STATE;
+}
+
 // backward of one layer stack; gx may be null (input gradient discarded).  Lane 1 only with eager BRC.
 int run_backward(bamboo_stage* st, int kind, int lane_id, int slot, const void* gy, void* gx) {
   const bamboo_cfg_t& c = st->cfg;
@@ -451,6 +516,20 @@ int run_backward(bamboo_stage* st, int kind, int lane_id, int slot, const void* 
     auto P = [&](uint64_t off) { return (const void*)(W + off * es); };
     void* dx = (l == 0) ? (gx ? gx : (void*)(ws + w.ping)) : (void*)(ws + (((n - 1 - l) & 1) ? w.pong : w.ping));
     if (dx == dy) dx = ws + w.pong;  // never alias input and output of a layer
+    if (small_layers(st, kind)) {
+      GradReduceBatch sums;
+      sums.n = 0;
+      BBCHK(small_backward(st, kind, s, ws, w, slot, l, dy, dx, G, &sums));
+      const bool post = c.arch == BAMBOO_ARCH_POST_LN_ENCODER;
+      const GemmDesc dW[4] = {
+          gemm_tn(rec + r.g, post ? ws + w.d3 : dy, G + st->po.W2, T, F, H), gemm_tn(rec + r.fin, dh, G + st->po.W1, T, H, F),
+          gemm_tn(rec + r.ctx, post ? d1 : d2, G + st->po.Wo, T, H, H), gemm_tn(rec + r.ain, dqkv, G + st->po.Wqkv, T, H, 3 * H)};
+      bool reduced = false;
+      BBCHK(p_gemm_group(st, s, dW, 4, &sums, &reduced));
+      if (!reduced) BBCHK(p_grad_reduce(st, s, sums));
+      dy = dx;
+      continue;
+    }
     AttnDesc a;
     memset(&a, 0, sizeof(a));
     a.B = c.micro_batch; a.S = c.seq; a.heads = c.heads; a.d = H / c.heads;

@@ -82,6 +82,39 @@ def test_iteration_matches_oracle(B, name):
     hz.succ.stage_destroy()
 
 
+@pytest.mark.parametrize("arch", [0, 1])
+@pytest.mark.parametrize("hidden,heads,ffn,seq,mb", [
+    (8, 2, 8, 1, 1),            # one token, fewer columns than a tile has
+    (64, 16, 520, 16, 3),       # a full row tile; three passes over the FFN's columns, the last of 8
+    (24, 2, 200, 17, 2),        # one row beyond a row tile
+    (64, 1, 264, 32, 1),        # the most keys and the widest head
+    (40, 5, 256, 31, 2)])
+def test_fp32_layers_of_a_sample_in_one_launch(B, arch, hidden, heads, ffn, seq, mb):
+    sc = synth.StageConfig("small", arch, 0, hidden, heads, ffn, seq, mb, 2, 2, 4, 1, 3, 51)
+    inp, st, hz = _build(B, sc)
+    hz.begin_iteration()
+    hz.run(st.stage_schedule())
+    hz.sync()
+    ref = _oracle(sc, inp)
+    for k in range(sc.M):
+        assert_close(B.to_host(hz.y[k]), ref.y[k], TOL[0], "small layers y")
+        assert_close(B.to_host(hz.z_frc[k]), ref.z_frc[k], TOL[0], "small layers z")
+        assert_close(B.to_host(hz.gx[k]), ref.gx[k], TOL[0], "small layers gx")
+        assert torch.equal(hz.z_frc[k], hz.z_succ[k])
+    check_grads(st.own_g.cpu().numpy(), ref.G_own, hidden, ffn, TOL[0], "own")
+    # with per-launch timing on, the same steps are launched one by one
+    inp, st1, hz1 = _build(B, sc)
+    st1.stage_profile(True)
+    hz1.begin_iteration()
+    hz1.run(st1.stage_schedule())
+    hz1.sync()
+    for k in range(sc.M):
+        assert_close(B.to_host(hz.y[k]), B.to_host(hz1.y[k]), TOL[0], "small layers y, launched singly")
+        assert_close(B.to_host(hz.gx[k]), B.to_host(hz1.gx[k]), TOL[0], "small layers gx, launched singly")
+    for s_ in (st, st1, hz.succ, hz1.succ):
+        s_.stage_destroy()
+
+
 @pytest.mark.parametrize("name,k_fail", [("tiny", 1), ("tiny", 3), ("ragged_fp32_causal", 0),
                                          ("ragged_fp32_causal", 3), ("bf16_post_ln", 2), ("bf16_causal_d128", 1)])
 def test_failover_matches_oracle_and_failure_free_run(B, name, k_fail):
