@@ -27,15 +27,31 @@ __device__ __forceinline__ float gelu_grad_f(float h) {
   return 0.5f * (1.0f + erff(h * 0.70710678118654752f)) + h * __expf(-0.5f * h * h) * 0.39894228040143268f;
 }
 
+// Sums and maxima over a wavefront whose lanes are all active: over 16 lanes by DPP, then through scalar registers.  (Six
+// __shfl_xor in a row are six trips through LDS.)
+#define BAMBOO_DPP(v, ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xf, 0xf, true))
+__device__ __forceinline__ float of_lane(float v, int j) {      // the value lane j (uniform) holds
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), j));
+}
+__device__ __forceinline__ float sum16(float v) {
+  v += BAMBOO_DPP(v, 0xb1);         // quad_perm 1 0 3 2
+  v += BAMBOO_DPP(v, 0x4e);         // quad_perm 2 3 0 1
+  v += BAMBOO_DPP(v, 0x124);        // row_ror 4
+  return v + BAMBOO_DPP(v, 0x128);  // row_ror 8
+}
+__device__ __forceinline__ float max16(float v) {
+  v = fmaxf(v, BAMBOO_DPP(v, 0xb1));
+  v = fmaxf(v, BAMBOO_DPP(v, 0x4e));
+  v = fmaxf(v, BAMBOO_DPP(v, 0x124));
+  return fmaxf(v, BAMBOO_DPP(v, 0x128));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v = sum16(v);
+  return (of_lane(v, 0) + of_lane(v, 16)) + (of_lane(v, 32) + of_lane(v, 48));
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  v = max16(v);
+  return fmaxf(fmaxf(of_lane(v, 0), of_lane(v, 16)), fmaxf(of_lane(v, 32), of_lane(v, 48)));
 }
 
 // ---- per-process launch state ------------------------------------------------

@@ -156,35 +156,16 @@ __device__ __forceinline__ void small_product(Frags& f, const float* act, int ld
   }
 }
 
-// Sums and maxima over 16 lanes by DPP, over the wavefront or its halves through scalar registers: no trip through LDS
-#define SMALL_DPP(ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xf, 0xf, true))
-__device__ __forceinline__ float of_lane(float v, int j) {      // the value lane j (uniform) holds
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), j));
-}
-__device__ __forceinline__ float sum16(float v) {
-  v += SMALL_DPP(0xb1);         // quad_perm 1 0 3 2
-  v += SMALL_DPP(0x4e);         // quad_perm 2 3 0 1
-  v += SMALL_DPP(0x124);        // row_ror 4
-  return v + SMALL_DPP(0x128);  // row_ror 8
-}
-__device__ __forceinline__ float small_sum(float v) {
-  v = sum16(v);
-  return (of_lane(v, 0) + of_lane(v, 16)) + (of_lane(v, 32) + of_lane(v, 48));
-}
 __device__ __forceinline__ float half_sum(float v) {
   v = sum16(v);
   const float lo = of_lane(v, 0) + of_lane(v, 16), hi = of_lane(v, 32) + of_lane(v, 48);
   return (threadIdx.x & 32) ? hi : lo;
 }
 __device__ __forceinline__ float half_max(float v) {
-  v = fmaxf(v, SMALL_DPP(0xb1));
-  v = fmaxf(v, SMALL_DPP(0x4e));
-  v = fmaxf(v, SMALL_DPP(0x124));
-  v = fmaxf(v, SMALL_DPP(0x128));
+  v = max16(v);
   const float lo = fmaxf(of_lane(v, 0), of_lane(v, 16)), hi = fmaxf(of_lane(v, 32), of_lane(v, 48));
   return (threadIdx.x & 32) ? hi : lo;
 }
-#undef SMALL_DPP
 // sum over j < n of x[j * ld] times the weight that lane j of this half-wave holds; n <= most (uniform) <= 32
 __device__ __forceinline__ float half_weighted(float weight, const float* x, int ld, int n, int most) {
   float o = 0.f;
@@ -226,8 +207,8 @@ __device__ __forceinline__ void small_ln_fwd(const float* in, int ld, int S, int
   const float g = gamma[min(lane, H - 1)], b = beta[min(lane, H - 1)];
   for (int row = wave; row < S; row += kWaves) {
     const float v = live ? in[row * ld + lane] : 0.f;
-    const float mean = small_sum(v) / (float)H;
-    const float rstd = rsqrtf(small_sum(live ? (v - mean) * (v - mean) : 0.f) / (float)H + eps);
+    const float mean = wave_sum(v) / (float)H;
+    const float rstd = rsqrtf(wave_sum(live ? (v - mean) * (v - mean) : 0.f) / (float)H + eps);
     if (live) out(row, lane, g * ((v - mean) * rstd) + b);
     if (lane == 0) {
       stats[2 * row] = mean;
@@ -538,7 +519,7 @@ __global__ __launch_bounds__(kThreads) void small_bwd_kernel(SmallLayers a, Smal
         const float in = live ? (step == 3 ? k.x[row * H + lane] : xh[row * LH + lane]) : 0.f;
         const float x = live ? (in - mean) * rstd : 0.f;
         const float dh = live ? D2[row * LH + lane] * gamma[lane] : 0.f;
-        const float m1 = small_sum(dh) / (float)H, m2 = small_sum(dh * x) / (float)H;
+        const float m1 = wave_sum(dh) / (float)H, m2 = wave_sum(dh * x) / (float)H;
         if (live) {
           float o = (dh - m1 - x * m2) * rstd;
           if (add != nullptr) o += add[row * LH + lane];

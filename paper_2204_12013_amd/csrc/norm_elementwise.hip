@@ -149,6 +149,76 @@ __global__ __launch_bounds__(256) void layernorm_fwd_long_kernel(int T_rows, int
   }
 }
 
+// Rows too long for a wavefront: a workgroup of eight takes a row, NC vectors a thread, and reads it once.  2048 rows of
+// 12288, launch to launch: 39 -> 22 us (before: a wavefront per row and three passes over it).
+constexpr int kWideThreads = 512;
+// sums of two values over the workgroup, for every thread; `red`: 16 floats that the next call does not use
+__device__ __forceinline__ void wide_sums(float& a, float& b, float* red) {
+  const int w = threadIdx.x >> 6;
+  a = wave_sum(a);
+  b = wave_sum(b);
+  if ((threadIdx.x & 63) == 0) {
+    red[w] = a;
+    red[8 + w] = b;
+  }
+  __syncthreads();
+  a = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+  b = ((red[8] + red[9]) + (red[10] + red[11])) + ((red[12] + red[13]) + (red[14] + red[15]));
+}
+template <typename T, int NC>
+__global__ __launch_bounds__(kWideThreads) void layernorm_fwd_wide_kernel(int H, float eps, const T* __restrict__ r,
+                                                                          const T* __restrict__ gamma,
+                                                                          const T* __restrict__ beta, T* __restrict__ y,
+                                                                          float* __restrict__ stats) {
+  constexpr int V = Vec<T>::N;
+  __shared__ float red[2][16];
+  const long row = blockIdx.x, off = row * H;
+  const int nvec = H / V;
+  typename Vec<T>::Raw raw[NC], graw[NC], braw[NC];
+  int cc[NC];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    cc[j] = min((int)threadIdx.x + kWideThreads * j, nvec - 1) * V;
+    raw[j] = Vec<T>::load_raw(r + off + cc[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    graw[j] = Vec<T>::load_raw(gamma + cc[j]);
+    braw[j] = Vec<T>::load_raw(beta + cc[j]);
+  }
+  float v[NC][V], s = 0.f, q = 0.f, none = 0.f;
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    Vec<T>::unpack(raw[j], v[j]);
+    if ((int)threadIdx.x + kWideThreads * j < nvec)
+#pragma unroll
+      for (int i = 0; i < V; ++i) s += v[j][i];
+  }
+  wide_sums(s, none, red[0]);
+  const float mean = s / (float)H;
+#pragma unroll
+  for (int j = 0; j < NC; ++j)
+    if ((int)threadIdx.x + kWideThreads * j < nvec)
+#pragma unroll
+      for (int i = 0; i < V; ++i) q += (v[j][i] - mean) * (v[j][i] - mean);
+  none = 0.f;
+  wide_sums(q, none, red[1]);
+  const float rstd = rsqrtf(q / (float)H + eps);
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    float g[V], b[V], o[V];
+    Vec<T>::unpack(graw[j], g);
+    Vec<T>::unpack(braw[j], b);
+#pragma unroll
+    for (int i = 0; i < V; ++i) o[i] = g[i] * ((v[j][i] - mean) * rstd) + b[i];
+    if ((int)threadIdx.x + kWideThreads * j < nvec) Vec<T>::store(y + off + cc[j], o);
+  }
+  if (threadIdx.x == 0) {
+    stats[2 * row] = mean;
+    stats[2 * row + 1] = rstd;
+  }
+}
+
 template <typename T>
 static hipError_t ln_fwd_impl(hipStream_t s, int T_rows, int H, float eps, const void* r, const void* gamma,
                               const void* beta, void* y, float* stats) {
@@ -162,7 +232,14 @@ static hipError_t ln_fwd_impl(hipStream_t s, int T_rows, int H, float eps, const
   else if (nch <= 2) LN_FWD((layernorm_fwd_kernel<T, 2>));
   else if (nch <= 4) LN_FWD((layernorm_fwd_kernel<T, 4>));
   else if (nch <= 8) LN_FWD((layernorm_fwd_kernel<T, 8>));
-  else LN_FWD(layernorm_fwd_long_kernel<T>);
+  else if (nch > 32) LN_FWD(layernorm_fwd_long_kernel<T>);
+#undef LN_FWD
+#define LN_FWD(NC)                                                                                              \
+  hipLaunchKernelGGL((layernorm_fwd_wide_kernel<T, NC>), dim3(T_rows), dim3(kWideThreads), 0, s, H, eps,         \
+                     (const T*)r, (const T*)gamma, (const T*)beta, (T*)y, stats)
+  else if (nch <= 16) LN_FWD(2);
+  else if (nch <= 24) LN_FWD(3);
+  else LN_FWD(4);
 #undef LN_FWD
   return hipGetLastError();
 }
@@ -179,50 +256,60 @@ hipError_t launch_layernorm_fwd(hipStream_t s, int dtype, int T, int H, float ep
 // gain and shift gradients (sum dout*rhat, sum dout) and, if COLSUM, the column sums of the stored
 // output dr (the bias gradient of the linear layer whose output gradient dr is), and writes one
 // partial row of each per workgroup; lane-owned columns stay in registers across rows.
-// A wavefront takes two of its rows per pass and requests all of their data before it works on
-// either: the kernel is bound by memory latency times bytes in flight, not by arithmetic.  Lanes
-// past the row's end re-read its last vector and zero it.
-template <typename T, int NCH, bool ADD, bool COLSUM>
-__global__ __launch_bounds__(256) void layernorm_bwd_fused_kernel(int T_rows, int H, int rows_per_block,
+// Eight wavefronts, two per SIMD; each requests U of its rows at once (4096 rows: all it has) before it works on them.
+// Lanes past the row's end re-read its last vector; their gain is zero and what they sum is not stored.
+// Launch to launch with cold operands: 4096 rows of 1024 12.0 -> 9.0 us, of 1600 with the residual 18.3 -> 15.5, 999 of 1024
+// 7.5 -> 5.3, 128 of 1024 6.2 -> 4.4 (before: four wavefronts, two rows per pass, 4-byte accesses in the reductions).  A
+// third of what is left is the launch and the first trip to memory, a fifth the reductions over the wavefronts.
+// the compiler is not to carry what it has unpacked from a raw vector on to its next use
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+template <typename RAW>
+__device__ __forceinline__ RAW keep_raw(const RAW& v) {
+  u32x4 t = __builtin_bit_cast(u32x4, v);
+  asm volatile("" : "+v"(t));
+  return __builtin_bit_cast(RAW, t);
+}
+template <typename T, int NCH, bool ADD, bool COLSUM, int U>
+__global__ __launch_bounds__(512) void layernorm_bwd_fused_kernel(int T_rows, int H, int rows_per_block,
                                                                   const T* __restrict__ dout, const T* __restrict__ r,
                                                                   const float* __restrict__ stats,
                                                                   const T* __restrict__ gamma,
                                                                   const T* __restrict__ add, T* __restrict__ dr,
                                                                   float* __restrict__ pg, float* __restrict__ pb,
                                                                   float* __restrict__ pc) {
-  constexpr int V = Vec<T>::N;
+  constexpr int V = Vec<T>::N, NW = 8;
+  constexpr bool KEEP = NCH * V <= 16;       // gain times gradient: kept, or formed again where registers run out
   typedef typename Vec<T>::Raw Raw;
-  extern __shared__ float red[];                 // [4][H]
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  extern __shared__ __attribute__((aligned(16))) float red[];      // [NW][NCH][V / 4][64] of 4 floats
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nvec = H / V;
-  float g[NCH][V], ag[NCH][V], ab[NCH][V], ac[COLSUM ? NCH : 1][V];
+  float ag[NCH][V], ab[NCH][V], ac[COLSUM ? NCH : 1][V];
+  Raw graw[NCH];
   int cc[NCH];
-  float keep[NCH];
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
     const int c = lane + 64 * j;
     cc[j] = min(c, nvec - 1) * V;
-    keep[j] = c < nvec ? 1.f : 0.f;
 #pragma unroll
     for (int i = 0; i < V; ++i) { ag[j][i] = 0.f; ab[j][i] = 0.f; }
     if (COLSUM) {
 #pragma unroll
       for (int i = 0; i < V; ++i) ac[j][i] = 0.f;
     }
-    Vec<T>::load(gamma + cc[j], g[j]);
+    graw[j] = Vec<T>::load_raw(gamma + cc[j]);
+    if (c >= nvec) graw[j] = Raw{};
   }
   const int row_end = min(T_rows, (int)(blockIdx.x + 1) * rows_per_block);
-  for (int row0 = blockIdx.x * rows_per_block + w; row0 < row_end; row0 += 8) {
-    // second row of the pass: if there is none, the first is read again and its results dropped
-    const bool two = row0 + 4 < row_end;
-    const int rows[2] = {row0, two ? row0 + 4 : row0};
-    Raw dw[2][NCH], xw[2][NCH], aw[2][ADD ? NCH : 1];
-    float mean[2], rstd[2];
+  for (int row0 = blockIdx.x * rows_per_block + w; row0 < row_end; row0 += NW * U) {
+    Raw dw[U][NCH], xw[U][NCH], aw[U][ADD ? NCH : 1];
+    float mean[U], rstd[U];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const long off = (long)rows[u] * H;
-      mean[u] = stats[2 * rows[u]];
-      rstd[u] = stats[2 * rows[u] + 1];
+    for (int u = 0; u < U; ++u) {
+      const int row = min(row0 + NW * u, row_end - 1);        // if there is none, one that has been read anyway
+      const long off = (long)row * H;
+      mean[u] = stats[2 * row];
+      rstd[u] = stats[2 * row + 1];
 #pragma unroll
       for (int j = 0; j < NCH; ++j) {
         dw[u][j] = Vec<T>::load_raw(dout + off + cc[j]);
@@ -231,35 +318,46 @@ __global__ __launch_bounds__(256) void layernorm_bwd_fused_kernel(int T_rows, in
       }
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const float use = (u == 0 || two) ? 1.f : 0.f;
-      const long off = (long)rows[u] * H;
-      float d[NCH][V], xh[NCH][V];
+    for (int u = 0; u < U; ++u) {
+      const int row = row0 + NW * u;
+      if (row >= row_end) break;                              // uniform over the wavefront
+      const long off = (long)row * H;
+      float dhat[KEEP ? NCH : 1][V], xh[NCH][V];
       float s1 = 0.f, s2 = 0.f;
 #pragma unroll
       for (int j = 0; j < NCH; ++j) {
-        float x[V];
-        Vec<T>::unpack(dw[u][j], d[j]);
+        float d[V], x[V], g[V];
+        Vec<T>::unpack(dw[u][j], d);
         Vec<T>::unpack(xw[u][j], x);
-        const float k = keep[j] * use;
+        Vec<T>::unpack(graw[j], g);
 #pragma unroll
         for (int i = 0; i < V; ++i) {
-          d[j][i] *= k;
           xh[j][i] = (x[i] - mean[u]) * rstd[u];
-          ag[j][i] += d[j][i] * xh[j][i];
-          ab[j][i] += d[j][i];
-          d[j][i] *= g[j][i];                      // dhat
-          s1 += d[j][i];
-          s2 += d[j][i] * xh[j][i];
+          ag[j][i] += d[i] * xh[j][i];
+          ab[j][i] += d[i];
+          d[i] *= g[i];
+          s1 += d[i];
+          s2 += d[i] * xh[j][i];
+          if (KEEP) dhat[j][i] = d[i];
         }
       }
       const float m1 = wave_sum(s1) / (float)H;
       const float m2 = wave_sum(s2) / (float)H;
 #pragma unroll
       for (int j = 0; j < NCH; ++j) {
-        float o[V];
+        float o[V], d[V];
+        if (KEEP) {
 #pragma unroll
-        for (int i = 0; i < V; ++i) o[i] = (d[j][i] - m1 - xh[j][i] * m2) * rstd[u];
+          for (int i = 0; i < V; ++i) d[i] = dhat[j][i];
+        } else {
+          float g[V];
+          Vec<T>::unpack(keep_raw(dw[u][j]), d);
+          Vec<T>::unpack(keep_raw(graw[j]), g);
+#pragma unroll
+          for (int i = 0; i < V; ++i) d[i] *= g[i];
+        }
+#pragma unroll
+        for (int i = 0; i < V; ++i) o[i] = (d[i] - m1 - xh[j][i] * m2) * rstd[u];
         if (ADD) {
           float a[V];
           Vec<T>::unpack(aw[u][j], a);
@@ -267,31 +365,136 @@ __global__ __launch_bounds__(256) void layernorm_bwd_fused_kernel(int T_rows, in
           for (int i = 0; i < V; ++i) o[i] += a[i];
         }
         if (COLSUM) {
-          const float k = keep[j] * use;
 #pragma unroll
-          for (int i = 0; i < V; ++i) ac[j][i] += k * round_storage<T>(o[i]);
+          for (int i = 0; i < V; ++i) ac[j][i] += round_storage<T>(o[i]);
         }
-        if (lane + 64 * j < nvec && (u == 0 || two)) Vec<T>::store(dr + off + cc[j], o);
+        if (lane + 64 * j < nvec) Vec<T>::store(dr + off + cc[j], o);
       }
     }
   }
-  // ordered reduction of the four wavefronts: gain gradient, shift gradient, output column sums
+  // ordered reduction over the wavefronts: gain gradient, shift gradient, output column sums
+  constexpr int UNITS = NCH * (V / 4) * 64;
 #pragma unroll
   for (int which = 0; which < (COLSUM ? 3 : 2); ++which) {
-    __syncthreads();
+    if (which > 0) __syncthreads();
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-      const int c = lane + 64 * j;
-      if (c < nvec) {
+    for (int j = 0; j < NCH; ++j)
 #pragma unroll
-        for (int i = 0; i < V; ++i)
-          red[w * H + c * V + i] = which == 0 ? ag[j][i] : (which == 1 ? ab[j][i] : ac[COLSUM ? j : 0][i]);
+      for (int q = 0; q < V / 4; ++q) {
+        f32x4 t;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          t[i] = which == 0 ? ag[j][4 * q + i] : (which == 1 ? ab[j][4 * q + i] : ac[COLSUM ? j : 0][4 * q + i]);
+        *(f32x4*)(red + ((w * UNITS) + (j * (V / 4) + q) * 64 + lane) * 4) = t;
       }
-    }
     __syncthreads();
     float* out = (which == 0 ? pg : (which == 1 ? pb : pc)) + (long)blockIdx.x * H;
-    for (int c = threadIdx.x; c < H; c += 256) out[c] = ((red[c] + red[H + c]) + red[2 * H + c]) + red[3 * H + c];
+    for (int k = threadIdx.x; k < UNITS; k += 512) {
+      f32x4 t = *(const f32x4*)(red + k * 4);
+#pragma unroll
+      for (int v = 1; v < NW; ++v) t += *(const f32x4*)(red + (v * UNITS + k) * 4);
+      const int c = ((k & 63) + 64 * (k / (64 * (V / 4)))) * V + 4 * ((k >> 6) % (V / 4));
+      if (c < H) *(f32x4*)(out + c) = t;
+    }
   }
+}
+
+// The same for rows too long for a wavefront: a workgroup works through its rows one after the other, the next one on its
+// way meanwhile, a thread keeping its columns' sums.  2048 rows of 12288, with the residual and the column sums: 97 -> 51 us
+// (before: column sums, gradient and its column sums as three launches).
+template <typename T, int NC, bool ADD, bool COLSUM>
+__global__ __launch_bounds__(kWideThreads) void layernorm_bwd_wide_kernel(int T_rows, int H, int rows_per_block,
+                                                                          const T* __restrict__ dout,
+                                                                          const T* __restrict__ r,
+                                                                          const float* __restrict__ stats,
+                                                                          const T* __restrict__ gamma,
+                                                                          const T* __restrict__ add, T* __restrict__ dr,
+                                                                          float* __restrict__ pg, float* __restrict__ pb,
+                                                                          float* __restrict__ pc) {
+  constexpr int V = Vec<T>::N;
+  typedef typename Vec<T>::Raw Raw;
+  __shared__ float red[2][16];
+  const int nvec = H / V;
+  float ag[NC][V] = {}, ab[NC][V] = {}, ac[COLSUM ? NC : 1][V] = {};
+  Raw graw[NC], dw[NC], xw[NC], aw[ADD ? NC : 1], dn[NC], xn[NC], an[ADD ? NC : 1];
+  int cc[NC];
+  const int first = blockIdx.x * rows_per_block, row_end = min(T_rows, first + rows_per_block);
+  auto fetch = [&](int row, Raw (&d)[NC], Raw (&x)[NC], Raw (&a)[ADD ? NC : 1]) __attribute__((always_inline)) {
+    const long off = (long)row * H;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      d[j] = Vec<T>::load_raw(dout + off + cc[j]);
+      x[j] = Vec<T>::load_raw(r + off + cc[j]);
+      if (ADD) a[j] = Vec<T>::load_raw(add + off + cc[j]);
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    const int c = threadIdx.x + kWideThreads * j;
+    cc[j] = min(c, nvec - 1) * V;
+    graw[j] = Vec<T>::load_raw(gamma + cc[j]);
+    if (c >= nvec) graw[j] = Raw{};
+  }
+  fetch(first, dw, xw, aw);
+  for (int row = first; row < row_end; ++row) {
+    const float mean = stats[2 * row], rstd = stats[2 * row + 1];
+    fetch(min(row + 1, row_end - 1), dn, xn, an);
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      float d[V], x[V], g[V];
+      Vec<T>::unpack(dw[j], d);
+      Vec<T>::unpack(xw[j], x);
+      Vec<T>::unpack(graw[j], g);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        x[i] = (x[i] - mean) * rstd;
+        ag[j][i] += d[i] * x[i];
+        ab[j][i] += d[i];
+        d[i] *= g[i];
+        s1 += d[i];
+        s2 += d[i] * x[i];
+      }
+    }
+    wide_sums(s1, s2, red[(row - first) & 1]);
+    const float m1 = s1 / (float)H, m2 = s2 / (float)H;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      float o[V], d[V], x[V], g[V];
+      Vec<T>::unpack(keep_raw(dw[j]), d);
+      Vec<T>::unpack(keep_raw(xw[j]), x);
+      Vec<T>::unpack(keep_raw(graw[j]), g);
+#pragma unroll
+      for (int i = 0; i < V; ++i) o[i] = (d[i] * g[i] - m1 - (x[i] - mean) * rstd * m2) * rstd;
+      if (ADD) {
+        float a[V];
+        Vec<T>::unpack(aw[j], a);
+#pragma unroll
+        for (int i = 0; i < V; ++i) o[i] += a[i];
+      }
+      if (COLSUM) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) ac[j][i] += round_storage<T>(o[i]);
+      }
+      if ((int)threadIdx.x + kWideThreads * j < nvec) Vec<T>::store(dr + (long)row * H + cc[j], o);
+      dw[j] = dn[j];
+      xw[j] = xn[j];
+      if (ADD) aw[j] = an[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NC; ++j)
+    if ((int)threadIdx.x + kWideThreads * j < nvec) {
+      const long c = (long)blockIdx.x * H + cc[j];
+      Vec<float>::store(pg + c, *(const float(*)[4])&ag[j][0]);
+      Vec<float>::store(pb + c, *(const float(*)[4])&ab[j][0]);
+      if (COLSUM) Vec<float>::store(pc + c, *(const float(*)[4])&ac[COLSUM ? j : 0][0]);
+      if (V == 8) {
+        Vec<float>::store(pg + c + 4, *(const float(*)[4])&ag[j][V - 4]);
+        Vec<float>::store(pb + c + 4, *(const float(*)[4])&ab[j][V - 4]);
+        if (COLSUM) Vec<float>::store(pc + c + 4, *(const float(*)[4])&ac[COLSUM ? j : 0][V - 4]);
+      }
+    }
 }
 
 // dr only (any row length); gain/shift gradients come from colreduce_kernel<.,1>
@@ -455,9 +658,9 @@ hipError_t launch_grad_reduce(hipStream_t s, const GradReduceBatch& b) {
 }
 
 // rows per workgroup and number of workgroups along the token axis
-static void split_rows(int T, int max_blocks, int* rows_per_block, int* blocks) {
+static void split_rows(int T, int max_blocks, int* rows_per_block, int* blocks, int least = 4) {
   int rpb = (T + max_blocks - 1) / max_blocks;
-  if (rpb < 4) rpb = 4;
+  if (rpb < least) rpb = least;
   *rows_per_block = rpb;
   *blocks = (T + rpb - 1) / rpb;
 }
@@ -517,12 +720,12 @@ static hipError_t ln_bwd_partials_impl(hipStream_t s, int T_rows, int H, const v
   constexpr int V = Vec<T>::N;
   const int nch = (H / V + 63) / 64;
   int rpb, rb;
-  if (nch <= 4 && (size_t)4 * H * sizeof(float) <= 48 * 1024) {
-    split_rows(T_rows, kMaxPartials, &rpb, &rb);
-    const size_t sh = (size_t)4 * H * sizeof(float);
+  if (nch <= 4) {
+    split_rows(T_rows, kMaxPartials, &rpb, &rb, 8);      // a row for each of the eight wavefronts
 #define LN_BWD1(NC, A, C)                                                                                          \
-  hipLaunchKernelGGL((layernorm_bwd_fused_kernel<T, NC, A, C>), dim3(rb), dim3(256), sh, s, T_rows, H, rpb,         \
-                     (const T*)dout, (const T*)r, stats, (const T*)gamma, (const T*)add, (T*)dr, pg, pb, pc)
+  hipLaunchKernelGGL((layernorm_bwd_fused_kernel<T, NC, A, C, (NC <= 2 ? 2 : 1)>), dim3(rb), dim3(512),              \
+                     (size_t)8 * NC * 64 * V * sizeof(float), s, T_rows, H, rpb, (const T*)dout,                     \
+                      (const T*)r, stats, (const T*)gamma, (const T*)add, (T*)dr, pg, pb, pc)
 #define LN_BWD(NC)                                                                                                 \
   do {                                                                                                             \
     if (add != nullptr) { if (pc != nullptr) LN_BWD1(NC, true, true); else LN_BWD1(NC, true, false); }             \
@@ -531,6 +734,15 @@ static hipError_t ln_bwd_partials_impl(hipStream_t s, int T_rows, int H, const v
     if (nch <= 1) LN_BWD(1);
     else if (nch <= 2) LN_BWD(2);
     else LN_BWD(4);
+#undef LN_BWD1
+  } else if (nch <= 24) {
+    split_rows(T_rows, kMaxPartials, &rpb, &rb, 1);
+#define LN_BWD1(NC, A, C)                                                                                          \
+  hipLaunchKernelGGL((layernorm_bwd_wide_kernel<T, NC, A, C>), dim3(rb), dim3(kWideThreads), 0, s, T_rows, H, rpb,   \
+                     (const T*)dout, (const T*)r, stats, (const T*)gamma, (const T*)add, (T*)dr, pg, pb, pc)
+    if (nch <= 8) LN_BWD(1);
+    else if (nch <= 16) LN_BWD(2);
+    else LN_BWD(3);
 #undef LN_BWD1
 #undef LN_BWD
   } else {

@@ -320,6 +320,15 @@ def test_layernorm_forward_backward(B, dtype, T, H):
     assert_close(dg.cpu().numpy(), 2 * dg_ref, 1e-4, "kernels dg.cpu().numpy()")
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("T,H", [(1, 8), (7, 512), (8, 520), (9, 1024), (17, 1032), (25, 2048), (2049, 72), (3, 2056), (9, 4104),
+                                 (5, 8192), (257, 8200), (5, 12288), (3, 12296), (2, 16392)])
+def test_layernorm_at_the_edges_of_its_kernels(B, dtype, T, H):
+    """Rows a wavefront holds in one, two and four vectors a lane, rows a workgroup holds in one to four a thread, and
+    longer ones; fewer rows than wavefronts, one more than a pass takes, one more than the partial rows."""
+    test_layernorm_forward_backward(B, dtype, T, H)
+
+
 def test_mfma_attention_refuses_sequences_beyond_its_32_bit_tile_offsets(B):
     # the MFMA kernels address a (batch, head) slice of qkv with 32-bit byte offsets: a sequence whose rows span
     # 4 GiB or more is refused when the kernels are forced, nothing is launched
