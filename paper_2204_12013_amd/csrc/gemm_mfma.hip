@@ -1305,6 +1305,22 @@ static const TileCost kCostAcc[] = {       // fp32 read-modify-write output (wei
     {11, 2, 0.69f, 0.444f, 6.39f}, {11, 4, 1.88f, 0.438f, 2.32f}, {22, 2, 12.15f, 0.935f, 0.f},
     {22, 3, 5.78f, 0.564f, 3.32f}, {24, 3, 9.21f, 0.981f, 3.42f}, {42, 3, 9.66f, 0.958f, 3.31f},
     {44, 2, 28.80f, 1.223f, 0.f}};
+// The same for the four products of a layer in one launch (launch_gemm_group_mfma), whose tiles share the rounds: fits to
+// timings of 18 groups (layers of 1024 x 4096, 1600 x 6400 and 512 x 2048, 64 to 4096 tokens), microseconds:
+//   tokens  layer         128 x 128, three deep   128 x 128, two deep, two per CU   256 x 256
+//   128     1024 x 4096    25.0                    24.7                              31.2
+//   768     1024 x 4096    37.2                    37.3                              42.2
+//   1000    1024 x 4096    42.1                    43.1                              46.8
+//   2048    1024 x 4096    64.8                    67.0                              65.7
+//   4096    1024 x 4096   112.5                   117.2                             103.9
+//   128     1600 x 6400    58.1                    52.5                              63.9
+//   1024    1600 x 6400   113.7                    92.9                             102.0
+//   2048    1600 x 6400   185.2                   152.6                             148.8
+// Two workgroups on a CU overlap one's gradient reads and writes, which are most of a short product's time, with the other's
+// loop.  (By the single launches' coefficients above the large tile was taken from 600 tokens on.)
+static const TileCost kCostGroup[] = {
+    {22, 3, 5.3f, 0.51f, 4.0f}, {22, 2, 9.6f, 0.84f, 1.1f}, {44, 2, 29.5f, 1.30f, 0.f}, {24, 3, 9.21f, 0.981f, 3.42f},
+    {42, 3, 9.66f, 0.958f, 3.31f}};
 static float rounds_of(long tiles, long slots) {
   const long full = tiles / slots, rest = tiles % slots;
   return (float)full + (rest > 0 ? 0.75f + 0.25f * (float)rest / (float)slots : 0.f);
@@ -1496,18 +1512,11 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
     if (!wgrad_form_ok(d[i])) return hipErrorNotSupported;
     g.d[i] = d[i];
   }
-  // Tile shape for the whole group: 128 x 128, 128 x 256 or 256 x 128 with a ring of three, or 256 x 256
-  // with a ring of two -- the cheapest by the cost model of the single launches, with all tiles of the
-  // group sharing the rounds.
-  const int codes[4] = {22, 44, 24, 42}, nss[4] = {3, 2, 3, 3};
-  int pick = 0;
+  // Tile shape for the whole group: the cheapest by the cost model, with all tiles of the group sharing the rounds.
+  int pick = 0, depth = 0;
   float best = 0.f;
-  for (int c = 0; c < 4; ++c) {
-    const TileCost* t = nullptr;
-    for (const TileCost& e : kCostAcc)
-      if (e.code == codes[c] && e.ns == nss[c]) t = &e;
-    if (!t) continue;
-    const int wm = codes[c] / 10, wn = codes[c] % 10;
+  for (const TileCost& t : kCostGroup) {
+    const int wm = t.code / 10, wn = t.code % 10;
     bool reached = true;
     for (int i = 0; i < n; ++i) reached = reached && tile_in_reach(d[i], 64 * wm, 64 * wn);
     if (!reached) continue;
@@ -1515,7 +1524,7 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
     double slices = 0;
     for (int i = 0; i < n; ++i) {
       long ti = (long)((d[i].M + 64 * wm - 1) / (64 * wm)) * ((d[i].N + 64 * wn - 1) / (64 * wn));
-      if (codes[c] == 44) {
+      if (t.code == 44) {
         int tm, tn;
         const int strips = edge_strips(d[i].M, d[i].N, &tm, &tn);
         ti = (long)tm * tn + (long)ceilf(strips * strip_share((float)k_slices(d[i].K)));
@@ -1523,9 +1532,11 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
       tiles += ti;
       slices += (double)ti * k_slices(d[i].K);
     }
-    const float cost = rounds_of(tiles, 256) * (t->a + t->b * (float)(slices / tiles)) + t->c;
+    const bool pairs = t.code == 22 && t.ns == 2;            // two workgroups to a CU
+    const float cost = rounds_of(tiles, pairs ? 512 : 256) * (t.a + t.b * (float)(slices / tiles)) + t.c;
     if (pick == 0 || cost < best) {
-      pick = codes[c];
+      pick = t.code;
+      depth = t.ns;
       best = cost;
     }
   }
@@ -1534,6 +1545,7 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
     for (int i = 0; i < n; ++i)
       if (!tile_in_reach(d[i], 64 * (g_forced_tile / 10), 64 * (g_forced_tile % 10))) return hipErrorNotSupported;
     pick = g_forced_tile;
+    depth = 3;
   } else if (g_forced_tile || g_forced_stages) {
     return hipErrorNotSupported;   // a forced shape this launch does not offer
   }
@@ -1541,7 +1553,7 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
     case 44: return launch_group_cfg<4, 4, 2>(s, g);
     case 24: return launch_group_cfg<2, 4, 3>(s, g);
     case 42: return launch_group_cfg<4, 2, 3>(s, g);
-    default: return launch_group_cfg<2, 2, 3>(s, g);
+    default: return depth == 2 ? launch_group_cfg<2, 2, 2>(s, g) : launch_group_cfg<2, 2, 3>(s, g);
   }
 }
 

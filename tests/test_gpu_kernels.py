@@ -127,6 +127,7 @@ def test_a_forced_ring_depth_holds_for_products_that_would_split_K(B):
     [(4096, 1024, 1024), (4096, 1024, 3072)],
     [(256, 200, 96)],
     [(100, 64, 64), (256, 64, 64)],            # a contraction length that ends inside a 64-deep slice
+    [(130, 6400, 1600), (130, 1600, 6400), (130, 1600, 1600), (130, 1600, 4800)],   # short products: two workgroups to a CU
 ])
 def test_grouped_weight_gradients_equal_the_single_launches_bitwise(B, shapes):
     rng = np.random.default_rng(len(shapes) * 7 + shapes[0][0])
