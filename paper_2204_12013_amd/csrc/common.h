@@ -27,8 +27,8 @@ __device__ __forceinline__ float gelu_grad_f(float h) {
   return 0.5f * (1.0f + erff(h * 0.70710678118654752f)) + h * __expf(-0.5f * h * h) * 0.39894228040143268f;
 }
 
-// Sums and maxima over a wavefront whose lanes are all active: over 16 lanes by DPP, then through scalar registers.  (Six
-// __shfl_xor in a row are six trips through LDS.)
+// Sums and maxima over a wavefront whose lanes are all active, by DPP and lane swaps.  (Six __shfl_xor in a row are six trips
+// through LDS.)
 #define BAMBOO_DPP(v, ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xf, 0xf, true))
 __device__ __forceinline__ float of_lane(float v, int j) {      // the value lane j (uniform) holds
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), j));
@@ -45,9 +45,20 @@ __device__ __forceinline__ float max16(float v) {
   v = fmaxf(v, BAMBOO_DPP(v, 0x124));
   return fmaxf(v, BAMBOO_DPP(v, 0x128));
 }
+// Pairs lanes 32 apart first, then 16, 8, 4, 2, 1 apart: the order, hence the bits, of a butterfly of __shfl_xor from 32 down.
 __device__ __forceinline__ float wave_sum(float v) {
-  v = sum16(v);
-  return (of_lane(v, 0) + of_lane(v, 16)) + (of_lane(v, 32) + of_lane(v, 48));
+  unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);      // (lower half twice, upper half twice)
+  const unsigned h0 = h[0], h1 = h[1];
+  v = __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1);
+  u = __builtin_bit_cast(unsigned, v);
+  const auto q = __builtin_amdgcn_permlane16_swap(u, u, false, false);      // (even rows of 16 twice, odd rows twice)
+  const unsigned q0 = q[0], q1 = q[1];
+  v = __builtin_bit_cast(float, q0) + __builtin_bit_cast(float, q1);
+  v += BAMBOO_DPP(v, 0x128);        // row_ror 8
+  v += BAMBOO_DPP(v, 0x124);        // row_ror 4: lanes 8 apart are alike by now
+  v += BAMBOO_DPP(v, 0x4e);         // quad_perm 2 3 0 1
+  return v + BAMBOO_DPP(v, 0xb1);   // quad_perm 1 0 3 2
 }
 __device__ __forceinline__ float wave_max(float v) {
   v = max16(v);
