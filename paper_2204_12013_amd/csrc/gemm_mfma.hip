@@ -142,7 +142,8 @@ __host__ __device__ __forceinline__ int k_slices(int K) { return (K + BK - 1) / 
 // The accumulators leave through a wavefront-private LDS staging area, one 32-row block of the
 // wave's sub-tile at a time; afterwards lane l owns, for pass `it`, the 8 consecutive outputs of
 // chunk idx = l + 64 * it of the staged 32 x (32 * WN) block (row idx / CHUNKS, columns
-// 8 * (idx % CHUNKS) ..).  What the epilogue has to read from memory for those outputs (residual,
+// 8 * (idx % CHUNKS) ..); fp32 outputs in chunks of 4, so that an access is 16 bytes a lane and
+// neighbouring lanes' accesses touch (see accumulate4).  What the epilogue has to read from memory for those outputs (residual,
 // stored activation derivative, fp32 gradient to add to) is known long before the accumulators are
 // final: EpiOperands::issue requests one row block's worth.  The kernel calls it for row block 0
 // ahead of the last slices of the main loop, so the latency is covered by MFMAs, and write_tile
@@ -184,31 +185,38 @@ struct EpiOperands {
       const int n = min(n0 + wn * 32 * WN + (idx % CHUNKS) * 8, d.N - 8);
       const long e = (long)m * d.N + n;
       if (BF) b[it] = *(const bf16x8*)((const bf16_t*)src + e);
-      if (F32) {      // a gradient is met again a layer stack later: past the caches (see epilogue8)
-        f[it][0] = __builtin_nontemporal_load((const f32x4*)((const float*)src + e));
-        f[it][1] = __builtin_nontemporal_load((const f32x4*)((const float*)src + e + 4));
+      if (F32) {      // a gradient is met again a layer stack later: past the caches (see accumulate4)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int q = lane + (2 * it + h) * 64;
+          const int mq = min(m0 + wm * 32 * WM + i * 32 + q / (2 * CHUNKS), d.M - 1);
+          const int nq = min(n0 + wn * 32 * WN + (q % (2 * CHUNKS)) * 4, d.N - 4);
+          f[it][h] = __builtin_nontemporal_load((const f32x4*)((const float*)src + (long)mq * d.N + nq));
+        }
       }
     }
   }
 };
 
-// epilogue on 8 consecutive outputs of one row; `pb` / `pf` are the operands fetched ahead
+// 4 consecutive fp32 outputs of one row, added to what was fetched ahead.  Read and written once per micro-batch,
+// hundreds of MB of other accesses apart: kept out of the caches it leaves them to the operands (GPT-2 stage
+// 65.1 -> 64.3 ms, both ends merged 17.65 -> 17.51).  With two such accesses 32 bytes apart a lane, as the bf16 forms'
+// chunks of 8 would have it, each touched every other 16 bytes of twice as many cache lines.  A layer's four weight
+// gradients in one launch, before -> after: 2048 tokens of 12288 x 49152 7590 -> 7195 us, 4096 of 1024 x 4096 107 -> 103,
+// 2048 of the same 68 -> 63.5, 1024 of 1600 x 6400 99 -> 93.5, 128 of the same 52.5 -> 48.2; 4096 of 1600 x 6400 alone
+// 274 -> 281 (in the whole stage level).  With plain loads, stores or both: 1-12 % slower but for the 12288-wide layer.
+__device__ __forceinline__ void accumulate4(const GemmDesc& d, int m, int n, const f32x4& acc, const f32x4& old) {
+  f32x4 v;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = old[j] + acc[j];
+  __builtin_nontemporal_store(v, (f32x4*)((float*)d.C + (long)m * d.N + n));
+}
+
+// epilogue on 8 consecutive bf16 outputs of one row; `pb` is the operand fetched ahead
 template <int EPI>
 __device__ __forceinline__ void epilogue8(const GemmDesc& d, int m, int n, const float (&acc)[8], const bf16x8& pb,
-                                          const f32x4 (&pf)[2], const bf16x8& pbias, unsigned gelu_tab,
-                                          float* stored = nullptr) {
+                                          const bf16x8& pbias, unsigned gelu_tab, float* stored = nullptr) {
   const long i = (long)m * d.N + n;
-  if (EPI == EPI_ACC_F32) {
-    float* c = (float*)d.C + i;
-    f32x4 a = pf[0], b = pf[1];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { a[j] += acc[j]; b[j] += acc[4 + j]; }
-    // read and written once per micro-batch, hundreds of MB of other accesses apart: kept out of the caches it leaves
-    // them to the operands (GPT-2 stage 65.1 -> 64.3 ms, both ends merged 17.65 -> 17.51)
-    __builtin_nontemporal_store(a, (f32x4*)c);
-    __builtin_nontemporal_store(b, (f32x4*)(c + 4));
-    return;
-  }
   float v[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) v[j] = acc[j];
@@ -282,7 +290,16 @@ __device__ __forceinline__ void write_tile(const GemmDesc& d, f32x16 (&acc)[WM][
     __builtin_amdgcn_wave_barrier();
     constexpr int CHUNKS = Ops::CHUNKS;   // 8-float chunks per staged row
 #pragma unroll
-    for (int it = 0; it < Ops::ITS; ++it) {
+    for (int it = 0; it < (Ops::F32 ? 2 * Ops::ITS : 0); ++it) {
+      const int idx = lane + it * 64;
+      const int row = idx / (2 * CHUNKS), ch = idx % (2 * CHUNKS);
+      const int m = m0 + wm * 32 * WM + i * 32 + row;
+      const int n = n0 + wn * 32 * WN + ch * 4;
+      const f32x4 v = *(const f32x4*)(stage + row * EPI_LD + ch * 4);
+      if (m < d.M && n < d.N) accumulate4(d, m, n, v, cur.f[it >> 1][it & 1]);
+    }
+#pragma unroll
+    for (int it = 0; it < (Ops::F32 ? 0 : Ops::ITS); ++it) {
       const int idx = lane + it * 64;
       const int row = idx / CHUNKS, ch = idx % CHUNKS;
       const int m = m0 + wm * 32 * WM + i * 32 + row;
@@ -293,13 +310,11 @@ __device__ __forceinline__ void write_tile(const GemmDesc& d, f32x16 (&acc)[WM][
         const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         if (CAN_SUM) {
           float st8[8];
-          epilogue8<EPI>(d, m, n, v, cur.b[Ops::BF ? it : 0], cur.f[Ops::F32 ? it : 0], first.bias[Ops::HASB ? it : 0],
-                         gelu_tab, st8);
+          epilogue8<EPI>(d, m, n, v, cur.b[Ops::BF ? it : 0], first.bias[Ops::HASB ? it : 0], gelu_tab, st8);
 #pragma unroll
           for (int j = 0; j < 8; ++j) cs[j] += st8[j];
         } else {
-          epilogue8<EPI>(d, m, n, v, cur.b[Ops::BF ? it : 0], cur.f[Ops::F32 ? it : 0], first.bias[Ops::HASB ? it : 0],
-                         gelu_tab);
+          epilogue8<EPI>(d, m, n, v, cur.b[Ops::BF ? it : 0], first.bias[Ops::HASB ? it : 0], gelu_tab);
         }
       }
     }
@@ -953,7 +968,7 @@ __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_kernel(GemmDesc d) {
 // With 256 x 256 tiles a remainder of up to 128 rows or columns at a matrix' edge is covered by 128 x 256 or 256 x 128
 // tiles (see edge_strips): a launch of 1600-wide matrices has 456 tiles and 76 strips instead of 532 tiles, i.e. two
 // rounds of the 256 CUs instead of three.  4096 tokens, 1600 x 6400 layers: 293 us as 128 x 256 tiles, 286 us like this,
-// 266 us with the gradients past the caches (see epilogue8): 133 us a round, 90 us of them main loop at the clock that
+// 266 us with the gradients past the caches (see accumulate4): 133 us a round, 90 us of them main loop at the clock that
 // 256 busy CUs leave, the rest fp32 reads and writes.
 template <int WM, int WN, int NS, int MINB>
 __global__ __launch_bounds__(256, MINB) void gemm_mfma_pl_group_kernel(GemmGroup g) {
@@ -1216,9 +1231,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_split_kernel(GemmDesc d) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) { v[j] += lo[j]; v[4 + j] += hi[j]; }
       }
-      const f32x4 none[2] = {};
       float st8[8];
-      epilogue8<EPI>(d, m, n, v, ops[q].pre, none, ops[q].bias, lds0 + SM::TABLE_OFF, SUMS ? st8 : nullptr);
+      epilogue8<EPI>(d, m, n, v, ops[q].pre, ops[q].bias, lds0 + SM::TABLE_OFF, SUMS ? st8 : nullptr);
       if (SUMS) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) cs[j] += st8[j];
