@@ -80,7 +80,7 @@ __device__ __forceinline__ void small_gemm(Frags f, const float* act, int lda, c
   const int lane = threadIdx.x & 63, i16 = lane & 15, kq = 4 * (lane >> 4);
   const int col = column_of(sh, n0, N);
   const Span sp = span_of(sh, K);
-  f32x4 acc[TT] = {};
+  f32x4 acc[TT][4] = {};        // every fourth k a sum of its own: short chains, and less rounding than one long one
   for (int s0 = sp.begin; s0 < sp.end; s0 += 4) {
     Frags next = f;
     if (s0 + 4 < sp.end) small_fetch<ROWS>(next, W, ldw, K, col, s0 + 4);
@@ -95,17 +95,18 @@ __device__ __forceinline__ void small_gemm(Frags f, const float* act, int lda, c
         f32x4 a = *(const f32x4*)(act + (t * 16 + i16) * lda + kc);
         a = kb < K ? a : zero;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc[t], 0, 0, 0);
+        for (int j = 0; j < 4; ++j) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc[t][j], 0, 0, 0);
       }
     }
     f = next;
   }
   // D[row][col]: lane holds col = lane % 16, rows 4 (lane / 16) .. + 3
 #pragma unroll
-  for (int t = 0; t < TT; ++t)
+  for (int t = 0; t < TT; ++t) {
+    const f32x4 v = (acc[t][0] + acc[t][1]) + (acc[t][2] + acc[t][3]);
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      part[(t * 16 + kq + r) * kPartLd + sh.part * sh.stride + sh.tile * 16 + i16] = acc[t][r];
+    for (int r = 0; r < 4; ++r) part[(t * 16 + kq + r) * kPartLd + sh.part * sh.stride + sh.tile * 16 + i16] = v[r];
+  }
 }
 
 // out(row, column, value, in(row, column)) once per output element of act W: a wavefront takes every 16th row, a lane
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(kThreads) void small_fwd_kernel(SmallLayers a) {
   }
 }
 
-// Column sums over the sample's rows, in row order: out[c] = sum of x[row][c] (times y[row][c])
+// Column sums over the sample's rows: out[c] = sum of x[row][c] (times y[row][c]), every fourth row in a sum of its own
 struct Sum { const float *x, *y; float* out; int ld, N; };
 // up to three of them, by threads 0 .., 256 .. and 512 .. of the workgroup
 __device__ __forceinline__ void small_colsums(const Sum (&s)[3], int S) {
@@ -358,13 +359,17 @@ __device__ __forceinline__ void small_colsums(const Sum (&s)[3], int S) {
     if (s[q].out == nullptr) continue;              // uniform
 #pragma unroll 1
     for (int c = ((int)threadIdx.x - 256 * q) & (kThreads - 1); c < s[q].N; c += kThreads) {
-      float t = 0.f;
-#pragma unroll 4
-      for (int row = 0; row < S; ++row) {
-        const float x = s[q].x[row * s[q].ld + c];
-        t += s[q].y != nullptr ? x * s[q].y[row * s[q].ld + c] : x;
+      float t[4] = {};
+#pragma unroll 1
+      for (int row = 0; row < S; row += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int at = min(row + u, S - 1) * s[q].ld + c;
+          const float x = s[q].x[at], v = s[q].y != nullptr ? x * s[q].y[at] : x;
+          t[u] += row + u < S ? v : 0.f;
+        }
       }
-      s[q].out[c] = t;
+      s[q].out[c] = (t[0] + t[1]) + (t[2] + t[3]);
     }
   }
 }
@@ -549,11 +554,13 @@ static int bwd_lds_bytes(int S, int H, int F) {
 // A wavefront holds a row of a LayerNorm in one register and half of one the keys of a query; beyond that the line lies
 // where a CU per sample stops being faster than the chip per step.  An iteration of 4 micro-batches, steps launched one by
 // one / this, us (samples x tokens, H, F, layers own + replica, multiply-adds a sample and layer):
-//   2 x 16,  64, 256, 1 + 1 (0.8 M)   506 / 283      4 x 32,  64, 256, 2 + 3 (1.6 M)    996 / 729
+//   2 x 16,  64, 256, 1 + 1 (0.8 M)   506 / 283      4 x 32,  64, 256, 2 + 3 (1.6 M)    996 / 762
 //   1 x  8,  32, 128, 1 + 1 (0.1 M)   511 / 227      4 x 32,  32, 128, 2 + 2 (0.4 M)    879 / 569
 //   2 x 16,  96, 384, 2 + 2 (1.8 M)   843 / 1026     4 x 16, 128, 512, 1 + 1 (3.1 M)    515 / 458
 //   1 x  8, 128, 512, 3 + 3 (1.6 M)  1137 / 1080     2 x 16, 128, 1024, 1 + 1 (5.2 M)   536 / 601
-// The forward of the first is one launch of 22 us, the backward 29 us and the weight gradients.
+// The forward of the first is one launch of 22 us, the backward 29 us and the weight gradients.  Sums split four ways
+// (small_gemm, small_colsums) cost 1 % at 16 tokens a sample and 5 % at 32 over one sum each, with which weight gradients
+// were 1.3 and bias gradients up to 1.9 times as far from 64 bits as the single kernels' (1.5e-7, 1.6e-7), now 1.04 and 1.0.
 bool small_layers_fit(int B, int S, int H, int heads, int F, const void* w) {
   const long macs = (long)S * (4L * H * H + 2L * H * F);
   return S <= 32 && H <= 64 && (H / heads) % 4 == 0 && ((uintptr_t)w & 15) == 0 && macs <= 2000000 &&
