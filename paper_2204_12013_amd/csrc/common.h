@@ -45,13 +45,16 @@ __device__ __forceinline__ float max16(float v) {
   v = fmaxf(v, BAMBOO_DPP(v, 0x124));
   return fmaxf(v, BAMBOO_DPP(v, 0x128));
 }
-// Pairs lanes 32 apart first, then 16, 8, 4, 2, 1 apart: the order, hence the bits, of a butterfly of __shfl_xor from 32 down.
-__device__ __forceinline__ float wave_sum(float v) {
-  unsigned u = __builtin_bit_cast(unsigned, v);
+// the value of the lane 32 places on or back
+__device__ __forceinline__ float lane_across(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
   const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);      // (lower half twice, upper half twice)
-  const unsigned h0 = h[0], h1 = h[1];
-  v = __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1);
-  u = __builtin_bit_cast(unsigned, v);
+  const unsigned lo = h[0], hi = h[1];
+  return __builtin_bit_cast(float, (threadIdx.x & 32) ? lo : hi);
+}
+// sums over the lanes of a half, pairs 16, 8, 4, 2, 1 apart
+__device__ __forceinline__ float sum32(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
   const auto q = __builtin_amdgcn_permlane16_swap(u, u, false, false);      // (even rows of 16 twice, odd rows twice)
   const unsigned q0 = q[0], q1 = q[1];
   v = __builtin_bit_cast(float, q0) + __builtin_bit_cast(float, q1);
@@ -60,6 +63,18 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += BAMBOO_DPP(v, 0x4e);         // quad_perm 2 3 0 1
   return v + BAMBOO_DPP(v, 0xb1);   // quad_perm 1 0 3 2
 }
+// Pairs lanes 32 apart first, then 16, 8, 4, 2, 1 apart: the order of a butterfly of __shfl_xor from 32 down, and its bits
+// where v is not a product: the compiler makes one instruction of a product and the addition that follows it, which it
+// cannot here.  wave_sum_of_products says so itself.
+__device__ __forceinline__ float wave_sum(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const unsigned h0 = h[0], h1 = h[1];
+  return sum32(__builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1));
+}
+// Sum of a * b.  A lane's own product enters the first addition unrounded, so the two halves of the wavefront can end a bit
+// apart; lanes 0 to 31 agree.
+__device__ __forceinline__ float wave_sum_of_products(float a, float b) { return sum32(fmaf(a, b, lane_across(a * b))); }
 __device__ __forceinline__ float wave_max(float v) {
   v = max16(v);
   return fmaxf(fmaxf(of_lane(v, 0), of_lane(v, 16)), fmaxf(of_lane(v, 32), of_lane(v, 48)));

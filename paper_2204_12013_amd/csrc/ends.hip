@@ -138,8 +138,9 @@ __device__ __forceinline__ float block_max(float v, float* red) {
   __syncthreads();
   return v;
 }
-__device__ __forceinline__ float block_sum(float v, float* red) {
-  v = wave_sum(v);
+// sum of a * b
+__device__ __forceinline__ float block_sum(float a, float b, float* red) {
+  float v = wave_sum_of_products(a, b);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   v = (red[0] + red[1]) + (red[2] + red[3]);
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(256) void xent_fwd_kernel(int V, const T* __restric
     }
   }
   const float top = block_max(m, red);
-  s = block_sum(s * expf(m - top), red);            // m = -inf: s (0 or NaN) times 0; NaN where the whole row is -inf
+  s = block_sum(s, expf(m - top), red);             // m = -inf: s (0 or NaN) times 0; NaN where the whole row is -inf
   if (threadIdx.x == 0) {
     const float l = top + logf(s);
     lse[t] = l;

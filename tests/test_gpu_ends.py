@@ -211,3 +211,26 @@ def test_softmax_cross_entropy_of_rows_without_a_finite_value_or_with_nan(B, dty
     B.bk_softmax_xent_fwd(x, _dev_ids([1] * 6), got, tok)
     assert bool(torch.isfinite(got[0])) and bool(torch.isfinite(tok[0]))
     assert bool(torch.isnan(got[1:]).all()) and bool(torch.isnan(tok[1:]).all())
+
+
+def test_log_sum_exp_adds_a_lanes_product_unrounded(B):
+    """A thread's sum is brought to the row's maximum by a product, which enters the first addition (of lanes 32 apart)
+    unrounded.  Half an ulp of a sum of exponentials, but bf16 gradients behind it round the other way.  Rows of one 0 (lane
+    32) and three equal negative values (lane 0): the sum is 1 + 3 e, to one rounding or two; where these differ the loss
+    has to be the one's.  With a sum of 1.3 to 1.6 they are 1.2e-7 apart, their logarithms 0.7e-7 at least; logf is
+    off by two ulps of up to 3e-8, so a few rows may look like the other's."""
+    T, V = 4000, 512
+    x = torch.full((T, V), -float("inf"), device=DEV)
+    x[:, 32 * 8] = 0.0
+    m = torch.log(torch.linspace(0.1, 0.2, T, device=DEV))
+    x[:, :3] = m[:, None]
+    got, tok = torch.empty(T, device=DEV), torch.empty(T, device=DEV)
+    B.bk_softmax_xent_fwd(x, _dev_ids([256] * T), got, tok)
+    e = torch.empty(T, 8, device=DEV)                    # the library's own exponentials: exp(x - 0), minus 1 at the label
+    B.bk_softmax_xent_bwd(m[:, None].repeat(1, 8), _dev_ids([7] * T), torch.zeros(T, device=DEV), 1.0, e)
+    p = 3.0 * e[:, 0].double()
+    once, twice = (1.0 + p).float(), (1.0 + p.float().double()).float()
+    differ = once != twice
+    assert differ.sum() > 200
+    to_once, to_twice = ((got.double() - torch.log(s.double())).abs()[differ] for s in (once, twice))
+    assert (to_once < to_twice).double().mean() > 0.9
