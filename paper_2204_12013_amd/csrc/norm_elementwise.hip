@@ -48,6 +48,14 @@ template <> struct Vec<bf16_t> {
   }
 };
 
+// The compiler is not to carry what it has unpacked from a raw vector on to its next use.
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+template <typename RAW>
+__device__ __forceinline__ RAW keep_raw(const RAW& v) {
+  u32x4 t = __builtin_bit_cast(u32x4, v);
+  asm volatile("" : "+v"(t));
+  return __builtin_bit_cast(RAW, t);
+}
 constexpr int kMaxPartials = 256;   // workgroups contributing partial column sums
 
 // ------------------------------------------------------------ LayerNorm forward
@@ -149,71 +157,57 @@ __global__ __launch_bounds__(256) void layernorm_fwd_long_kernel(int T_rows, int
   }
 }
 
-// Rows too long for a wavefront: a workgroup of eight takes a row, NC vectors a thread, and reads it once.  2048 rows of
-// 12288, launch to launch: 39 -> 22 us (before: a wavefront per row and three passes over it).
-constexpr int kWideThreads = 512;
-// sums of two values over the workgroup, for every thread; `red`: 16 floats that the next call does not use
-__device__ __forceinline__ void wide_sums(float& a, float& b, float* red) {
-  const int w = threadIdx.x >> 6;
-  a = wave_sum(a);
-  b = wave_sum(b);
-  if ((threadIdx.x & 63) == 0) {
-    red[w] = a;
-    red[8 + w] = b;
-  }
-  __syncthreads();
-  a = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
-  b = ((red[8] + red[9]) + (red[10] + red[11])) + ((red[12] + red[13]) + (red[14] + red[15]));
-}
-template <typename T, int NC>
-__global__ __launch_bounds__(kWideThreads) void layernorm_fwd_wide_kernel(int H, float eps, const T* __restrict__ r,
-                                                                          const T* __restrict__ gamma,
-                                                                          const T* __restrict__ beta, T* __restrict__ y,
-                                                                          float* __restrict__ stats) {
+// Rows of more than 8 vectors a lane: read once and held as they came, unpacked again for each use.  The sums take the order
+// of the kernel above, to the bit.  Bound by the trip to memory and, for few rows, by the chain of additions a lane makes.
+// bf16, three passes / this: 2048 rows of 12288 34.1 / 22.0 us, of 4104 11.5 / 10.1, 128 rows of 12288 15.8 / 11.6.  (Eight
+// wavefronts a row took 16.5, 8.9 and 3.9, but sum in another order.)  Up to 32 vectors a lane: 249 registers of the 256 that
+// two wavefronts per SIMD leave each.
+template <typename T, int NCH>
+__global__ __launch_bounds__(256) void layernorm_fwd_held_kernel(int T_rows, int H, float eps, const T* __restrict__ r,
+                                                                 const T* __restrict__ gamma,
+                                                                 const T* __restrict__ beta, T* __restrict__ y,
+                                                                 float* __restrict__ stats) {
   constexpr int V = Vec<T>::N;
-  __shared__ float red[2][16];
-  const long row = blockIdx.x, off = row * H;
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= T_rows) return;
+  const T* rr = r + (long)row * H;
   const int nvec = H / V;
-  typename Vec<T>::Raw raw[NC], graw[NC], braw[NC];
-  int cc[NC];
+  typename Vec<T>::Raw raw[NCH];
 #pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    cc[j] = min((int)threadIdx.x + kWideThreads * j, nvec - 1) * V;
-    raw[j] = Vec<T>::load_raw(r + off + cc[j]);
+  for (int j = 0; j < NCH; ++j) raw[j] = Vec<T>::load_raw(rr + min(lane + 64 * j, nvec - 1) * V);
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < NCH; ++j) {
+    float v[V];
+    Vec<T>::unpack(raw[j], v);
+    if (lane + 64 * j < nvec)
+#pragma unroll
+      for (int i = 0; i < V; ++i) s += v[i];
   }
+  const float mean = wave_sum(s) / (float)H;
+  float q = 0.f;
 #pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    graw[j] = Vec<T>::load_raw(gamma + cc[j]);
-    braw[j] = Vec<T>::load_raw(beta + cc[j]);
+  for (int j = 0; j < NCH; ++j) {
+    float v[V];
+    Vec<T>::unpack(keep_raw(raw[j]), v);
+    if (lane + 64 * j < nvec)
+#pragma unroll
+      for (int i = 0; i < V; ++i) q = fmaf(v[i] - mean, v[i] - mean, q);
   }
-  float v[NC][V], s = 0.f, q = 0.f, none = 0.f;
+  const float rstd = rsqrtf(wave_sum(q) / (float)H + eps);
 #pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    Vec<T>::unpack(raw[j], v[j]);
-    if ((int)threadIdx.x + kWideThreads * j < nvec)
+  for (int j = 0; j < NCH; ++j) {
+    const int c = min(lane + 64 * j, nvec - 1) * V;
+    float v[V], g[V], b[V], o[V];
+    Vec<T>::unpack(keep_raw(raw[j]), v);
+    Vec<T>::load(gamma + c, g);
+    Vec<T>::load(beta + c, b);
 #pragma unroll
-      for (int i = 0; i < V; ++i) s += v[j][i];
+    for (int i = 0; i < V; ++i) o[i] = g[i] * ((v[i] - mean) * rstd) + b[i];
+    if (lane + 64 * j < nvec) Vec<T>::store(y + (long)row * H + c, o);
   }
-  wide_sums(s, none, red[0]);
-  const float mean = s / (float)H;
-#pragma unroll
-  for (int j = 0; j < NC; ++j)
-    if ((int)threadIdx.x + kWideThreads * j < nvec)
-#pragma unroll
-      for (int i = 0; i < V; ++i) q += (v[j][i] - mean) * (v[j][i] - mean);
-  none = 0.f;
-  wide_sums(q, none, red[1]);
-  const float rstd = rsqrtf(q / (float)H + eps);
-#pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    float g[V], b[V], o[V];
-    Vec<T>::unpack(graw[j], g);
-    Vec<T>::unpack(braw[j], b);
-#pragma unroll
-    for (int i = 0; i < V; ++i) o[i] = g[i] * ((v[j][i] - mean) * rstd) + b[i];
-    if ((int)threadIdx.x + kWideThreads * j < nvec) Vec<T>::store(y + off + cc[j], o);
-  }
-  if (threadIdx.x == 0) {
+  if (lane == 0) {
     stats[2 * row] = mean;
     stats[2 * row + 1] = rstd;
   }
@@ -232,14 +226,10 @@ static hipError_t ln_fwd_impl(hipStream_t s, int T_rows, int H, float eps, const
   else if (nch <= 2) LN_FWD((layernorm_fwd_kernel<T, 2>));
   else if (nch <= 4) LN_FWD((layernorm_fwd_kernel<T, 4>));
   else if (nch <= 8) LN_FWD((layernorm_fwd_kernel<T, 8>));
-  else if (nch > 32) LN_FWD(layernorm_fwd_long_kernel<T>);
-#undef LN_FWD
-#define LN_FWD(NC)                                                                                              \
-  hipLaunchKernelGGL((layernorm_fwd_wide_kernel<T, NC>), dim3(T_rows), dim3(kWideThreads), 0, s, H, eps,         \
-                     (const T*)r, (const T*)gamma, (const T*)beta, (T*)y, stats)
-  else if (nch <= 16) LN_FWD(2);
-  else if (nch <= 24) LN_FWD(3);
-  else LN_FWD(4);
+  else if (nch <= 16) LN_FWD((layernorm_fwd_held_kernel<T, 16>));
+  else if (nch <= 24) LN_FWD((layernorm_fwd_held_kernel<T, 24>));
+  else if (nch <= 32) LN_FWD((layernorm_fwd_held_kernel<T, 32>));
+  else LN_FWD(layernorm_fwd_long_kernel<T>);
 #undef LN_FWD
   return hipGetLastError();
 }
@@ -261,14 +251,6 @@ hipError_t launch_layernorm_fwd(hipStream_t s, int dtype, int T, int H, float ep
 // Launch to launch with cold operands: 4096 rows of 1024 12.0 -> 9.0 us, of 1600 with the residual 18.3 -> 15.5, 999 of 1024
 // 7.5 -> 5.3, 128 of 1024 6.2 -> 4.4 (before: four wavefronts, two rows per pass, 4-byte accesses in the reductions).  A
 // third of what is left is the launch and the first trip to memory, a fifth the reductions over the wavefronts.
-// the compiler is not to carry what it has unpacked from a raw vector on to its next use
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-template <typename RAW>
-__device__ __forceinline__ RAW keep_raw(const RAW& v) {
-  u32x4 t = __builtin_bit_cast(u32x4, v);
-  asm volatile("" : "+v"(t));
-  return __builtin_bit_cast(RAW, t);
-}
 template <typename T, int NCH, bool ADD, bool COLSUM, int U>
 __global__ __launch_bounds__(512) void layernorm_bwd_fused_kernel(int T_rows, int H, int rows_per_block,
                                                                   const T* __restrict__ dout, const T* __restrict__ r,
@@ -399,9 +381,14 @@ __global__ __launch_bounds__(512) void layernorm_bwd_fused_kernel(int T_rows, in
   }
 }
 
-// The same for rows too long for a wavefront: a workgroup works through its rows one after the other, the next one on its
-// way meanwhile, a thread keeping its columns' sums.  2048 rows of 12288, with the residual and the column sums: 97 -> 51 us
-// (before: column sums, gradient and its column sums as three launches).
+// The same for rows too long for a wavefront to keep their columns' sums: up to eight rows at a time, first a wavefront each
+// for the two sums over a row, in the order of layernorm_bwd_kernel, hence its bits in dr; then one after the other by the
+// whole workgroup, a thread keeping its columns' sums, the next row on its way meanwhile.  From 5 vectors a lane, where the
+// columns' sums outgrow a wavefront's registers, to 24: 244 of 256 registers at three vectors a thread, with the residual and
+// the column sums.  bf16 without either, two launches / this: 2048 rows of 12288 63.5 / 46.0 us, of 3072 22.7 / 16.5, 128 rows of
+// 12288 26.0 / 19.2; at 16384 the launches take 104.  (With the two sums over a row formed by the whole workgroup 34.0, 15.6 and
+// 14.9, in another order.)
+constexpr int kWideThreads = 512;
 template <typename T, int NC, bool ADD, bool COLSUM>
 __global__ __launch_bounds__(kWideThreads) void layernorm_bwd_wide_kernel(int T_rows, int H, int rows_per_block,
                                                                           const T* __restrict__ dout,
@@ -413,8 +400,8 @@ __global__ __launch_bounds__(kWideThreads) void layernorm_bwd_wide_kernel(int T_
                                                                           float* __restrict__ pc) {
   constexpr int V = Vec<T>::N;
   typedef typename Vec<T>::Raw Raw;
-  __shared__ float red[2][16];
-  const int nvec = H / V;
+  __shared__ float means[2][8];
+  const int nvec = H / V, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   float ag[NC][V] = {}, ab[NC][V] = {}, ac[COLSUM ? NC : 1][V] = {};
   Raw graw[NC], dw[NC], xw[NC], aw[ADD ? NC : 1], dn[NC], xn[NC], an[ADD ? NC : 1];
   int cc[NC];
@@ -436,51 +423,79 @@ __global__ __launch_bounds__(kWideThreads) void layernorm_bwd_wide_kernel(int T_
     if (c >= nvec) graw[j] = Raw{};
   }
   fetch(first, dw, xw, aw);
-  for (int row = first; row < row_end; ++row) {
-    const float mean = stats[2 * row], rstd = stats[2 * row + 1];
-    fetch(min(row + 1, row_end - 1), dn, xn, an);
-    float s1 = 0.f, s2 = 0.f;
+  for (int row0 = first; row0 < row_end; row0 += 8) {
+    if (row0 + wave < row_end) {
+      const long off = (long)(row0 + wave) * H;
+      const float mean = stats[2 * (row0 + wave)], rstd = stats[2 * (row0 + wave) + 1];
+      constexpr int A = NC < 3 ? 8 : 6;        // vectors of each requested together
+      float s1 = 0.f, s2 = 0.f;
+#pragma unroll 1
+      for (int c0 = 0; c0 < nvec; c0 += 64 * A) {
+        Raw d8[A], x8[A], g8[A];
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
-      float d[V], x[V], g[V];
-      Vec<T>::unpack(dw[j], d);
-      Vec<T>::unpack(xw[j], x);
-      Vec<T>::unpack(graw[j], g);
+        for (int u = 0; u < A; ++u) {
+          const int c = min(c0 + 64 * u + lane, nvec - 1) * V;
+          d8[u] = Vec<T>::load_raw(dout + off + c);
+          x8[u] = Vec<T>::load_raw(r + off + c);
+          g8[u] = Vec<T>::load_raw(gamma + c);
+        }
 #pragma unroll
-      for (int i = 0; i < V; ++i) {
-        x[i] = (x[i] - mean) * rstd;
-        ag[j][i] += d[i] * x[i];
-        ab[j][i] += d[i];
-        d[i] *= g[i];
-        s1 += d[i];
-        s2 += d[i] * x[i];
+        for (int u = 0; u < A; ++u) {
+          float d[V], x[V], g[V];
+          Vec<T>::unpack(d8[u], d);
+          Vec<T>::unpack(x8[u], x);
+          Vec<T>::unpack(g8[u], g);
+          if (c0 + 64 * u + lane < nvec)
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+              s1 = fmaf(d[i], g[i], s1);
+              s2 = fmaf(d[i] * g[i], (x[i] - mean) * rstd, s2);
+            }
+        }
+      }
+      s1 = wave_sum(s1) / (float)H;
+      s2 = wave_sum(s2) / (float)H;
+      if (lane == 0) {
+        means[0][wave] = s1;
+        means[1][wave] = s2;
       }
     }
-    wide_sums(s1, s2, red[(row - first) & 1]);
-    const float m1 = s1 / (float)H, m2 = s2 / (float)H;
+    __syncthreads();
+    for (int row = row0; row < min(row0 + 8, row_end); ++row) {
+      const float mean = stats[2 * row], rstd = stats[2 * row + 1];
+      const float m1 = means[0][row - row0], m2 = means[1][row - row0];
+      fetch(min(row + 1, row_end - 1), dn, xn, an);
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
-      float o[V], d[V], x[V], g[V];
-      Vec<T>::unpack(keep_raw(dw[j]), d);
-      Vec<T>::unpack(keep_raw(xw[j]), x);
-      Vec<T>::unpack(keep_raw(graw[j]), g);
+      for (int j = 0; j < NC; ++j) {
+        float o[V], d[V], x[V], g[V];
+        Vec<T>::unpack(dw[j], d);
+        Vec<T>::unpack(xw[j], x);
+        Vec<T>::unpack(graw[j], g);
 #pragma unroll
-      for (int i = 0; i < V; ++i) o[i] = (d[i] * g[i] - m1 - (x[i] - mean) * rstd * m2) * rstd;
-      if (ADD) {
-        float a[V];
-        Vec<T>::unpack(aw[j], a);
+        for (int i = 0; i < V; ++i) {
+          const float xh = (x[i] - mean) * rstd;
+          ag[j][i] = fmaf(d[i], xh, ag[j][i]);
+          ab[j][i] += d[i];
+          o[i] = fmaf(-xh, m2, fmaf(d[i], g[i], -m1)) * rstd;
+        }
+        if (ADD) {
+#pragma clang fp contract(off)        // two roundings, as in layernorm_bwd_kernel, where the addition is a branch of its own
+          float a[V];
+          Vec<T>::unpack(aw[j], a);
 #pragma unroll
-        for (int i = 0; i < V; ++i) o[i] += a[i];
+          for (int i = 0; i < V; ++i) o[i] += a[i];
+        }
+        if (COLSUM) {
+#pragma unroll
+          for (int i = 0; i < V; ++i) ac[j][i] += round_storage<T>(o[i]);
+        }
+        if ((int)threadIdx.x + kWideThreads * j < nvec) Vec<T>::store(dr + (long)row * H + cc[j], o);
+        dw[j] = dn[j];
+        xw[j] = xn[j];
+        if (ADD) aw[j] = an[j];
       }
-      if (COLSUM) {
-#pragma unroll
-        for (int i = 0; i < V; ++i) ac[j][i] += round_storage<T>(o[i]);
-      }
-      if ((int)threadIdx.x + kWideThreads * j < nvec) Vec<T>::store(dr + (long)row * H + cc[j], o);
-      dw[j] = dn[j];
-      xw[j] = xn[j];
-      if (ADD) aw[j] = an[j];
     }
+    __syncthreads();                           // the means have been read
   }
 #pragma unroll
   for (int j = 0; j < NC; ++j)

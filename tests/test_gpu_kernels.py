@@ -330,6 +330,53 @@ def test_layernorm_at_the_edges_of_its_kernels(B, dtype, T, H):
     test_layernorm_forward_backward(B, dtype, T, H)
 
 
+def _fma(a, b, c):
+    """One rounding, as the device's fma (fp64 holds the product of two fp32 values exactly)."""
+    return (a.double() * b.double() + c.double()).float()
+
+
+def _wavefront_sum(step, H, V, T):
+    """A wavefront's sum over a row: lane l takes vectors l, l + 64, .. in order, then pairs 32, 16, .. 1 lanes apart.
+    step(s, e): s with element e [T, lanes] of a lane's vector added; e indexes the columns, at least one lane's."""
+    s = torch.zeros(T, 64, device=DEV)
+    cols = torch.arange(H, device=DEV).view(H // V, V)
+    for k in range(0, H // V, 64):
+        c = cols[k:k + 64]
+        for i in range(V):
+            s[:, :len(c)] = step(s[:, :len(c)], c[:, i])
+    for o in (32, 16, 8, 4, 2, 1):
+        s = s[:, :o] + s[:, o:]
+    return s[:, 0]
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("T,H", [(3, 1032), (9, 2056), (300, 2056), (17, 4104), (3, 8192), (2, 12288), (2, 16384)])
+def test_layernorm_sums_a_row_in_the_order_of_a_wavefront(B, dtype, T, H):
+    """Whatever kernel takes a row (a wavefront, or a workgroup for several): mean, rstd and dr to the bit as single
+    operations in that order give them, since everything behind a LayerNorm is rounded to bf16."""
+    rng = np.random.default_rng(H + T)
+    V = 8 if dtype else 4
+    mk = lambda s: B.to_device(synth.round_to_storage(s, dtype), dtype)
+    r, d = mk(rng.normal(0.3, 1, (T, H))), mk(rng.normal(0, 1, (T, H)))
+    gamma, beta = mk(rng.normal(1, 0.1, H)), mk(rng.normal(0, 0.1, H))
+    y, stats, dr = torch.empty_like(r), torch.empty(T, 2, device=DEV), torch.empty_like(r)
+    dg, db = torch.zeros(H, device=DEV), torch.zeros(H, device=DEV)
+    B.bk_layernorm_fwd(r, gamma, beta, y, stats)
+    B.bk_layernorm_bwd(d, r, stats, gamma, dr, dg, db)
+    x, df, g = r.float(), d.float(), gamma.float()
+    n = torch.tensor(float(H), device=DEV)
+    mean = _wavefront_sum(lambda s, c: s + x[:, c], H, V, T) / n
+    assert torch.equal(stats[:, 0], mean)
+    m, rs = stats[:, :1], stats[:, 1:]
+    var = _wavefront_sum(lambda s, c: _fma(x[:, c] - m, x[:, c] - m, s), H, V, T) / n
+    assert (stats[:, 1].double() * (var.double() + 1e-5).sqrt() - 1).abs().max() < 2.0 ** -22      # rsqrt: an ulp or so
+    dh, xh = df * g, (x - m) * rs
+    m1 = _wavefront_sum(lambda s, c: _fma(df[:, c], g[c], s), H, V, T) / n
+    m2 = _wavefront_sum(lambda s, c: _fma(dh[:, c], xh[:, c], s), H, V, T) / n
+    want = _fma(-xh, m2[:, None], _fma(df, g, -m1[:, None])) * rs
+    assert torch.equal(dr, want.to(dr.dtype))
+
+
 def test_mfma_attention_refuses_sequences_beyond_its_32_bit_tile_offsets(B):
     # the MFMA kernels address a (batch, head) slice of qkv with 32-bit byte offsets: a sequence whose rows span
     # 4 GiB or more is refused when the kernels are forced, nothing is launched
