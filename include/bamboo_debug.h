@@ -21,8 +21,9 @@ extern "C" {
 /* Per-launch-site timing for roofline measurements.  stage_profile(st, 1) clears earlier records and
  * brackets every later kernel launch with a HIP event pair on the launch's own stream;
  * stage_profile(st, 0) stops.  stage_profile_read synchronises, then reports for one site the summed
- * launch durations in ms, the number of launches and the summed algorithmic work (flops for GEMM and
- * attention sites, bytes for the others).  The GEMM sites are the call sites of one layer pass, so
+ * launch durations in ms, the number of launches and the summed algorithmic work (flops for GEMM,
+ * attention and whole-layer sites, bytes for the others).  The launches are those of a stage that is not timed,
+ * and so are the results.  The GEMM sites are the call sites of one layer pass, so
  * that a report can name the single launch that dominates. */
 enum bamboo_kernel_class {
   BAMBOO_K_GEMM_QKV = 0,        /* qkv = ain Wqkv + bqkv */
@@ -39,10 +40,18 @@ enum bamboo_kernel_class {
   BAMBOO_K_LN_FWD = 11,
   BAMBOO_K_LN_BWD = 12,
   BAMBOO_K_COLSUM = 13,
-  BAMBOO_K_COUNT = 14
+  BAMBOO_K_SMALL_FWD = 14,      /* fp32 layers of a few tokens: the forward of a stack in one launch */
+  BAMBOO_K_SMALL_BWD = 15,      /* the same: the input-gradient chain of one layer in one launch */
+  BAMBOO_K_COUNT = 16
 };
 int stage_profile(bamboo_stage_t* st, int enable);
 int stage_profile_read(bamboo_stage_t* st, int32_t kernel_class, double* total_ms, int64_t* launches, double* work);
+
+/* enable != 0: this stage's later forwards and backwards launch every step of a layer by itself, also where a
+ * configuration's layers would go through the kernels that take a sample through them in one launch
+ * (BAMBOO_K_SMALL_FWD, BAMBOO_K_SMALL_BWD).  Sums are then taken in another order, so results differ by rounding: for
+ * comparisons of the two, never for one stage of a pipeline alone. */
+int stage_single_launches(bamboo_stage_t* st, int enable);
 
 /* Byte offsets, inside the workspace passed to stage_init, of the lane-0 buffers a backward pass
  * leaves its intermediate gradients in (storage dtype, row-major), so that a test can read them

@@ -24,7 +24,8 @@ OK, E_BADCFG, E_BADMB, E_STATE, E_HIP, E_ARG, E_NOMEM = 0, -1, -2, -3, -4, -5, -
 (RECV_ACT, SEND_ACT, RECV_GRAD, SEND_GRAD, FWD, BWD, FRC, BRC, BUBBLE, JOIN, ALLREDUCE, APPLY) = range(12)
 # launch sites of the per-site timing (enum bamboo_kernel_class in bamboo_debug.h)
 KERNEL_CLASSES = ("gemm_qkv", "gemm_attn_out", "gemm_ffn1", "gemm_ffn2", "dgrad_ffn2", "dgrad_ffn1", "dgrad_attn_out",
-                  "dgrad_qkv", "wgrad_group", "attn_fwd", "attn_bwd", "ln_fwd", "ln_bwd", "colsum")
+                  "dgrad_qkv", "wgrad_group", "attn_fwd", "attn_bwd", "ln_fwd", "ln_bwd", "colsum",
+                  "small_fwd", "small_bwd")
 
 
 class Cfg(C.Structure):
@@ -103,6 +104,7 @@ _SIGS = {
     "stage_sync": (C.c_int, [_vp]),
     "stage_destroy": (C.c_int, [_vp]),
     "stage_profile": (C.c_int, [_vp, C.c_int]),
+    "stage_single_launches": (C.c_int, [_vp, C.c_int]),
     "stage_profile_read": (C.c_int, [_vp, _i32, C.POINTER(C.c_double), C.POINTER(_i64), C.POINTER(C.c_double)]),
     "ends_query_sizes": (C.c_int, [_cfgp, _i32, C.POINTER(EndsSizes)]),
     "ends_init": (C.c_int, [_cfgp, _i32, C.POINTER(EndsSizes)] + [_vp] * 7 + [C.POINTER(_vp)]),
@@ -419,6 +421,9 @@ class Stage:
 
     def stage_profile(self, enable):
         _check(lib.stage_profile(self._h, int(enable)), "stage_profile")
+
+    def stage_single_launches(self, enable):
+        _check(lib.stage_single_launches(self._h, int(enable)), "stage_single_launches")
 
     def stage_profile_read(self, kernel_class):
         """(total ms, launches, algorithmic work) of one kernel class."""

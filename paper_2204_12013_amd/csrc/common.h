@@ -271,7 +271,7 @@ struct SmallBackward {
   float *dh, *d1, *d2, *d3, *dctx, *dqkv;
   float *p_ln[2][3], *p_dh, *p_dqkv, *p_df;
 };
-bool small_layers_fit(int B, int S, int H, int heads, int F, const void* w);
+bool small_layers_fit(int B, int S, int H, int heads, int F);
 hipError_t launch_small_fwd(hipStream_t s, int B, const SmallLayers& a);
 hipError_t launch_small_bwd(hipStream_t s, int B, const SmallLayers& a, const SmallBackward& b);
 

@@ -561,9 +561,9 @@ static int bwd_lds_bytes(int S, int H, int F) {
 // The forward of the first is one launch of 22 us, the backward 29 us and the weight gradients.  Sums split four ways
 // (small_gemm, small_colsums) cost 1 % at 16 tokens a sample and 5 % at 32 over one sum each, with which weight gradients
 // were 1.3 and bias gradients up to 1.9 times as far from 64 bits as the single kernels' (1.5e-7, 1.6e-7), now 1.04 and 1.0.
-bool small_layers_fit(int B, int S, int H, int heads, int F, const void* w) {
+bool small_layers_fit(int B, int S, int H, int heads, int F) {
   const long macs = (long)S * (4L * H * H + 2L * H * F);
-  return S <= 32 && H <= 64 && (H / heads) % 4 == 0 && ((uintptr_t)w & 15) == 0 && macs <= 2000000 &&
+  return S <= 32 && H <= 64 && (H / heads) % 4 == 0 && macs <= 2000000 &&
          (size_t)B <= reduce_max_partials() && bwd_lds_bytes(S, H, F) <= 160 * 1024;
 }
 

@@ -203,6 +203,7 @@ struct bamboo_stage {
   hipEvent_t ev_swap_join;
   // optional per-kernel-class timing: an event pair around every launch
   bool prof_on;
+  bool single_launches;                // stage_single_launches
   struct ProfRec { int cls; double work; hipEvent_t a, b; };
   std::vector<ProfRec> prof_recs;
   std::vector<hipEvent_t> prof_pool;
@@ -264,7 +265,8 @@ enum KernelClass {
   K_GEMM_FFN2 = BAMBOO_K_GEMM_FFN2, K_DGRAD_FFN2 = BAMBOO_K_DGRAD_FFN2, K_DGRAD_FFN1 = BAMBOO_K_DGRAD_FFN1,
   K_DGRAD_ATTN_OUT = BAMBOO_K_DGRAD_ATTN_OUT, K_DGRAD_QKV = BAMBOO_K_DGRAD_QKV, K_WGRAD_GROUP = BAMBOO_K_WGRAD_GROUP,
   K_ATTN_FWD = BAMBOO_K_ATTN_FWD, K_ATTN_BWD = BAMBOO_K_ATTN_BWD, K_LN_FWD = BAMBOO_K_LN_FWD,
-  K_LN_BWD = BAMBOO_K_LN_BWD, K_COLSUM = BAMBOO_K_COLSUM, K_COUNT = BAMBOO_K_COUNT
+  K_LN_BWD = BAMBOO_K_LN_BWD, K_COLSUM = BAMBOO_K_COLSUM, K_SMALL_FWD = BAMBOO_K_SMALL_FWD,
+  K_SMALL_BWD = BAMBOO_K_SMALL_BWD, K_COUNT = BAMBOO_K_COUNT
 };
 
 // site: which GEMM of the layer pass this is (for the per-site timing)
@@ -366,12 +368,22 @@ GemmDesc gemm_tn(const void* X, const void* dY, float* dW, int T, int Kw, int Nw
 }
 
 // Whether the stage's layers go through the kernels that take a sample through them in one launch.  Decided by the
-// configuration and the parameters' alignment alone; with per-launch timing on, every launch is made singly, as the sites
-// that are timed are the single kernels.
-bool small_layers(const bamboo_stage* st, int kind) {
+// configuration alone, so that a replica's forward keeps the bits of the stage that it is a replica of (stage_init takes
+// parameters aligned to kAlign only); stage_single_launches overrides it for comparisons.
+bool small_layers(const bamboo_stage* st) {
   const bamboo_cfg_t& c = st->cfg;
-  return c.dtype == BAMBOO_F32 && !st->prof_on &&
-         small_layers_fit(c.micro_batch, c.seq, c.hidden, c.heads, c.ffn, st->w[kind]);
+  return c.dtype == BAMBOO_F32 && !st->single_launches && small_layers_fit(c.micro_batch, c.seq, c.hidden, c.heads, c.ffn);
+}
+// flops of a layer's forward products and of its attention
+double layer_fwd_flops(const bamboo_cfg_t& c) {
+  const double T = (double)c.micro_batch * c.seq, H = c.hidden;
+  return 2.0 * T * (4.0 * H * H + 2.0 * H * c.ffn) +
+         4.0 * T * c.seq * H * (c.arch == BAMBOO_ARCH_PRE_LN_CAUSAL ? 0.5 : 1.0);
+}
+double layer_input_grad_flops(const bamboo_cfg_t& c) {      // the products once more, the attention 2.5 times
+  const double T = (double)c.micro_batch * c.seq, H = c.hidden;
+  const double gemms = 2.0 * T * (4.0 * H * H + 2.0 * H * c.ffn);
+  return gemms + 2.5 * (layer_fwd_flops(c) - gemms);
 }
 SmallLayers small_args(const bamboo_stage* st, int kind, int slot, int layer, int n, const void* in, void* out) {
   const bamboo_cfg_t& c = st->cfg;
@@ -405,7 +417,8 @@ int run_forward(bamboo_stage* st, int kind, int lane_id, int slot, const void* x
   (void)hipGetLastError();  // do not inherit an unrelated earlier error of this thread
   const RecordLayout& r = st->rl;
   char* rec0 = st->stash[kind] + (uint64_t)slot * n * r.bytes;
-  if (small_layers(st, kind)) {
+  if (small_layers(st)) {
+    ProfScope ps(st, K_SMALL_FWD, s, n * layer_fwd_flops(c));
     HIPCHK(launch_small_fwd(s, c.micro_batch, small_args(st, kind, slot, 0, n, x, y)));
     return BAMBOO_OK;
   }
@@ -472,7 +485,10 @@ int small_backward(bamboo_stage* st, int kind, hipStream_t s, char* ws, const La
   for (int i = 0; i < 2; ++i)
     for (int j = 0; j < 3; ++j) b.p_ln[i][j] = (float*)(ws + w.p_ln[i][j]);
   b.p_dh = (float*)(ws + w.p_dh); b.p_dqkv = (float*)(ws + w.p_dqkv); b.p_df = (float*)(ws + w.p_df);
-  HIPCHK(launch_small_bwd(s, B, small_args(st, kind, slot, layer, 1, dy, dx), b));
+  {
+    ProfScope ps(st, K_SMALL_BWD, s, layer_input_grad_flops(c));
+    HIPCHK(launch_small_bwd(s, B, small_args(st, kind, slot, layer, 1, dy, dx), b));
+  }
   bool ok;
   if (c.arch == BAMBOO_ARCH_POST_LN_ENCODER) {
     ok = grad_reduce_add(batch, H, B, b.p_ln[1][0], G + p.g2, b.p_ln[1][1], G + p.be2) &&
@@ -516,7 +532,7 @@ int run_backward(bamboo_stage* st, int kind, int lane_id, int slot, const void* 
     auto P = [&](uint64_t off) { return (const void*)(W + off * es); };
     void* dx = (l == 0) ? (gx ? gx : (void*)(ws + w.ping)) : (void*)(ws + (((n - 1 - l) & 1) ? w.pong : w.ping));
     if (dx == dy) dx = ws + w.pong;  // never alias input and output of a layer
-    if (small_layers(st, kind)) {
+    if (small_layers(st)) {
       GradReduceBatch sums;
       sums.n = 0;
       BBCHK(small_backward(st, kind, s, ws, w, slot, l, dy, dx, G, &sums));
@@ -836,6 +852,7 @@ int stage_init(const bamboo_cfg_t* cfg, const bamboo_sizes_t* sizes, const void*
     st->ev_join = nullptr;
     st->last_frc_on_lane1 = -1;
     st->prof_on = false;
+    st->single_launches = false;
     st->opt[0] = st->opt[1] = nullptr;
     st->host_stash = nullptr;
     st->lane_swap = nullptr;
@@ -1202,6 +1219,12 @@ int stage_profile(bamboo_stage_t* st, int enable) {
   }
   st->prof_recs.clear();
   st->prof_on = enable != 0;
+  return BAMBOO_OK;
+}
+
+int stage_single_launches(bamboo_stage_t* st, int enable) {
+  if (!st) return BAMBOO_E_ARG;
+  st->single_launches = enable != 0;
   return BAMBOO_OK;
 }
 

@@ -102,9 +102,9 @@ def test_fp32_layers_of_a_sample_in_one_launch(B, arch, hidden, heads, ffn, seq,
         assert_close(B.to_host(hz.gx[k]), ref.gx[k], TOL[0], "small layers gx")
         assert torch.equal(hz.z_frc[k], hz.z_succ[k])
     check_grads(st.own_g.cpu().numpy(), ref.G_own, hidden, ffn, TOL[0], "own")
-    # with per-launch timing on, the same steps are launched one by one
+    # the same steps launched one by one
     inp, st1, hz1 = _build(B, sc)
-    st1.stage_profile(True)
+    st1.stage_single_launches(True)
     hz1.begin_iteration()
     hz1.run(st1.stage_schedule())
     hz1.sync()
@@ -113,6 +113,30 @@ def test_fp32_layers_of_a_sample_in_one_launch(B, arch, hidden, heads, ffn, seq,
         assert_close(B.to_host(hz.gx[k]), B.to_host(hz1.gx[k]), TOL[0], "small layers gx, launched singly")
     for s_ in (st, st1, hz.succ, hz1.succ):
         s_.stage_destroy()
+
+
+@pytest.mark.parametrize("name", ["tiny", "ragged_fp32_causal", "bf16_post_ln"])
+def test_timing_a_stage_changes_neither_its_launches_nor_its_bits(B, name):
+    sc = SMALL[name]
+    runs, sites = [], {}
+    for timed in (False, True):
+        _, st, hz = _build(B, sc)
+        if timed:
+            st.stage_profile(True)
+        hz.begin_iteration()
+        hz.run(st.stage_schedule())
+        hz.sync()
+        runs.append([t.clone() for t in hz.y + hz.gx + hz.z_frc] + [st.own_g.clone()])
+        if timed:
+            # a replica's forward is the successor's, timed or not
+            assert all(torch.equal(hz.z_frc[k], hz.z_succ[k]) for k in range(sc.M))
+            sites = {n: st.stage_profile_read(i)[1] for i, n in enumerate(B.KERNEL_CLASSES)}
+        st.stage_destroy()
+        hz.succ.stage_destroy()
+    assert all(torch.equal(a, b) for a, b in zip(*runs))
+    if name == "tiny":
+        assert sites["small_fwd"] == 2 * sc.M and sites["small_bwd"] == sc.M * sc.n_own
+        assert sites["gemm_qkv"] == 0 and sites["ln_bwd"] == 0 and sites["wgrad_group"] == sc.M * sc.n_own
 
 
 @pytest.mark.parametrize("name,k_fail", [("tiny", 1), ("tiny", 3), ("ragged_fp32_causal", 0),
