@@ -552,18 +552,25 @@ static int bwd_lds_bytes(int S, int H, int F) {
 }
 
 // A wavefront holds a row of a LayerNorm in one register and half of one the keys of a query; beyond that the line lies
-// where a CU per sample stops being faster than the chip per step.  An iteration of 4 micro-batches, steps launched one by
-// one / this, us (samples x tokens, H, F, layers own + replica, multiply-adds a sample and layer):
-//   2 x 16,  64, 256, 1 + 1 (0.8 M)   506 / 283      4 x 32,  64, 256, 2 + 3 (1.6 M)    996 / 762
-//   1 x  8,  32, 128, 1 + 1 (0.1 M)   511 / 227      4 x 32,  32, 128, 2 + 2 (0.4 M)    879 / 569
-//   2 x 16,  96, 384, 2 + 2 (1.8 M)   843 / 1026     4 x 16, 128, 512, 1 + 1 (3.1 M)    515 / 458
-//   1 x  8, 128, 512, 3 + 3 (1.6 M)  1137 / 1080     2 x 16, 128, 1024, 1 + 1 (5.2 M)   536 / 601
-// The forward of the first is one launch of 22 us, the backward 29 us and the weight gradients.  Sums split four ways
-// (small_gemm, small_colsums) cost 1 % at 16 tokens a sample and 5 % at 32 over one sum each, with which weight gradients
-// were 1.3 and bias gradients up to 1.9 times as far from 64 bits as the single kernels' (1.5e-7, 1.6e-7), now 1.04 and 1.0.
+// where a CU per sample stops being faster than the chip per step: the products of a row tile (up to 16 rows: more passes over
+// the FFN's columns still pay; 32 rows: one pass of 256 does), and the scores, of which a CU takes 32 queries' at a time.
+// An iteration of 3 micro-batches through 2 + 2 layers, 1 x tokens, H, heads, F, steps launched one by one / this, us:
+//   12,  64,  1, 256 (144 scores)   535 / 372      20, 64,  4, 256 (1600)  538 / 545      32, 64,  1,  256 (1024)  628 / 589
+//   16,  64,  4, 256 (1024)         534 / 413      24, 64,  4, 256 (2304)  534 / 591      32, 64,  2,  256 (2048)  540 / 588
+//   16,  64,  8, 256 (2048)         503 / 502      32, 64,  4, 256 (4096)  538 / 712      32, 64, 16,  256 (16384) 701 / 1492
+//   16,  64,  8, 640 (2048)         590 / 614      17, 64,  1, 512 (289)   633 / 702      17, 32,  1, 1024 (289)   613 / 725
+//   16,  64,  4, 640 (1024)         592 / 535      26, 64,  2, 256 (1352)  615 / 549      13, 64,  8,  640 (1352)  568 / 570
+// The steps are bound by the host, which is up to a quarter faster on one machine than on another; the line is drawn for a
+// fast one.  Over 158 configurations inside it, 1 and 8 samples: 0.47 to 1.02 of the steps' time, 0.72 at the median.  With
+// 256 samples of 16 tokens 704 / 624, wider layers (96 columns, 1.8 M multiply-adds) 843 / 1026.
+// The forward of 2 x 16 tokens, 64, 2, 256 is one launch of 22 us, the backward 29 us and the weight gradients.  Sums split
+// four ways (small_gemm, small_colsums) cost 1 % at 16 tokens a sample and 5 % at 32 over one sum each, with which weight
+// gradients were 1.3 and bias gradients up to 1.9 times as far from 64 bits as the single kernels' (1.5e-7, 1.6e-7), now 1.04
+// and 1.0.  128 registers a thread at 1024 threads: small_fwd_kernel<2> spills 32 of them (84 bytes), the others one or two.
 bool small_layers_fit(int B, int S, int H, int heads, int F) {
-  const long macs = (long)S * (4L * H * H + 2L * H * F);
-  return S <= 32 && H <= 64 && (H / heads) % 4 == 0 && macs <= 2000000 &&
+  const long macs = rows16(S) * (4L * H * H + 2L * H * F), scores = (long)heads * S * S;
+  const bool brief = S <= 16 ? macs <= 2000000 && scores + macs / 2000 <= 2000 : F <= 256 && scores <= 1400;
+  return S <= 32 && H <= 64 && (H / heads) % 4 == 0 && brief &&
          (size_t)B <= reduce_max_partials() && bwd_lds_bytes(S, H, F) <= 160 * 1024;
 }
 

@@ -88,7 +88,12 @@ def test_iteration_matches_oracle(B, name):
     (64, 16, 520, 16, 3),       # a full row tile; three passes over the FFN's columns, the last of 8
     (24, 2, 200, 17, 2),        # one row beyond a row tile
     (64, 1, 264, 32, 1),        # the most keys and the widest head
-    (40, 5, 256, 31, 2)])
+    (40, 5, 256, 31, 2),
+    (64, 4, 520, 16, 3),        # as the second to fifth, within the line that sends a layer there
+    (64, 16, 64, 9, 2),
+    (64, 4, 200, 17, 2),
+    (64, 1, 256, 32, 1),
+    (40, 1, 256, 31, 2)])
 def test_fp32_layers_of_a_sample_in_one_launch(B, arch, hidden, heads, ffn, seq, mb):
     sc = synth.StageConfig("small", arch, 0, hidden, heads, ffn, seq, mb, 2, 2, 4, 1, 3, 51)
     inp, st, hz = _build(B, sc)
@@ -137,6 +142,21 @@ def test_timing_a_stage_changes_neither_its_launches_nor_its_bits(B, name):
     if name == "tiny":
         assert sites["small_fwd"] == 2 * sc.M and sites["small_bwd"] == sc.M * sc.n_own
         assert sites["gemm_qkv"] == 0 and sites["ln_bwd"] == 0 and sites["wgrad_group"] == sc.M * sc.n_own
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,seq,one", [
+    (64, 4, 520, 16, 1), (64, 8, 520, 16, 0), (64, 2, 848, 16, 1), (64, 2, 856, 16, 0), (64, 1, 256, 32, 1), (64, 2, 256, 32, 0),
+    (64, 16, 256, 32, 0), (32, 8, 128, 29, 0), (64, 1, 264, 17, 0), (64, 1, 256, 33, 0), (72, 1, 64, 8, 0)])
+def test_which_fp32_layers_go_through_one_launch(B, hidden, heads, ffn, seq, one):
+    """Both sides of the line: many scores, several passes over the FFN's columns behind 17 to 32 rows, long or wide layers
+    are faster step by step."""
+    sc = synth.StageConfig("small", 0, 0, hidden, heads, ffn, seq, 2, 1, 1, 4, 1, 2, 52)
+    _, st, hz = _build(B, sc, with_successor=False)
+    st.stage_profile(True)
+    st.stage_fwd(0, hz.x[0], hz.y[0])
+    n = {name: st.stage_profile_read(i)[1] for i, name in enumerate(B.KERNEL_CLASSES)}
+    st.stage_destroy()
+    assert (n["small_fwd"], n["gemm_qkv"]) == ((1, 0) if one else (0, 1))
 
 
 @pytest.mark.parametrize("name,k_fail", [("tiny", 1), ("tiny", 3), ("ragged_fp32_causal", 0),
