@@ -48,10 +48,11 @@ __device__ __forceinline__ void block_of(int wg, int nblk, int nbh, int* blk, in
 // chunk ch of row r sits at position ch ^ swz(r) of its row, which every lane applies to the chunk that it FETCHES.  The
 // placement serves both ways a tile is read: 16 consecutive rows of one chunk (frag_k) and 4 rows x 64 bytes (frag_tr)
 // each cover the 64 banks once.  With the rows padded to D + 8 (D + 16 for the values of the forward pass) and staged
-// through registers the second kind, half of the backward's reads, met its own banks twice.  Forward / backward in us,
-// before and now (samples x tokens x heads x size):
-//   8 x 512 x 16 x 64    16.8 -> 16.2, 46.1 -> 43.3     1 x 8192 x 16 x 64 causal  171 -> 168, 534 -> 507
-//   4 x 512 x 16 x 64    11.1 -> 10.6, 24.4 -> 23.5     1 x 2048 x 96 x 128 causal 126 -> 125, 614 -> 531
+// through registers the second kind, half of the backward's reads, met its own banks twice.  Backward in us, before and now
+// (samples x tokens x heads x size; the forward: see fwd_launch):
+//   8 x 512 x 16 x 64   45.0 / 42.6     4 x 1024 x 25 x 64 causal   81.3 / 79.8     1 x 2048 x 96 x 128 causal  613 / 512
+//   4 x 512 x 16 x 64   23.7 / 22.8     2 x 2048 x 25 x 64 causal  129.9 / 129.2    2 x 512 x 24 x 128        52.9 / 50.1
+//   3 x 333 x 16 x 64   17.3 / 16.7     1 x 8192 x 16 x 64 causal  517 / 492        1 x 1500 x 20 x 128 causal 136.5 / 124.6
 // What bounds both passes is still a wavefront's own chain of matrix and vector instructions, at two wavefronts per SIMD.
 // Rows at or beyond row_lim are read from row row_lim - 1 (finite values that the consumers' masks turn
 // into exact zeros), so no load sits behind a branch.  A thread's byte offsets inside a tile and their
@@ -95,42 +96,76 @@ struct TileCopy {
                    : "memory", "m0");
   }
 };
-// vmcnt(N): at most the N youngest of this wavefront's loads are still on their way
-template <int N>
-__device__ __forceinline__ void wait_tiles() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// Addresses of a tile's operand fragments, relative to the tile (256-byte aligned).
+// every load of this wavefront has landed
+__device__ __forceinline__ void wait_tiles() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// The same placement through registers: requested (fetch) ahead of a step, put into LDS (stash) behind it.
 template <int D>
+struct RegCopy {
+  static constexpr int N = TileCopy<D>::N;
+  bf16x8 v[N];
+  __device__ __forceinline__ void fetch(const TileCopy<D>& c, const bf16_t* g, int tile) {
+    const unsigned t0 = (unsigned)tile * c.tile_bytes;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = *(const bf16x8*)((const char*)g + min(t0 + c.ofs[i], c.last[i]));
+  }
+  __device__ __forceinline__ void stash(unsigned lds) const {
+    typedef __attribute__((address_space(3))) bf16x8* lds_ptr;
+#pragma unroll
+    for (int i = 0; i < N; ++i) *(lds_ptr)(lds + i * 4096) = v[i];
+  }
+};
+
+// Addresses of the operand fragments.  Tiles are 256-byte aligned and the placement moves bits 4 to 7 only, so a fragment's
+// address is the slot's + (row 0, this lane's chunk ^ chunk) + an immediate offset for the tile in the slot and the row.
+// HELD: one register per chunk, and with slots that are constants (for_each_tile) no address arithmetic in a step: the
+// forward 0.94 to 0.98 of the time with addresses formed in each.  The backward passes, where registers are short, form
+// them from chunk 0, once for both tiles of a slot (held there: 1.02 to 1.08 of the time, from other schedules and spills).
+template <int D, bool HELD>
 struct FragAddr {
-  unsigned k;        // frag_k at row 0, k-step 0
-  unsigned tr[2];    // frag_tr at column 0, row 0: its two halves
-  __device__ __forceinline__ void init() {
+  unsigned k[HELD ? D / 16 : 1];       // frag_k at row 0
+  unsigned tr[HELD ? D / 32 : 1][2];   // frag_tr at row 0: its two halves
+  __device__ __forceinline__ void init(unsigned ring) {
     const int l = threadIdx.x & 63, i = l & 15, q = 4 * (l >> 5) + (i >> 2);
-    k = (l & 31) * D * 2 + (((l >> 5) ^ swz<D>(l & 31)) << 4);
     const int ch = ((l >> 4) & 1) * 2 + ((i & 3) >> 1);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) tr[h] = (q + 8 * h) * D * 2 + ((ch ^ swz<D>(q + 8 * h)) << 4) + (i & 1) * 8;
+    for (int ks = 0; ks < (HELD ? D / 16 : 1); ++ks)
+      k[ks] = ring + (l & 31) * D * 2 + ((((l >> 5) ^ swz<D>(l & 31)) ^ (2 * ks)) << 4);
+#pragma unroll
+    for (int dt = 0; dt < (HELD ? D / 32 : 1); ++dt)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        tr[dt][h] = ring + (q + 8 * h) * D * 2 + (((ch ^ swz<D>(q + 8 * h)) ^ (4 * dt)) << 4) + (i & 1) * 8;
   }
   // Operand fragment with the contraction index contiguous in LDS: lane l holds
   // row row_base + l%32, contraction elements 16*ks + 8*(l/32) .. +7.
-  __device__ __forceinline__ bf16x8 frag_k(unsigned tile, int row_base, int ks) const {
+  __device__ __forceinline__ bf16x8 frag_k(unsigned slot, unsigned tile, int row_base, int ks) const {
     typedef __attribute__((address_space(3))) const bf16x8* lds_ptr;
-    return *(lds_ptr)(((tile + k) ^ (ks << 5)) + row_base * D * 2);
+    const unsigned at = HELD ? k[HELD ? ks : 0] + slot : (k[0] + slot) ^ (ks << 5);
+    return *(lds_ptr)(at + (tile + row_base * D * 2));
   }
   // Operand fragment with the contraction index running over LDS rows (transposing
-  // load): lane l holds column col_base + l%32; its 8 contraction slots are rows
+  // load): lane l holds column 32*dt + l%32; its 8 contraction slots are rows
   // kbase + 4*(l/32) + {0..3} and kbase + 8 + 4*(l/32) + {0..3} -- the order in
   // which a 32x32 accumulator tile hands 8 of a lane's 16 values to the next MFMA.
-  __device__ __forceinline__ bf16x8 frag_tr(unsigned tile, int col_base, int kbase) const {
+  __device__ __forceinline__ bf16x8 frag_tr(unsigned slot, unsigned tile, int dt, int kbase) const {
     typedef __attribute__((address_space(3))) short4_t* lds_ptr;
     union { short4_t s4[2]; bf16x8 b; } u;
-    u.s4[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(((tile + tr[0]) ^ (col_base << 1)) + kbase * D * 2));
-    u.s4[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(((tile + tr[1]) ^ (col_base << 1)) + kbase * D * 2));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const unsigned at = HELD ? tr[HELD ? dt : 0][h] + slot : (tr[0][h] + slot) ^ (dt << 6);
+      u.s4[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(at + (tile + kbase * D * 2)));
+    }
     return u.b;
   }
 };
+// step(t, slot) for t = 0 .. nt - 1, slot = t mod 2 as a constant
+template <typename STEP>
+__device__ __forceinline__ void for_each_tile(int nt, STEP step) {
+  for (int t = 0; t < nt; t += 2) {
+    step(t, 0);
+    if (t + 1 < nt) step(t + 1, 1);
+  }
+}
 // registers 8*half .. 8*half+7 of an accumulator tile as a bf16 operand fragment
 __device__ __forceinline__ bf16x8 pack8(const f32x16& t, int half) {
   bf16x8 o;
@@ -238,12 +273,12 @@ __device__ __forceinline__ void block_colsum_write(float (&cs)[8], float* xch, f
 }
 
 // =============================================================== forward
-// NR: tiles of keys and values in LDS (see fwd_launch)
-template <int D, bool CAUSAL, int NR>
-__global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
+// REGS: the tiles pass through registers (see fwd_launch)
+template <int D, bool CAUSAL, bool REGS>
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_fwd_mfma_kernel(AttnDesc a) {
   constexpr unsigned TB = TileCopy<D>::BYTES;
   extern __shared__ __attribute__((aligned(256))) unsigned char smem_raw[];
-  const unsigned ring = lds_address(smem_raw);    // [NR][keys, values]
+  const unsigned ring = lds_address(smem_raw);    // [2][keys, values]
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 5;
   const int H = a.heads * D, S = a.S;
   int qblk, bh;
@@ -268,25 +303,37 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
   const int nt = (kend + TILE - 1) / TILE;
   TileCopy<D> copy;
   copy.init(rs, S);
-  FragAddr<D> fr;
-  fr.init();
-  auto fetch = [&](int t, unsigned at) __attribute__((always_inline)) {
-    copy.issue(base + H, t, at);
-    copy.issue(base + 2 * H, t, at + TB);
-  };
-  constexpr unsigned RING = NR * 2 * TB;
-  // the NR - 1 tiles after t are on their way while tile t is worked on
-  fetch(0, ring);
-  if (NR > 2 && nt > 1) fetch(1, ring + 2 * TB);
-  unsigned cur = 0;
-  for (int t = 0; t < nt; ++t) {
-    const unsigned ks_ = ring + cur, vs_ = ks_ + TB;
-    const unsigned free_slot = cur == 0 ? RING - 2 * TB : cur - 2 * TB;      // of tile t - 1
-    if (NR > 2 && t + 1 < nt) wait_tiles<2 * TileCopy<D>::N>();              // tile t has landed,
-    else wait_tiles<0>();
-    __syncthreads();                              // everywhere, and tile t - 1 has been read everywhere
-    if (t + NR - 1 < nt) fetch(t + NR - 1, ring + free_slot);
-    cur = cur + 2 * TB == RING ? 0 : cur + 2 * TB;
+  FragAddr<D, true> fr;
+  fr.init(ring);
+  RegCopy<D> kr, vr;
+  const unsigned put = ring + threadIdx.x * 16;
+  if constexpr (REGS) {
+    kr.fetch(copy, base + H, 0);
+    vr.fetch(copy, base + 2 * H, 0);
+    kr.stash(put);
+    vr.stash(put + TB);
+    __syncthreads();
+  } else {
+    copy.issue(base + H, 0, ring);
+    copy.issue(base + 2 * H, 0, ring + TB);
+  }
+  for_each_tile(nt, [&](int t, int slot) __attribute__((always_inline)) {
+    const unsigned at = slot * 2 * TB;
+    if constexpr (REGS) {
+      if (t + 1 < nt) {
+        kr.fetch(copy, base + H, t + 1);
+        vr.fetch(copy, base + 2 * H, t + 1);
+      }
+    } else {
+      wait_tiles();                               // tile t has landed
+      __syncthreads();                            // everywhere, and tile t - 1 has been read everywhere
+      if (t + 1 < nt) {
+        // formed here: captured, it moves the register allocation of the other form, 3 % of its time at head size 128
+        const unsigned ring = lds_address(smem_raw);
+        copy.issue(base + H, t + 1, ring + (slot ^ 1) * 2 * TB);
+        copy.issue(base + 2 * H, t + 1, ring + (slot ^ 1) * 2 * TB + TB);
+      }
+    }
     const int k0 = t * TILE;
     if (!CAUSAL || k0 <= qw0 + 31) {              // wave-uniform: tile not entirely above the diagonal
       f32x16 s[2];
@@ -298,7 +345,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
       for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
         for (int u = 0; u < 2; ++u)
-          s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(ks_, u * 32, ks), qf[ks], s[u], 0, 0, 0);
+          s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(at, 0, u * 32, ks), qf[ks], s[u], 0, 0, 0);
       // Online softmax in the log2 domain.  The running maximum m_i is only raised when some row's
       // maximum has grown by more than 8 (a factor 256, harmless in fp32 and bf16): softmax is
       // invariant to the shift, and the rescaling of the running output then happens on a few
@@ -353,11 +400,18 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
         for (int j = 0; j < 8; ++j) l_i += s[u >> 1][8 * (u & 1) + j];
 #pragma unroll
         for (int dt = 0; dt < D / 32; ++dt)
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(vs_, dt * 32, 16 * u), pb, o[dt], 0, 0, 0);
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(at, TB, dt, 16 * u), pb, o[dt], 0, 0, 0);
       }
     }
-  }
-  __syncthreads();                                // the tiles' place takes the results
+    if constexpr (REGS) {
+      if (t + 1 < nt) {
+        kr.stash(put + (slot ^ 1) * 2 * TB);
+        vr.stash(put + (slot ^ 1) * 2 * TB + TB);
+      }
+      __syncthreads();
+    }
+  });
+  if constexpr (!REGS) __syncthreads();                     // the tiles' place takes the results
   const float l_tot = l_i + __shfl_xor(l_i, 32, 64);
   const float inv = 1.f / l_tot;
   bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
@@ -369,16 +423,17 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(AttnDesc a) {
 // Two passes, by one kernel template: PASS_DQ and PASS_DKV are launched one after the other; with PASS_BOTH the first
 // n workgroups own key rows (the longer pass) and the others query rows, side by side.
 enum BwdPass { PASS_DQ, PASS_DKV, PASS_BOTH };
-// At head size 128 the dQ pass fits two wavefronts per SIMD since its tiles no longer pass through registers, with 16 to 28
-// bytes spilled (1 x 2048 x 96 x 128 causal: backward 570 us with one, 531 with two); the other pass holds 72 registers more.
+// At head size 128 the dQ pass fits two wavefronts per SIMD since its tiles no longer pass through registers, with 12 to 24
+// bytes spilled (1 x 2048 x 96 x 128 causal, when this was chosen: backward 570 us with one, 531 with two; 512 now); the
+// other pass holds 72 to 81 registers more.
 template <int D, bool CAUSAL, int PASS>
 __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void attn_bwd_mfma_kernel(AttnDesc a, int n) {
   constexpr unsigned TB = TileCopy<D>::BYTES;
   constexpr bool OWN_DELTA = PASS == PASS_BOTH;
   extern __shared__ __attribute__((aligned(256))) unsigned char smem_raw[];
   const unsigned ring = lds_address(smem_raw);      // [2][two tiles]
-  FragAddr<D> fr;
-  fr.init();
+  FragAddr<D, false> fr;
+  fr.init(0);
   // dQ: a wavefront owns 32 queries (lane = query) and streams 64-key tiles.
   if (PASS == PASS_DQ || (PASS == PASS_BOTH && (int)blockIdx.x >= n)) {
     const int wg = PASS == PASS_BOTH ? (int)blockIdx.x - n : (int)blockIdx.x;
@@ -433,14 +488,15 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
     copy.init(rs, S);
     copy.issue(base + H, 0, ring);
     copy.issue(base + 2 * H, 0, ring + TB);
-    wait_tiles<0>();
+    wait_tiles();
     __syncthreads();
     for (int t = 0; t < nt; ++t) {
-      const unsigned ks_ = ring + (t & 1) * 2 * TB, vs_ = ks_ + TB;
+      const int slot = t & 1;
+      const unsigned at = ring + slot * 2 * TB;
       const int k0 = t * TILE;
       if (t + 1 < nt) {
-        copy.issue(base + H, t + 1, ring + ((t + 1) & 1) * 2 * TB);
-        copy.issue(base + 2 * H, t + 1, ring + ((t + 1) & 1) * 2 * TB + TB);
+        copy.issue(base + H, t + 1, ring + (slot ^ 1) * 2 * TB);
+        copy.issue(base + 2 * H, t + 1, ring + (slot ^ 1) * 2 * TB + TB);
       }
       if (!CAUSAL || k0 <= qw0 + 31) {
         f32x16 s[2], dp[2];
@@ -448,8 +504,8 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
         for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(ks_, u * 32, ks), qf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
-            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(vs_, u * 32, ks), dof[ks], ks == 0 ? neg_delta : dp[u], 0,
+            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(at, 0, u * 32, ks), qf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
+            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(at, TB, u * 32, ks), dof[ks], ks == 0 ? neg_delta : dp[u], 0,
                                                             0, 0);
           }
         const bool need_mask = (k0 + TILE > S) || (CAUSAL && k0 + TILE - 1 > qw0);
@@ -474,10 +530,10 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
           const bf16x8 dsb = pack8(s[u >> 1], u & 1);
 #pragma unroll
           for (int dt = 0; dt < D / 32; ++dt)
-            dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(ks_, dt * 32, 16 * u), dsb, dq[dt], 0, 0, 0);
+            dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(at, 0, dt, 16 * u), dsb, dq[dt], 0, 0, 0);
         }
       }
-      wait_tiles<0>();
+      wait_tiles();
       __syncthreads();
     }
     bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
@@ -569,11 +625,11 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
     copy_do.issue(dbase, qbeg / TILE, ring + TB);
     fetch_stats(qbeg);
     stash_stats(0);
-    wait_tiles<0>();
+    wait_tiles();
     __syncthreads();
     for (int t = 0; t < nt; ++t) {
       const int buf = t & 1;
-      const unsigned qs_ = ring + buf * 2 * TB, dos_ = qs_ + TB;
+      const unsigned at = ring + buf * 2 * TB;
       const int q0t = qbeg + t * TILE;
       if (t + 1 < nt) {
         fetch_stats(q0t + TILE);
@@ -597,8 +653,8 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
         for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(qs_, u * 32, ks), kf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
-            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(dos_, u * 32, ks), vf[ks], dp[u], 0, 0, 0);
+            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(at, 0, u * 32, ks), kf[ks], ks == 0 ? zero16 : s[u], 0, 0, 0);
+            dp[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_k(at, TB, u * 32, ks), vf[ks], dp[u], 0, 0, 0);
           }
         const bool need_mask = (q0t + TILE > S) || (kw0 + 32 > S) || (CAUSAL && q0t < kw0 + 31);
 #pragma unroll
@@ -633,13 +689,13 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
           const bf16x8 dsb = pack8(dp[u >> 1], u & 1);
 #pragma unroll
           for (int dt = 0; dt < D / 32; ++dt) {
-            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(dos_, dt * 32, 16 * u), pb, dv[dt], 0, 0, 0);
-            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(qs_, dt * 32, 16 * u), dsb, dk[dt], 0, 0, 0);
+            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(at, TB, dt, 16 * u), pb, dv[dt], 0, 0, 0);
+            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(at, 0, dt, 16 * u), dsb, dk[dt], 0, 0, 0);
           }
         }
       }
       if (t + 1 < nt) stash_stats(buf ^ 1);
-      wait_tiles<0>();
+      wait_tiles();
       __syncthreads();
     }
     bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
@@ -669,25 +725,40 @@ static bool covered(const AttnDesc& a) {
   return !(misaligned(a.qkv) || misaligned(a.ctx) || misaligned(a.dctx) || misaligned(a.dqkv));
 }
 
-template <int D, bool CAUSAL, int NR>
-static hipError_t fwd_launch_ring(hipStream_t s, const AttnDesc& a, unsigned grid) {
-  constexpr int BYTES = NR * 2 * TileCopy<D>::BYTES;
+template <int D, bool CAUSAL, bool REGS>
+static hipError_t fwd_launch_form(hipStream_t s, const AttnDesc& a, unsigned grid) {
+  constexpr int BYTES = 2 * 2 * TileCopy<D>::BYTES;
   static_assert(BYTES >= 4 * 32 * (D + 8) * 2, "the four staging areas");
-  constexpr auto kern = attn_fwd_mfma_kernel<D, CAUSAL, NR>;
+  constexpr auto kern = attn_fwd_mfma_kernel<D, CAUSAL, REGS>;
   const hipError_t e = ensure_lds_attribute<kern, BYTES>();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), BYTES, s, a);
   return hipGetLastError();
 }
-// Three tiles in LDS, as a step takes less than a trip to memory, except at head size 128 where they leave room for one
-// workgroup per CU instead of two and the launch has more than that.
+// Tiles go straight to LDS where what a chiplet's workgroups read stays in its 4 MB of L2, and through registers where not:
+// loads to LDS that miss it return later (428 clocks a request on average against 353, with the same misses, at 1 x 1536 x
+// 20 x 128 causal), and a workgroup alone on its SIMDs waits for them.  Workgroup i runs on chiplet i mod 8 and reads the
+// keys and values of pair i mod (samples x heads): `met` bytes in all.  Long causal sequences share what is fetched, from
+// 32 row blocks of a pair on a chiplet on.  At head size 128 causal launches are the faster through registers, all.
+// Forward in us: before (padded rows, through registers) / straight to LDS / through registers, the form chosen marked *:
+//   8 x 512 x 16 x 64          14.6 / 13.5* / 14.5      1 x 4096 x 20 x 64 causal   69.2 / 72.7 / 66.4*
+//   3 x 333 x 16 x 64           8.8 /  8.0* /  8.5      2 x 2048 x 25 x 64 causal   42.4 / 43.3 / 41.7*
+//   8 x 1024 x 16 x 64 causal  31.3 / 30.1* / 30.4      4 x 1024 x 25 x 64 causal   26.4 / 25.7 / 25.1*
+//   1 x 8192 x 16 x 64 causal   171 /  164* /  166      1 x 3072 x 10 x 64 causal   45.8 / 52.7 / 44.8*
+//   2 x 4096 x 16 x 64 causal  92.2 / 85.2* / 90.2      1 x 3072 x 10 x 64          46.9 / 45.8 / 44.2*
+//   1 x 2048 x 96 x 128         226 /  212* /  223      1 x 1536 x 20 x 128         36.1 / 36.9 / 36.1*
+//   2 x 512 x 24 x 128         14.9 / 14.0* / 14.9      1 x 1500 x 20 x 128 causal  36.1 / 40.9 / 36.1*
+//   1 x 2048 x 96 x 128 causal  122 /  120  /  123*     4 x 1024 x 12 x 128 causal  28.8 / 29.9 / 28.4*
+// Rings of three tiles lost to two in every case but one (1 x 2048 x 17 x 128: 58.4 against 60.7).
 template <int D, bool CAUSAL>
 static hipError_t fwd_launch(hipStream_t s, const AttnDesc& a) {
   const unsigned grid = (unsigned)(((a.S + 127) / 128) * a.B * a.heads);
-  if constexpr (D == 128) {
-    if (grid > 256) return fwd_launch_ring<D, CAUSAL, 2>(s, a, grid);
-  }
-  return fwd_launch_ring<D, CAUSAL, 3>(s, a, grid);
+  const int pairs = a.B * a.heads, shared = pairs % 8 == 0 ? 8 : pairs % 4 == 0 ? 4 : pairs % 2 == 0 ? 2 : 1;
+  const double met = (double)(pairs / shared) * a.S * D * 4;
+  bool regs;
+  if (CAUSAL) regs = D == 128 || (met > 2.2e6 && (a.S + 127) / 128 * shared < 256);
+  else regs = met > 3e6 && grid <= 256;
+  return regs ? fwd_launch_form<D, CAUSAL, true>(s, a, grid) : fwd_launch_form<D, CAUSAL, false>(s, a, grid);
 }
 
 // Both backward passes as one launch up to 512 workgroups at head size 64 (what the chip holds at once, two per CU) and up

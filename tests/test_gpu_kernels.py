@@ -477,9 +477,27 @@ def test_attention_at_the_longest_sequence_of_the_one_launch_backward(B, causal,
                                                (1, 192, 2, 128), (1, 193, 3, 64), (2, 257, 2, 128), (1, 129, 128, 128),
                                                (1, 129, 129, 128)])
 def test_attention_at_the_ends_of_its_tile_ring(B, causal, batch, seq, heads, d):
-    """One to five tiles of 64 rows through a ring of two or three, a last tile of one row, and at head size 128 both
-    sides of the 256 workgroups from which on the ring is the shorter one."""
+    """One to five tiles of 64 rows through a ring of two, a last tile of one row, and at head size 128 both sides of the
+    256 workgroups from which on some CUs hold two."""
     test_attention_forward_backward(B, 1, 2, causal, batch, seq, heads, d)
+
+
+@pytest.mark.parametrize("causal,batch,seq,heads,d", [(0, 7, 641, 3, 64), (1, 7, 641, 3, 64), (0, 7, 704, 3, 64),
+                                                      (1, 7, 704, 3, 64), (0, 7, 385, 3, 128), (0, 5, 448, 5, 128)])
+def test_attention_forward_through_registers_and_straight_to_lds_is_the_same(B, causal, batch, seq, heads, d):
+    """A whole batch (more keys and values than a chiplet's L2 holds, few workgroups: tiles through registers) against its
+    samples one by one (straight to LDS); odd and even numbers of tiles, a last tile of one row."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seq + d)
+    H, T = heads * d, batch * seq
+    qkv = torch.randn(T, 3 * H, generator=gen, device=DEV).bfloat16()
+    ctx, lse = _empty((T, H), 1), torch.empty(batch * heads * seq, device=DEV)
+    B.bk_attention_fwd(qkv, ctx, lse, batch, seq, heads, causal, impl=2)
+    one, lse_one = _empty((seq, H), 1), torch.empty(heads * seq, device=DEV)
+    for b in range(batch):
+        rows = slice(b * seq, (b + 1) * seq)
+        B.bk_attention_fwd(qkv[rows], one, lse_one, 1, seq, heads, causal, impl=2)
+        assert torch.equal(one, ctx[rows]) and torch.equal(lse_one, lse[b * heads * seq:(b + 1) * heads * seq]), b
 
 
 @pytest.mark.parametrize("causal", [0, 1])
