@@ -761,20 +761,28 @@ static hipError_t fwd_launch(hipStream_t s, const AttnDesc& a) {
   return regs ? fwd_launch_form<D, CAUSAL, true>(s, a, grid) : fwd_launch_form<D, CAUSAL, false>(s, a, grid);
 }
 
-// Both backward passes as one launch up to 512 workgroups at head size 64 (what the chip holds at once, two per CU) and up
-// to 320 at 128, where it holds 256: the second pass need not wait for the first, which leaves most CUs idle, and a
-// launch is saved; it costs the key owners their own delta.  The limit at 128 is where the two were measured to meet,
-// between 320 and 384.  Backward in us, two launches / one (samples, tokens, heads, size):
-// (timed before tiles went straight to LDS)
-//   1 x 128 x 16 x 64: 13.0 / 8.1    3 x 333 x 16 x 64: 25.7 / 19.1    4 x 512 x 16 x 64 (512 workgroups): 32.9 / 27.2
-//   8 x 512 x 16 x 64 (1024): 48.6 / 50.6    1 x 700 x 24 x 128 (288): 67.2 / 51.3    2 x 512 x 24 x 128 (384): 55.6 / 55.5
-//   1 x 1024 x 4 x 64 (64): 48.3 / 33.4    2 x 512 x 20 x 128 (320): 52.3 / 44.7
+// Both backward passes as one launch: the second need not wait for the first, whose last workgroups leave most CUs idle, and
+// a launch is saved; it costs the key owners their own delta.  With a causal mask the passes' workgroups differ in length
+// and fill each other's gaps, so it pays to more workgroups.  The chip holds 512 at head size 64 and 256 at 128, where the
+// kernel of both passes leaves room for one wavefront per SIMD and the dQ pass by itself for two.  The limits are where
+// the two were measured to meet.  Backward in us, two launches / one (samples x tokens x heads, workgroups of both passes):
+//   head size 64                                            causal
+//   1 x 1024 x 4   (64)    43.0 / 31.7   6 x 512 x 16 (768)  36.6 / 34.5    4 x 512 x 16 (512)   29.8 / 22.5
+//   4 x 512 x 16  (512)    27.1 / 22.8   7 x 512 x 16 (896)  43.5 / 44.0    8 x 512 x 16 (1024)  37.0 / 33.8
+//   5 x 512 x 16  (640)    36.0 / 29.3   8 x 512 x 16 (1024) 43.4 / 46.7   12 x 512 x 16 (1536)  54.3 / 51.1
+//   3 x 1024 x 16 (768)    61.0 / 59.7   9 x 512 x 16 (1152) 61.9 / 52.5   16 x 512 x 16 (2048)  69.3 / 70.7
+//   head size 128
+//   1 x 1024 x 8  (128)    81.7 / 60.3   1 x 1024 x 22 (352) 88.1 / 98.5    1 x 1024 x 32 (512)  87.6 / 66.6
+//   2 x 512 x 20  (320)    49.4 / 41.5   2 x 512 x 24 (384)  50.2 / 53.0    8 x 256 x 16 (512)   37.1 / 33.5
+//   5 x 256 x 16  (320)    31.6 / 26.8   1 x 1024 x 32 (512) 88.5 / 98.4    3 x 1024 x 16 (768)  94.3 / 101
+// Up to two row blocks a sequence the causal workgroups hardly differ: 16 x 256 x 16 x 64 (1024) 27.6 / 29.4.
 // Longer sequences keep two launches: the deltas of a sequence are held in LDS, 4 KB of it here (few heads of more
 // tokens were not measured).
 constexpr int kBothMaxSeq = 1024;
-template <int D>
+template <int D, bool CAUSAL>
 static bool side_by_side(const AttnDesc& a, unsigned wgs) {
-  return a.S <= kBothMaxSeq && 2 * wgs <= (D == 64 ? 512u : 320u);
+  const unsigned most = D == 64 ? (CAUSAL && a.S > 256 ? 1536u : 768u) : (CAUSAL ? 512u : 320u);
+  return a.S <= kBothMaxSeq && 2 * wgs <= most;
 }
 
 template <int D, bool CAUSAL>
@@ -788,7 +796,7 @@ static hipError_t bwd_launch(hipStream_t s, const AttnDesc& a) {
   if (e == hipSuccess) e = ensure_lds_attribute<kkv, BYTES_DKV>();
   if (e != hipSuccess) return e;
   dim3 grid(((a.S + 127) / 128) * a.B * a.heads);
-  if (side_by_side<D>(a, grid.x)) {
+  if (side_by_side<D, CAUSAL>(a, grid.x)) {
     constexpr int BYTES_BOTH = BYTES_DKV + kBothMaxSeq * 4;
     constexpr auto kboth = attn_bwd_mfma_kernel<D, CAUSAL, PASS_BOTH>;
     e = ensure_lds_attribute<kboth, BYTES_BOTH>();

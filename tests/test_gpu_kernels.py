@@ -501,9 +501,11 @@ def test_attention_forward_through_registers_and_straight_to_lds_is_the_same(B, 
 
 
 @pytest.mark.parametrize("causal", [0, 1])
-@pytest.mark.parametrize("batch,seq,heads,d", [(8, 129, 16, 64), (8, 129, 17, 64), (3, 200, 27, 128)])
+@pytest.mark.parametrize("batch,seq,heads,d", [(8, 129, 16, 64), (8, 129, 17, 64), (3, 200, 27, 128),
+                                                (12, 129, 17, 64), (6, 300, 43, 64), (5, 200, 27, 128)])
 def test_attention_backward_in_one_launch_and_in_two_is_the_same(B, causal, batch, seq, heads, d):
-    """A whole batch (256 workgroups a pass: one launch; 272 and 162: two) against its samples one by one (one launch)."""
+    """A whole batch against its samples one by one (one launch): two launches for the third case without a mask, for
+    the fourth to sixth (408, 774 and 270 workgroups a pass) with and without."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seq + heads)
     H, T = heads * d, batch * seq
