@@ -82,6 +82,8 @@ int bk_gemm_tile(int code);
 /* Force the depth of the LDS slice ring of the pipelined MFMA GEMM kernel (2, 3 or 4 buffers; a
  * depth that does not fit the tile's LDS budget or exceeds the number of K slices falls back to the
  * next smaller one); no product splits K over wavefronts meanwhile.  0 restores the automatic choice.  Returns the previous value, or BAMBOO_E_ARG.
+ * The grouped weight gradients offer 2 and 3 for a forced 128 x 128 tile and the 256 x 256 tile's own; with any other
+ * tile forced, or a depth without a tile, the products are launched singly.
  * Process-wide, like bk_gemm_tile. */
 int bk_gemm_stages(int n);
 

@@ -204,7 +204,7 @@ struct EpiOperands {
 // chunks of 8 would have it, each touched every other 16 bytes of twice as many cache lines.  A layer's four weight
 // gradients in one launch, before -> after: 2048 tokens of 12288 x 49152 7590 -> 7195 us, 4096 of 1024 x 4096 107 -> 103,
 // 2048 of the same 68 -> 63.5, 1024 of 1600 x 6400 99 -> 93.5, 128 of the same 52.5 -> 48.2; 4096 of 1600 x 6400 alone
-// 274 -> 281 (in the whole stage level).  With plain loads, stores or both: 1-12 % slower but for the 12288-wide layer.
+// 274 -> 281 (in the whole stage, traced in turn, 274.7 -> 277.5).  With plain loads, stores or both: 1-12 % slower but for the 12288-wide layer.
 __device__ __forceinline__ void accumulate4(const GemmDesc& d, int m, int n, const f32x4& acc, const f32x4& old) {
   f32x4 v;
 #pragma unroll
@@ -1320,21 +1320,23 @@ static const TileCost kCostAcc[] = {       // fp32 read-modify-write output (wei
     {22, 3, 5.78f, 0.564f, 3.32f}, {24, 3, 9.21f, 0.981f, 3.42f}, {42, 3, 9.66f, 0.958f, 3.31f},
     {44, 2, 28.80f, 1.223f, 0.f}};
 // The same for the four products of a layer in one launch (launch_gemm_group_mfma), whose tiles share the rounds: fits to
-// timings of 18 groups (layers of 1024 x 4096, 1600 x 6400 and 512 x 2048, 64 to 4096 tokens), microseconds:
-//   tokens  layer         128 x 128, three deep   128 x 128, two deep, two per CU   256 x 256
-//   128     1024 x 4096    25.0                    24.7                              31.2
-//   768     1024 x 4096    37.2                    37.3                              42.2
-//   1000    1024 x 4096    42.1                    43.1                              46.8
-//   2048    1024 x 4096    64.8                    67.0                              65.7
-//   4096    1024 x 4096   112.5                   117.2                             103.9
-//   128     1600 x 6400    58.1                    52.5                              63.9
-//   1024    1600 x 6400   113.7                    92.9                             102.0
-//   2048    1600 x 6400   185.2                   152.6                             148.8
+// timings of 18 groups.  Timed again with the present epilogue (accumulate4), microseconds:
+//   tokens  layer         128 x 128, three deep   128 x 128, two deep, two per CU   256 x 256   128 x 256   256 x 128
+//   128      768 x 3072    14.8                    14.3                              20.6        14.6        16.2
+//   128     1024 x 4096    22.3                    22.4                              27.9        27.7        28.6
+//   768     1024 x 4096    35.7                    38.1                              39.9        41.2        42.6
+//   2048    1024 x 4096    63.8                    67.7                              63.6        73.3        72.0
+//   4096    1024 x 4096   113.1                   126.0                             101.7       127.9       122.7
+//   128     1600 x 6400    49.9                    48.0                              59.3        51.9        55.2
+//   1024    1600 x 6400   102.5                    90.5                              96.2       100.0       111.5
+//   4096    1600 x 6400   317.8                   283.4                             284.3       282.6       311.5
+//   4096    1280 x 5120   205.2                   202.7                             202.7       202.4       197.1
 // Two workgroups on a CU overlap one's gradient reads and writes, which are most of a short product's time, with the other's
-// loop.  (By the single launches' coefficients above the large tile was taken from 600 tokens on.)
+// loop.  Over 65 groups (layers of 512 x 2048 to 2048 x 8192, 64 to 4096 tokens) the choice by these coefficients takes 0.4 %
+// more than the best of the five tiles, at most 6.7 % (768 tokens of 1024 x 4096); a least-squares fit to all of them 1.2 % and
+// 21 %.  128 x 256 and 256 x 128 are not offered: the best in two of the 65, by 0.3 and 2.5 %.
 static const TileCost kCostGroup[] = {
-    {22, 3, 5.3f, 0.51f, 4.0f}, {22, 2, 9.6f, 0.84f, 1.1f}, {44, 2, 29.5f, 1.30f, 0.f}, {24, 3, 9.21f, 0.981f, 3.42f},
-    {42, 3, 9.66f, 0.958f, 3.31f}};
+    {22, 3, 5.3f, 0.51f, 4.0f}, {22, 2, 9.6f, 0.84f, 1.1f}, {44, 2, 29.5f, 1.30f, 0.f}};
 static float rounds_of(long tiles, long slots) {
   const long full = tiles / slots, rest = tiles % slots;
   return (float)full + (rest > 0 ? 0.75f + 0.25f * (float)rest / (float)slots : 0.f);
@@ -1555,20 +1557,16 @@ hipError_t launch_gemm_group_mfma(hipStream_t s, const GemmDesc* d, int n, const
     }
   }
   if (pick == 0) return hipErrorNotSupported;
-  if (g_forced_tile == 22 || g_forced_tile == 44 || g_forced_tile == 24 || g_forced_tile == 42) {
+  if (g_forced_tile == 22 || g_forced_tile == 44) {
     for (int i = 0; i < n; ++i)
       if (!tile_in_reach(d[i], 64 * (g_forced_tile / 10), 64 * (g_forced_tile % 10))) return hipErrorNotSupported;
     pick = g_forced_tile;
-    depth = 3;
+    depth = g_forced_stages == 2 ? 2 : 3;          // of the 128 x 128 tile; the others have one
   } else if (g_forced_tile || g_forced_stages) {
     return hipErrorNotSupported;   // a forced shape this launch does not offer
   }
-  switch (pick) {
-    case 44: return launch_group_cfg<4, 4, 2>(s, g);
-    case 24: return launch_group_cfg<2, 4, 3>(s, g);
-    case 42: return launch_group_cfg<4, 2, 3>(s, g);
-    default: return depth == 2 ? launch_group_cfg<2, 2, 2>(s, g) : launch_group_cfg<2, 2, 3>(s, g);
-  }
+  if (pick == 44) return launch_group_cfg<4, 4, 2>(s, g);
+  return depth == 2 ? launch_group_cfg<2, 2, 2>(s, g) : launch_group_cfg<2, 2, 3>(s, g);
 }
 
 hipError_t launch_gemm_mfma(hipStream_t s, const GemmDesc& d) {

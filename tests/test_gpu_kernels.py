@@ -140,7 +140,7 @@ def test_grouped_weight_gradients_equal_the_single_launches_bitwise(B, shapes):
     for X, dY, dW in zip(Xs, dYs, single):
         B.bk_linear_bwd_weight(X, dY, dW)
     try:
-        for tile in (0, 22, 44, 24, 42):
+        for tile in (0, 22, 44, 24, 42):             # the last two are launched singly
             B.bk_gemm_tile(tile)
             grouped = [w.clone() for w in inits]
             B.bk_linear_bwd_weight_group(Xs, dYs, grouped)
@@ -152,6 +152,30 @@ def test_grouped_weight_gradients_equal_the_single_launches_bitwise(B, shapes):
     T, K, N = shapes[0]
     want = inits[0].cpu().numpy().astype(np.float64) + B.to_host(Xs[0]).T @ B.to_host(dYs[0])
     assert_close(single[0].cpu().numpy(), want, 1e-5, "kernels single[0].cpu().numpy()")
+
+
+@pytest.mark.parametrize("depth", [2, 3])
+@pytest.mark.parametrize("shapes", [[(64, 136, 264), (64, 128, 128)], [(65, 520, 72), (1, 64, 64), (200, 256, 1032)],
+                                    [(1000, 640, 2560), (1000, 2560, 640), (1000, 640, 640), (1000, 640, 1920)]])
+def test_grouped_weight_gradients_with_either_ring_of_the_128_tile(B, shapes, depth):
+    """One slice and fewer than the ring holds, a contraction that ends inside a slice, more tiles than fit the chip at two
+    a CU; bitwise the single launches."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(depth)
+    Xs = [torch.randn(T, K, generator=gen, device=DEV).bfloat16() for T, K, N in shapes]
+    dYs = [torch.randn(T, N, generator=gen, device=DEV).bfloat16() for T, K, N in shapes]
+    single = [torch.randn(K, N, generator=gen, device=DEV) for T, K, N in shapes]
+    grouped = [w.clone() for w in single]
+    for X, dY, dW in zip(Xs, dYs, single):
+        B.bk_linear_bwd_weight(X, dY, dW)
+    try:
+        B.bk_gemm_tile(22)
+        B.bk_gemm_stages(depth)
+        B.bk_linear_bwd_weight_group(Xs, dYs, grouped)
+    finally:
+        B.bk_gemm_tile(0)
+        B.bk_gemm_stages(0)
+    assert all(torch.equal(a, b) for a, b in zip(grouped, single))
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
