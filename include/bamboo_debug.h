@@ -69,6 +69,11 @@ int stage_workspace_fields(const bamboo_cfg_t* cfg, uint64_t out[7]);
  * name of its own.  Its known traffic calibrates the HBM byte counters read for the other kernels. */
 int bk_copy(const void* src, void* dst, uint64_t bytes, void* stream);
 
+/* bk_layernorm_bwd as a stage runs it: also dbias[H] (fp32) += the token sums of the stored dr (the bias gradient of the linear
+ * layer ahead of the LayerNorm).  partial: fp32 scratch of 3 / 2 bk_layernorm_bwd_scratch_floats(H) floats. */
+int bk_layernorm_bwd_bias(int dtype, int T, int H, const void* dout, const void* r, const float* stats, const void* gamma,
+                          const void* add, void* dr, float* dgamma, float* dbeta, float* dbias, float* partial, void* stream);
+
 /* Choose the output tile of the MFMA GEMM kernel for all later calls in this process.
  * code = 10*WM + WN selects a (64*WM) x (64*WN) tile, one of 44, 43, 42, 24, 22, 11; 0 restores the
  * automatic choice.  Returns the previous code, or BAMBOO_E_ARG for a code that is not offered.

@@ -126,6 +126,7 @@ _SIGS = {
     "bk_attention_bwd": (C.c_int, [C.c_int] * 7 + [_vp] * 7),
     "bk_layernorm_fwd": (C.c_int, [C.c_int] * 3 + [_f32] + [_vp] * 6),
     "bk_layernorm_bwd": (C.c_int, [C.c_int] * 3 + [_vp] * 10),
+    "bk_layernorm_bwd_bias": (C.c_int, [C.c_int] * 3 + [_vp] * 11),
     "bk_layernorm_bwd_scratch_floats": (C.c_uint64, [C.c_int]),
     "bk_copy": (C.c_int, [_vp, _vp, C.c_uint64, _vp]),
     "bk_embedding_fwd": (C.c_int, [C.c_int] * 5 + [_vp] * 5),
@@ -535,6 +536,16 @@ def bk_layernorm_bwd(dout, r, stats, gamma, dr, dgamma, dbeta, add=None, stream=
     partial = torch.empty(int(lib.bk_layernorm_bwd_scratch_floats(H)), dtype=torch.float32, device=r.device)
     _check(lib.bk_layernorm_bwd(_dt(r), T, H, _ptr(dout), _ptr(r), _ptr(stats), _ptr(gamma), _ptr(add), _ptr(dr),
                                 _ptr(dgamma), _ptr(dbeta), _ptr(partial), _stream(stream)), "bk_layernorm_bwd")
+    return partial
+
+
+def bk_layernorm_bwd_bias(dout, r, stats, gamma, dr, dgamma, dbeta, dbias, add=None, stream=None):
+    import torch
+    T, H = r.shape
+    partial = torch.empty(int(lib.bk_layernorm_bwd_scratch_floats(H)) // 2 * 3, dtype=torch.float32, device=r.device)
+    _check(lib.bk_layernorm_bwd_bias(_dt(r), T, H, _ptr(dout), _ptr(r), _ptr(stats), _ptr(gamma), _ptr(add), _ptr(dr),
+                                     _ptr(dgamma), _ptr(dbeta), _ptr(dbias), _ptr(partial), _stream(stream)),
+           "bk_layernorm_bwd_bias")
     return partial
 
 

@@ -148,6 +148,25 @@ int bk_layernorm_bwd(int dtype, int T, int H, const void* dout, const void* r, c
   return finish(launch_layernorm_bwd((hipStream_t)stream, dtype, T, H, dout, r, stats, gamma, add, dr, dgamma, dbeta,
                                      partial));
 }
+int bk_layernorm_bwd_bias(int dtype, int T, int H, const void* dout, const void* r, const float* stats, const void* gamma,
+                          const void* add, void* dr, float* dgamma, float* dbeta, float* dbias, float* partial, void* stream) {
+  if ((dtype != 0 && dtype != 1) || T <= 0 || H <= 0 || H % 8 || !dout || !r || !stats || !gamma || !dr || !dgamma ||
+      !dbeta || !dbias || !partial)
+    return BAMBOO_E_ARG;
+  (void)hipGetLastError();
+  const size_t rows = ln_bwd_partial_floats(H) / 2;
+  float *pg = partial, *pb = pg + rows, *pc = pb + rows;
+  int parts = 0;
+  hipError_t e = launch_layernorm_bwd_partials((hipStream_t)stream, dtype, T, H, dout, r, stats, gamma, add, dr, pg, pb, pc,
+                                               &parts);
+  GradReduceBatch sums;
+  sums.n = 0;
+  if (e == hipSuccess && !(grad_reduce_add(&sums, H, parts, pg, dgamma, pb, dbeta) &&
+                           grad_reduce_add(&sums, H, parts, pc, dbias, nullptr, nullptr)))
+    return BAMBOO_E_STATE;
+  if (e == hipSuccess) e = launch_grad_reduce((hipStream_t)stream, sums);
+  return finish(e);
+}
 uint64_t bk_layernorm_bwd_scratch_floats(int H) { return ln_bwd_partial_floats(H); }
 
 int bk_copy(const void* src, void* dst, uint64_t bytes, void* stream) {

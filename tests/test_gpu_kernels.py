@@ -354,6 +354,33 @@ def test_layernorm_at_the_edges_of_its_kernels(B, dtype, T, H):
     test_layernorm_forward_backward(B, dtype, T, H)
 
 
+@pytest.mark.parametrize("residual", [0, 1])
+@pytest.mark.parametrize("dtype,T,H", [(0, 9, 64), (0, 700, 512), (0, 300, 1024), (0, 301, 1032), (0, 2100, 2056), (0, 5, 4104),
+                                       (0, 20, 6144), (0, 7, 6152), (1, 9, 72), (1, 700, 1024), (1, 2100, 1600), (1, 301, 2048),
+                                       (1, 301, 2056), (1, 2100, 4104), (1, 300, 8200), (1, 2057, 12288), (1, 7, 12296)])
+def test_layernorm_backward_with_the_bias_gradient(B, dtype, T, H, residual):
+    """The sums a stage asks for beside gain and shift: of dr as it is stored.  Every kernel, few rows, several a workgroup
+    (one or two passes of its wavefronts) and a short last workgroup.  dr is the same as without them but for an fp32
+    rounding (half an ulp, 2^-24, on either side); sums of T fp32 terms are off by at most T 2^-24 of the sum of magnitudes."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T + H)
+    act = torch.bfloat16 if dtype else torch.float32
+    r, d, add = (torch.randn(T, H, generator=gen, device=DEV).to(act) for _ in range(3))
+    gamma, beta = (torch.randn(H, generator=gen, device=DEV).to(act) for _ in range(2))
+    add = add if residual else None
+    y, stats = torch.empty_like(r), torch.empty(T, 2, device=DEV)
+    B.bk_layernorm_fwd(r, gamma, beta, y, stats)
+    plain, dr = torch.empty_like(r), torch.empty_like(r)
+    g0, b0, g1, b1 = (torch.zeros(H, device=DEV) for _ in range(4))
+    c1 = torch.full((H,), 3.0, device=DEV)
+    B.bk_layernorm_bwd(d, r, stats, gamma, plain, g0, b0, add=add)
+    B.bk_layernorm_bwd_bias(d, r, stats, gamma, dr, g1, b1, c1, add=add)
+    assert (dr.double() - plain.double()).norm() <= 2.0 ** -23 * plain.double().norm()
+    assert torch.equal(g0, g1) and torch.equal(b0, b1)
+    want = 3.0 + dr.double().sum(0)
+    assert bool(((c1.double() - want).abs() <= T * 2.0 ** -24 * (3.0 + dr.double().abs().sum(0))).all())
+
+
 def _fma(a, b, c):
     """One rounding, as the device's fma (fp64 holds the product of two fp32 values exactly)."""
     return (a.double() * b.double() + c.double()).float()
