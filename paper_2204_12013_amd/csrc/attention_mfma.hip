@@ -96,8 +96,11 @@ struct TileCopy {
                    : "memory", "m0");
   }
 };
-// every load of this wavefront has landed
-__device__ __forceinline__ void wait_tiles() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// at most the N youngest of this wavefront's loads are still on their way
+template <int N>
+__device__ __forceinline__ void wait_tiles() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 // The same placement through registers: requested (fetch) ahead of a step, put into LDS (stash) behind it.
 template <int D>
 struct RegCopy {
@@ -278,6 +281,8 @@ template <int D, bool CAUSAL, bool REGS>
 __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_fwd_mfma_kernel(AttnDesc a) {
   constexpr unsigned TB = TileCopy<D>::BYTES;
   extern __shared__ __attribute__((aligned(256))) unsigned char smem_raw[];
+  // both slots requested ahead of the first step: 2-3 % at head size 64, nothing or -1 % in the other forms
+  constexpr bool BOTH = !REGS && D == 64 && !CAUSAL;
   const unsigned ring = lds_address(smem_raw);    // [2][keys, values]
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 5;
   const int H = a.heads * D, S = a.S;
@@ -316,6 +321,10 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_fwd_mfma_kernel(Att
   } else {
     copy.issue(base + H, 0, ring);
     copy.issue(base + 2 * H, 0, ring + TB);
+    if (BOTH && nt > 1) {
+      copy.issue(base + H, 1, ring + 2 * TB);
+      copy.issue(base + 2 * H, 1, ring + 3 * TB);
+    }
   }
   for_each_tile(nt, [&](int t, int slot) __attribute__((always_inline)) {
     const unsigned at = slot * 2 * TB;
@@ -325,9 +334,10 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_fwd_mfma_kernel(Att
         vr.fetch(copy, base + 2 * H, t + 1);
       }
     } else {
-      wait_tiles();                               // tile t has landed
+      if (BOTH && t == 0 && nt > 1) wait_tiles<2 * TileCopy<D>::N>();        // tile t has landed
+      else wait_tiles<0>();
       __syncthreads();                            // everywhere, and tile t - 1 has been read everywhere
-      if (t + 1 < nt) {
+      if ((!BOTH || t > 0) && t + 1 < nt) {
         // formed here: captured, it moves the register allocation of the other form, 3 % of its time at head size 128
         const unsigned ring = lds_address(smem_raw);
         copy.issue(base + H, t + 1, ring + (slot ^ 1) * 2 * TB);
@@ -488,7 +498,7 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
     copy.init(rs, S);
     copy.issue(base + H, 0, ring);
     copy.issue(base + 2 * H, 0, ring + TB);
-    wait_tiles();
+    wait_tiles<0>();
     __syncthreads();
     for (int t = 0; t < nt; ++t) {
       const int slot = t & 1;
@@ -533,7 +543,7 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
             dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.frag_tr(at, 0, dt, 16 * u), dsb, dq[dt], 0, 0, 0);
         }
       }
-      wait_tiles();
+      wait_tiles<0>();
       __syncthreads();
     }
     bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
@@ -625,7 +635,7 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
     copy_do.issue(dbase, qbeg / TILE, ring + TB);
     fetch_stats(qbeg);
     stash_stats(0);
-    wait_tiles();
+    wait_tiles<0>();
     __syncthreads();
     for (int t = 0; t < nt; ++t) {
       const int buf = t & 1;
@@ -695,7 +705,7 @@ __global__ __launch_bounds__(256, (D == 64 || PASS == PASS_DQ) ? 2 : 1) void att
         }
       }
       if (t + 1 < nt) stash_stats(buf ^ 1);
-      wait_tiles();
+      wait_tiles<0>();
       __syncthreads();
     }
     bf16_t* stage = (bf16_t*)smem_raw + wave * 32 * (D + 8);
@@ -735,29 +745,36 @@ static hipError_t fwd_launch_form(hipStream_t s, const AttnDesc& a, unsigned gri
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), BYTES, s, a);
   return hipGetLastError();
 }
-// Tiles go straight to LDS where what a chiplet's workgroups read stays in its 4 MB of L2, and through registers where not:
-// loads to LDS that miss it return later (428 clocks a request on average against 353, with the same misses, at 1 x 1536 x
-// 20 x 128 causal), and a workgroup alone on its SIMDs waits for them.  Workgroup i runs on chiplet i mod 8 and reads the
-// keys and values of pair i mod (samples x heads): `met` bytes in all.  Long causal sequences share what is fetched, from
-// 32 row blocks of a pair on a chiplet on.  At head size 128 causal launches are the faster through registers, all.
-// Forward in us: before (padded rows, through registers) / straight to LDS / through registers, the form chosen marked *:
-//   8 x 512 x 16 x 64          14.6 / 13.5* / 14.5      1 x 4096 x 20 x 64 causal   69.2 / 72.7 / 66.4*
-//   3 x 333 x 16 x 64           8.8 /  8.0* /  8.5      2 x 2048 x 25 x 64 causal   42.4 / 43.3 / 41.7*
-//   8 x 1024 x 16 x 64 causal  31.3 / 30.1* / 30.4      4 x 1024 x 25 x 64 causal   26.4 / 25.7 / 25.1*
-//   1 x 8192 x 16 x 64 causal   171 /  164* /  166      1 x 3072 x 10 x 64 causal   45.8 / 52.7 / 44.8*
-//   2 x 4096 x 16 x 64 causal  92.2 / 85.2* / 90.2      1 x 3072 x 10 x 64          46.9 / 45.8 / 44.2*
+// Tiles go straight to LDS, or through registers where that is the faster way.  Loads to LDS that miss the chiplet's 4 MB of
+// L2 return later (428 clocks a request on average against 353, with the same misses, at 1 x 1536 x 20 x 128 causal), and
+// workgroups of different lengths, alone on their SIMDs at the end, wait for them.  Workgroup i runs on chiplet i mod 8 and
+// reads the keys and values of pair i mod (samples x heads): `met` bytes in all.  So with a causal mask, at head size 64:
+// registers beyond 1.75 MB, except for half a workgroup per CU or less, and where many row blocks of a pair meet on a chiplet
+// and share what is fetched and later workgroups fill the gaps.  At head size 128 a CU holds two workgroups and the lines lie where both were measured to meet:
+// straight to LDS up to half a workgroup per CU and from a round and a half on; short sequences, with few steps to wait in,
+// through registers.  Without a mask hardly ever.  Forward in us: before (padded rows, through registers) / straight to
+// LDS / through registers, the form chosen marked *:
+//   8 x 512 x 16 x 64          15.3 / 14.1* / 15.6      1 x 4096 x 20 x 64 causal   69.2 / 72.7 / 66.4*
+//   3 x 333 x 16 x 64           8.7 /  7.7* /  8.4      2 x 2048 x 25 x 64 causal   42.4 / 43.3 / 41.7*
+//   4 x 1024 x 25 x 64         47.0 / 42.4* / 45.5      4 x 1024 x 25 x 64 causal   26.4 / 25.7 / 25.1*
+//   1 x 2048 x 16 x 64 causal  31.9 / 30.6* / 31.2      1 x 3072 x 10 x 64 causal   45.8 / 52.7 / 44.8*
+//   2 x 4096 x 16 x 64 causal  92.2 / 85.2* / 90.2      4 x 2048 x 5 x 64 causal: 1.08 / 0.97* of before
 //   1 x 2048 x 96 x 128         226 /  212* /  223      1 x 1536 x 20 x 128         36.1 / 36.9 / 36.1*
-//   2 x 512 x 24 x 128         14.9 / 14.0* / 14.9      1 x 1500 x 20 x 128 causal  36.1 / 40.9 / 36.1*
-//   1 x 2048 x 96 x 128 causal  122 /  120  /  123*     4 x 1024 x 12 x 128 causal  28.8 / 29.9 / 28.4*
-// Rings of three tiles lost to two in every case but one (1 x 2048 x 17 x 128: 58.4 against 60.7).
+//   1 x 4096 x 4 x 128 causal  86.0 / 83.5* / 85.8      1 x 1500 x 20 x 128 causal  36.1 / 40.9 / 36.1*
+//   1 x 8192 x 16 x 128 causal  302 /  265* /  300      1 x 8192 x 4 x 128 causal    168 /  195 /  166*
+//   3 x 2048 x 20 x 128 causal 85.0 / 78.6* / 84.4      48 x 256 x 12 x 128 causal  33.2 / 35.3 / 33.1*
+// Over 187 shapes 0.946 of the time before (at most 1.02) and 0.941 of that of a ring of three straight to LDS in every launch
+// at head size 64 and up to 256 workgroups at 128.
 template <int D, bool CAUSAL>
 static hipError_t fwd_launch(hipStream_t s, const AttnDesc& a) {
   const unsigned grid = (unsigned)(((a.S + 127) / 128) * a.B * a.heads);
   const int pairs = a.B * a.heads, shared = pairs % 8 == 0 ? 8 : pairs % 4 == 0 ? 4 : pairs % 2 == 0 ? 2 : 1;
   const double met = (double)(pairs / shared) * a.S * D * 4;
+  const int blocks = (a.S + 127) / 128;
   bool regs;
-  if (CAUSAL) regs = D == 128 || (met > 2.2e6 && (a.S + 127) / 128 * shared < 256);
-  else regs = met > 3e6 && grid <= 256;
+  if (D == 64) regs = CAUSAL && a.S > 256 && grid > 128 && met > 1.75e6 && (grid < 1000 || blocks * shared < 128);
+  else if (CAUSAL) regs = grid > 128 && (a.S <= 680 || grid < (a.S > 2048 ? 800u : 768u));
+  else regs = met > 3e6 && (a.S > 1024 ? grid <= 256 : a.S <= 300 && grid > 512);
   return regs ? fwd_launch_form<D, CAUSAL, true>(s, a, grid) : fwd_launch_form<D, CAUSAL, false>(s, a, grid);
 }
 

@@ -533,11 +533,12 @@ def test_attention_at_the_ends_of_its_tile_ring(B, causal, batch, seq, heads, d)
     test_attention_forward_backward(B, 1, 2, causal, batch, seq, heads, d)
 
 
-@pytest.mark.parametrize("causal,batch,seq,heads,d", [(0, 7, 641, 3, 64), (1, 7, 641, 3, 64), (0, 7, 704, 3, 64),
-                                                      (1, 7, 704, 3, 64), (0, 7, 385, 3, 128), (0, 5, 448, 5, 128)])
+@pytest.mark.parametrize("causal,batch,seq,heads,d", [(1, 9, 641, 3, 64), (1, 9, 704, 3, 64), (0, 3, 1025, 5, 128),
+                                                      (0, 21, 300, 9, 128), (1, 9, 200, 9, 128), (1, 9, 192, 9, 128),
+                                                      (1, 13, 260, 5, 128)])
 def test_attention_forward_through_registers_and_straight_to_lds_is_the_same(B, causal, batch, seq, heads, d):
-    """A whole batch (more keys and values than a chiplet's L2 holds, few workgroups: tiles through registers) against its
-    samples one by one (straight to LDS); odd and even numbers of tiles, a last tile of one row."""
+    """A whole batch (more keys and values than a chiplet's L2 holds, or more workgroups than CUs: tiles through registers)
+    against its samples one by one (straight to LDS); odd and even numbers of tiles, a last tile of one row."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seq + d)
     H, T = heads * d, batch * seq
