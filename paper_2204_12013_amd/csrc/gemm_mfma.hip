@@ -204,7 +204,8 @@ struct EpiOperands {
 // chunks of 8 would have it, each touched every other 16 bytes of twice as many cache lines.  A layer's four weight
 // gradients in one launch, before -> after: 2048 tokens of 12288 x 49152 7590 -> 7195 us, 4096 of 1024 x 4096 107 -> 103,
 // 2048 of the same 68 -> 63.5, 1024 of 1600 x 6400 99 -> 93.5, 128 of the same 52.5 -> 48.2; 4096 of 1600 x 6400 alone
-// 274 -> 281 (in the whole stage, traced in turn, 274.7 -> 277.5).  With plain loads, stores or both: 1-12 % slower but for the 12288-wide layer.
+// 274 -> 281 (in the whole stage, traced in turn, 274.7 -> 277.5).  With plain loads, stores or both: 1-12 % slower but for
+// the 12288-wide layer.
 __device__ __forceinline__ void accumulate4(const GemmDesc& d, int m, int n, const f32x4& acc, const f32x4& old) {
   f32x4 v;
 #pragma unroll

@@ -250,7 +250,8 @@ hipError_t launch_layernorm_fwd(hipStream_t s, int dtype, int T, int H, float ep
 // Lanes past the row's end re-read its last vector; their gain is zero and what they sum is not stored.
 // Launch to launch with cold operands: 4096 rows of 1024 12.0 -> 9.0 us, of 1600 with the residual 18.3 -> 15.5, 999 of 1024
 // 7.5 -> 5.3, 128 of 1024 6.2 -> 4.4 (before: four wavefronts, two rows per pass, 4-byte accesses in the reductions).  A
-// third of what is left is the launch and the first trip to memory, a fifth the reductions over the wavefronts.
+// third of what is left is the launch and the first trip to memory, a fifth the reductions over the wavefronts.  With four
+// bf16 vectors a lane and the column sums it spills two of its 256 registers.
 template <typename T, int NCH, bool ADD, bool COLSUM, int U>
 __global__ __launch_bounds__(512) void layernorm_bwd_fused_kernel(int T_rows, int H, int rows_per_block,
                                                                   const T* __restrict__ dout, const T* __restrict__ r,
@@ -385,9 +386,9 @@ __global__ __launch_bounds__(512) void layernorm_bwd_fused_kernel(int T_rows, in
 // for the two sums over a row, in the order of layernorm_bwd_kernel, hence its bits in dr; then one after the other by the
 // whole workgroup, a thread keeping its columns' sums, the next row on its way meanwhile.  From 5 vectors a lane, where the
 // columns' sums outgrow a wavefront's registers, to 24: 244 of 256 registers at three vectors a thread, with the residual and
-// the column sums.  bf16 without either, two launches / this: 2048 rows of 12288 63.5 / 46.0 us, of 3072 22.7 / 16.5, 128 rows of
-// 12288 26.0 / 19.2; at 16384 the launches take 104.  (With the two sums over a row formed by the whole workgroup 34.0, 15.6 and
-// 14.9, in another order.)
+// the column sums.  bf16 without either, two launches / this: 2048 rows of 12288 63.5 / 46.0 us, of 3072 22.7 / 16.5, 128
+// rows of 12288 26.0 / 19.2; at 16384 the launches take 104.  (With the two sums over a row formed by the whole workgroup
+// 34.0, 15.6 and 14.9, in another order.)
 constexpr int kWideThreads = 512;
 template <typename T, int NC, bool ADD, bool COLSUM>
 __global__ __launch_bounds__(kWideThreads) void layernorm_bwd_wide_kernel(int T_rows, int H, int rows_per_block,
